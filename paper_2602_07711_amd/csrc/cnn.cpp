@@ -36,7 +36,8 @@ long long cnn_direct_size(int Co, int Ci);
 hipError_t cnn_wgrad_1x1(const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci, int V, int B,
                          float *part, long long part_elems, float *dW, hipStream_t s);
 hipError_t cnn_wgrad_direct(int use_bf16, const float *g, long long g_bs, int Co, const float *in, long long in_bs,
-                            int Ci, int S, int B, float *part, long long part_elems, float *dW, hipStream_t s);
+                            int Ci, int S, int B, float *part, long long part_elems, float *bpart, float *dW, float *db,
+                            hipStream_t s);
 hipError_t cnn_pack_direct(int use_bf16, const float *W, int Co, int Ci, int transpose, void *wt, hipStream_t s);
 hipError_t cnn_features(const double *k2h, const double2 *fh, int halo, int nf, int S, double k0sq, double cs,
                         double fs, float *x, hipStream_t s);
@@ -84,7 +85,7 @@ struct helm_cnn {
     float *part = nullptr;
     long long part_elems = 0;
     double *mse_part = nullptr, *loss_dev = nullptr;
-    float *bias_part = nullptr;      // 64 slices per channel of the bias-gradient reduction
+    float *bias_part = nullptr;      // partial sums of the bias gradients
     double2 *pwork = nullptr;        // separable cubic prolongation intermediates (grown on demand)
     long long pwork_elems = 0;
 };
@@ -147,13 +148,13 @@ helm_status conv_bwd(helm_cnn &n, int l, View in, View g, View *gin, int B) {
     const int ci = LAYERS[l][0], co = LAYERS[l][1], taps = LAYERS[l][2], lev = LAYERS[l][4];
     const int S = S_of(n, lev);
     if (taps == 27) {
-        NTRY(cnn_wgrad_direct(n.bf16, g.p, g.bs, co, in.p, in.bs, ci, S, B, n.part, n.part_elems, n.grads + n.woff[l],
-                              n.stream));
+        NTRY(cnn_wgrad_direct(n.bf16, g.p, g.bs, co, in.p, in.bs, ci, S, B, n.part, n.part_elems, n.bias_part,
+                              n.grads + n.woff[l], n.grads + n.boff[l], n.stream));
     } else {
         NTRY(cnn_wgrad_1x1(g.p, g.bs, co, in.p, in.bs, ci, (int)V_of(n, lev), B, n.part, n.part_elems,
                            n.grads + n.woff[l], n.stream));
+        NTRY(cnn_bias_grad(g.p, g.bs, B, V_of(n, lev), co, n.bias_part, n.grads + n.boff[l], n.stream));
     }
-    NTRY(cnn_bias_grad(g.p, g.bs, B, V_of(n, lev), co, n.bias_part, n.grads + n.boff[l], n.stream));
     if (gin && taps == 27)
         NTRY(cnn_conv_direct(n.bf16, g.p, g.bs, co, S, n.wtT[l], n.COPt[l], nullptr, ci, gin->p, gin->bs, 0, B,
                              n.part, n.part_elems, n.stream));
@@ -309,7 +310,8 @@ helm_status helm_cnn_create(helm_cnn **out, int size, int max_batch, int bf16, u
     long long pe = 0;
     for (int l = 0; l < NL; ++l) pe = std::max(pe, 129LL * pad16(LAYERS[l][1]) * pad64(LAYERS[l][0] * LAYERS[l][2]));
     n->part_elems = pe;
-    if (nalloc(*n, &n->part, pe) || nalloc(*n, &n->bias_part, 64 * 64)) return fail(HELM_ENOMEM, "partials");
+    // bias partials: one value per output channel (at most 64) and tile group (at most 512)
+    if (nalloc(*n, &n->part, pe) || nalloc(*n, &n->bias_part, 64 * 512)) return fail(HELM_ENOMEM, "partials");
     long long mp = ((long long)2 * V_of(*n, 0) * max_batch + 255) / 256;
     if (nalloc(*n, &n->mse_part, mp) || nalloc(*n, &n->loss_dev, 1)) return fail(HELM_ENOMEM, "loss");
     // He-uniform initial weights (fan-in), zero biases, from a 64-bit LCG seeded by `seed`

@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdint>
 
 #include "helm_internal.h"
 
@@ -613,112 +614,313 @@ __global__ void k_pack_direct(const float *__restrict__ W, int Co, int Ci, int t
 }
 
 
-// Weight gradient of a 27-tap layer, dW[o][i][tap] = sum_{b,v} g[b][o][v] in[b][i][v + off(tap)]. A workgroup
-// (input-channel chunk ch, tile group tg) loops over the tiles tg, tg + G, ... of all samples; per tile it stages
-// g (COP rows x the tile's 256 voxels) and the chunk's input tile with halo in LDS. Wave w accumulates taps
-// w, w+4, ... as GEMMs with M = output channels, N = the chunk's 16 channels and K = voxels (16 per step: two
-// 8-voxel x-rows); the A fragment of a step is shared by the wave's taps. BF16 keeps the input tile in three
-// copies shifted by dx = 0, 1, 2 so each lane's four consecutive voxels are one aligned 8-byte read.
-// Partial sums per tile group: part[tg][o][i][tap] (o < Co, i < Ci), added in order by k_wgrad_direct_sum.
-constexpr int WG_GPAD = 8;
-template <typename T> struct WgLayout {
-    static constexpr int NSH = MT<T>::KL == 4 ? 3 : 1;      // shifted copies of the input tile
-    static constexpr int RW = MT<T>::KL == 4 ? DT_X : DH_X; // stored row width
+// Weight and bias gradient of a 27-tap layer, dW[o][i][tap] = sum_{b,v} g[b][o][v] in[b][i][v + off(tap)] and
+// db[o] = sum_{b,v} g[b][o][v]. Per tap this is a product with M = output channels, N = 16 input channels and
+// K = voxels. A workgroup (input-channel chunk ch, tile group tg) loops over consecutive TX x 4 x TZ tiles of all samples
+// and stages g and the input tile with its halo channel-first in LDS, so that a lane's four consecutive voxels are one
+// 8-byte read. A wave owns one block of 16 output rows and all 27 taps (4 / FR waves share the K rows of such a
+// block): the operands of the three taps of one (dz, dy) come from one 16-byte window of the input row, shifted in
+// registers, and the windows of six rows serve four output rows: 22 LDS reads for 108 products.
+// Bound: bringing g and the input to the CUs. The tiles take whole rows (TX = 64, 32 or 16 by the volume's width): with
+// rows of 16 voxels every 128-byte line was fetched for a part of it, and the 48 -> 16 layer at 4 x 64^3 read 1.7 GB
+// for its 268 MB.
+// At 4 x 64^3 in BF16 (the launch that sums the parts included): 48 -> 16 channels 232 us (before: one 8 x 8 x 4 tile at
+// a time with every load waiting for its own result, 4-byte loads and a scalar reduction, 720 us), 16 -> 16 at 84 us
+// (175 us), 96 -> 32 at 32^3 101 us (250 us), all layers of a training step 0.70 ms (1.95 ms).
+// Partial sums per tile group, part[tg][ch][tap][COP][16] and bpart[tg][o], are added in order by k_wgrad_sum.
+constexpr int WY = 4, WHY = WY + 2;                           // tile height, rows with halo
+template <typename T, int TX> struct WgTile {
+    static constexpr int TZ = (MT<T>::KL == 4 && TX == 64 ? 128 : 64) / TX, HZ = TZ + 2;   // 256 voxels, 512 in the widest
+    static constexpr int ROW = TX + 4;                        // stored row: halo at 1 and TX + 2, interior from 2
+    static constexpr int XCH = HZ * WHY * ROW + 8;            // channel strides: 4 mod 8 banks, so that the 16 channels
+    static constexpr int GCH = TX * WY * TZ + 8;              // of a quarter wave's reads share no bank
 };
 
-template <typename T, int FR>
-__global__ __launch_bounds__(256) void k_wgrad_direct(const float *__restrict__ g, long long g_bs, int Co,
-                                                      const float *__restrict__ in, long long in_bs, int Ci, int S,
-                                                      int B, int G, float *__restrict__ part) {
-    constexpr int KL = MT<T>::KL;
-    constexpr int COP = FR * 16;
-    constexpr int NSH = WgLayout<T>::NSH, RW = WgLayout<T>::RW;
-    constexpr int NT = 7;                                     // taps per wave (27 = 7 + 7 + 7 + 6)
-    __shared__ __attribute__((aligned(16))) T sG[COP][DT_X * DT_Y * DT_Z + WG_GPAD];
-    __shared__ __attribute__((aligned(16))) T sX[NSH][DCC][DH_Z][DH_Y][RW];
-    const int ch = blockIdx.x / G, tg = blockIdx.x % G;
+// pair (a, b) of operand values as stored
+__device__ __forceinline__ unsigned bf_pair(float a, float b) {
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    const v2bf r = {(__bf16)a, (__bf16)b};
+    unsigned u;
+    __builtin_memcpy(&u, &r, 4);
+    return u;
+}
+__device__ __forceinline__ void st_two(float *p, float a, float b) { p[0] = a; p[1] = b; }
+__device__ __forceinline__ void st_two(bf16 *p, float a, float b) { *reinterpret_cast<unsigned *>(p) = bf_pair(a, b); }
+__device__ __forceinline__ void st_one(float *p, float a) { *p = a; }
+__device__ __forceinline__ void st_one(bf16 *p, float a) { p->u = (unsigned short)bf_pair(a, 0.f); }
+
+// Value, or four consecutive values, of a row of length S from x on, zero where `in` is false or outside the row. The
+// loads are unconditional, from the row's start where the value is not wanted: under a branch each would wait for its
+// own result before the next is issued. V4: S and x are multiples of 4.
+__device__ __forceinline__ float row1(const float *row, int x, int S, bool in) {
+    const bool ok = in && (unsigned)x < (unsigned)S;
+    const float v = row[ok ? x : 0];
+    return ok ? v : 0.f;
+}
+template <bool V4> __device__ __forceinline__ float4 row4(const float *row, int x, int S, bool in) {
+    if constexpr (V4) {
+        const bool ok = in && (unsigned)x < (unsigned)S;
+        float4 v = *reinterpret_cast<const float4 *>(row + (ok ? x : 0));
+        v.x = ok ? v.x : 0.f;
+        v.y = ok ? v.y : 0.f;
+        v.z = ok ? v.z : 0.f;
+        v.w = ok ? v.w : 0.f;
+        return v;
+    } else {
+        return make_float4(row1(row, x, S, in), row1(row, x + 1, S, in), row1(row, x + 2, S, in), row1(row, x + 3, S, in));
+    }
+}
+
+// A lane's window of an input row, from two elements before its four voxels of the output row to two after, and the
+// products of one K step of 16 voxels (a: the lane's four values of g) for the three taps dx on it
+template <typename T> struct WgWin;
+template <> struct WgWin<bf16> {
+    uint2 lo, hi;
+    typedef uint2 av;
+    __device__ __forceinline__ void load(const bf16 *p) {
+        lo = *reinterpret_cast<const uint2 *>(p);
+        hi = *reinterpret_cast<const uint2 *>(p + 4);
+    }
+    __device__ __forceinline__ static av load_a(const bf16 *p) { return *reinterpret_cast<const uint2 *>(p); }
+    __device__ __forceinline__ void mul(const av &a, v4f *acc) const {
+        const unsigned m01 = __builtin_amdgcn_alignbit(lo.y, lo.x, 16), m12 = __builtin_amdgcn_alignbit(hi.x, lo.y, 16);
+        const unsigned m23 = __builtin_amdgcn_alignbit(hi.y, hi.x, 16);
+        const uint2 b[3] = {make_uint2(m01, m12), make_uint2(lo.y, hi.x), make_uint2(m12, m23)};
+        v4s a4, b4;
+        __builtin_memcpy(&a4, &a, 8);
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+            __builtin_memcpy(&b4, &b[dx], 8);
+            acc[dx] = MT<bf16>::mma(a4, b4, acc[dx]);
+        }
+    }
+};
+template <> struct WgWin<float> {
+    float w[6];
+    typedef float4 av;
+    __device__ __forceinline__ void load(const float *p) {
+        const float2 a = *reinterpret_cast<const float2 *>(p + 2), b = *reinterpret_cast<const float2 *>(p + 4);
+        w[0] = p[1]; w[1] = a.x; w[2] = a.y; w[3] = b.x; w[4] = b.y; w[5] = p[6];
+    }
+    __device__ __forceinline__ static av load_a(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+    __device__ __forceinline__ void mul(const av &a, v4f *acc) const {
+        const float as[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[dx] = MT<float>::mma(as[j], w[j + dx], acc[dx]);
+    }
+};
+
+template <typename T, int FR, int TX, bool V4>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && (FR == 1 || (FR == 2 && TX < 64)) ? 2 : 1))) void k_wgrad_direct(
+    const float *__restrict__ g, long long g_bs, int Co, const float *__restrict__ in, long long in_bs, int Ci, int S,
+    int B, int G, float *__restrict__ part, float *__restrict__ bpart) {
+    typedef WgTile<T, TX> W;
+    constexpr int TZ = W::TZ, HZ = W::HZ, ROW = W::ROW, XCH = W::XCH, GCH = W::GCH, NQ = TX / 4;
+    constexpr int COP = FR * 16, KS = 4 / FR;                 // K parts per row block
+    constexpr int ST = (DCC * XCH + COP * GCH) * (int)sizeof(T);
+    constexpr int RB = FR * (KS - 1) * 9 * 4 * 64 * 4;        // values passed on per reduction round
+    __shared__ __attribute__((aligned(16))) unsigned char sm[ST > RB ? ST : RB];
+    T *sX = reinterpret_cast<T *>(sm), *sG = sX + DCC * XCH;
+    const int nch = (Ci + DCC - 1) / DCC;
+    const int per = (nch * G + 7) / 8;
+    const int lin = (blockIdx.x % 8) * per + blockIdx.x / 8;  // neighbouring tile groups on one XCD
+    if (lin >= nch * G) return;
+    const int ch = lin % nch, tg = lin / nch;                 // the chunks of a tile group share its g
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ntx = (S + DT_X - 1) / DT_X, nty = (S + DT_Y - 1) / DT_Y, ntz = (S + DT_Z - 1) / DT_Z;
+    const int rg = wave % FR, ks = wave / FR;
+    const int ntx = (S + TX - 1) / TX, nty = (S + WY - 1) / WY, ntz = (S + TZ - 1) / TZ;
     const int tiles = ntx * nty * ntz;
     const int V = S * S * S;
-    v4f acc[NT][FR];
+    const int nc = Ci - ch * DCC < DCC ? Ci - ch * DCC : DCC;
+    v4f acc[27];
 #pragma unroll
-    for (int q = 0; q < NT; ++q)
+    for (int q = 0; q < 27; ++q) acc[q] = v4f{0, 0, 0, 0};
+    // this thread's quads of the tile of g: GQ quads of one channel are spread over a whole number of threads, so that
+    // its channels are fixed and their sums (the bias gradient) stay in registers
+    constexpr int GQ = NQ * WY * TZ, GP = 256 / GQ > 0 ? 256 / GQ : 1, GN = COP / GP;   // channels at a time, passes
+    float bs[GN];
 #pragma unroll
-        for (int f = 0; f < FR; ++f) acc[q][f] = v4f{0, 0, 0, 0};
-    for (int tt = tg; tt < B * tiles; tt += G) {
+    for (int q = 0; q < GN; ++q) bs[q] = 0.f;
+    static_assert(GQ * GP == 256 && GN * GP == COP, "256 threads take whole channels of g");
+    const int gq = tid % GQ, go = tid / GQ;
+    const int gx = (gq % NQ) * 4, gy = (gq / NQ) % WY, gz = gq / (NQ * WY);
+    // of the input tile: per channel XI interior quads, then two halo ends per row, whose value is the last or first of
+    // the quad beside the tile
+    constexpr int XI = HZ * WHY * NQ, XU = XI + 2 * HZ * WHY, XP = (XU + 255) / 256;
+    const int k4 = 4 * (lane >> 4);
+    const T *arow = sG + (rg * 16 + (lane & 15)) * GCH + k4;
+    const T *wrow = sX + (lane & 15) * XCH + k4;
+    const int total = B * tiles, each = (total + G - 1) / G;
+    const int t1 = (tg + 1) * each < total ? (tg + 1) * each : total;
+    for (int tt = tg * each; tt < t1; ++tt) {
         const int b = tt / tiles, t = tt % tiles;
-        const int x0 = (t % ntx) * DT_X, y0 = ((t / ntx) % nty) * DT_Y, z0 = (t / (ntx * nty)) * DT_Z;
+        const int x0 = (t % ntx) * TX, y0 = ((t / ntx) % nty) * WY, z0 = (t / (ntx * nty)) * TZ;
+        const float *ib = in + ((long long)b * in_bs + (long long)ch * DCC * V);
         const float *gb = g + (long long)b * g_bs;
-        const float *ib = in + (long long)b * in_bs;
-        __syncthreads();
-        for (int e = tid; e < COP * DT_X * DT_Y * DT_Z; e += 256) {
-            const int o = e / (DT_X * DT_Y * DT_Z), v = e % (DT_X * DT_Y * DT_Z);
-            const int gx = x0 + v % DT_X, gy = y0 + (v / DT_X) % DT_Y, gz = z0 + v / (DT_X * DT_Y);
-            float val = 0.f;
-            if (o < Co && gx < S && gy < S && gz < S) val = gb[(long long)o * V + (gz * S + gy) * S + gx];
-            sG[o][v] = MT<T>::cvt(val);
-        }
-        // input rows (c, hz, hy): the 10 values of x0-1 .. x0+8, stored once (FP32) or as three shifted 8-wide
-        // copies (BF16)
-        for (int rrow = tid; rrow < DCC * DH_Z * DH_Y; rrow += 256) {
-            const int c = rrow / (DH_Z * DH_Y), hz = (rrow / DH_Y) % DH_Z, hy = rrow % DH_Y;
-            const int ci = ch * DCC + c, gz = z0 + hz - 1, gy = y0 + hy - 1;
-            const bool rin = ci < Ci && (unsigned)gz < (unsigned)S && (unsigned)gy < (unsigned)S;
-            const float *rowp = ib + (long long)ci * V + ((long long)gz * S + gy) * S;
-            float r[DH_X];
-#pragma unroll
-            for (int hx = 0; hx < DH_X; ++hx) {
-                const int gx = x0 + hx - 1;
-                r[hx] = (rin && (unsigned)gx < (unsigned)S) ? rowp[gx] : 0.f;
-            }
-#pragma unroll
-            for (int sh = 0; sh < NSH; ++sh)
-#pragma unroll
-                for (int j = 0; j < RW; ++j) sX[sh][c][hz][hy][j] = MT<T>::cvt(r[j + sh]);
-        }
         __syncthreads();
 #pragma unroll 1
-        for (int ks = 0; ks < 16; ++ks) {                     // K-step: output plane ks/4, rows 2(ks%4), +1
-            const int oz = ks >> 2, oy = (ks & 3) * 2;
+        for (int p = 0; p < XP; ++p) {
+            const int u = tid + 256 * p;
+            const bool quad = u < XI, used = u < XU;
+            const int r = !used ? 0 : quad ? u / NQ : (u - XI) >> 1, xp = quad ? u % NQ : (u & 1);
+            const int z = z0 + r / WHY - 1, y = y0 + r % WHY - 1, x = x0 + (quad ? 4 * xp : (xp ? TX : -4));
+            const bool rin = used && (unsigned)z < (unsigned)S && (unsigned)y < (unsigned)S;
+            const float *row = ib + (rin ? ((long long)z * S + y) * S : 0);
+            float4 v[DCC];
 #pragma unroll
-            for (int sub = 0; sub < 4 / KL; ++sub) {
-                const int k = sub * 4 + KL * (lane >> 4);      // first voxel of this lane in the step
-                const int ky = oy + (k >> 3), kx = k & 7;
-                typename MT<T>::op af[FR];
+            for (int c = 0; c < DCC; ++c) v[c] = row4<V4>(row + (long long)(c < nc ? c : 0) * V, x, S, rin && c < nc);
+            T *d = sX + r * ROW + (quad ? 2 + 4 * xp : 1 + (TX + 1) * xp);
+            if (quad) {
 #pragma unroll
-                for (int f = 0; f < FR; ++f)
-                    af[f] = load_op<T>(&sG[f * 16 + (lane & 15)][(oz * DT_Y + ky) * DT_X + kx]);
-                const int i = lane & 15;
+                for (int c = 0; c < DCC; ++c) {
+                    st_two(d + c * XCH, v[c].x, v[c].y);
+                    st_two(d + c * XCH + 2, v[c].z, v[c].w);
+                }
+            } else if (used) {
 #pragma unroll
-                for (int q = 0; q < NT; ++q) {
-                    const int tap = wave + 4 * q;
-                    if (tap < 27) {
-                        const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-                        const T *bp = (NSH == 3) ? &sX[dx][i][oz + dz][ky + dy][kx]
-                                                 : &sX[0][i][oz + dz][ky + dy][kx + dx];
-                        const typename MT<T>::op bf = load_op<T>(bp);
+                for (int c = 0; c < DCC; ++c) st_one(d + c * XCH, xp ? v[c].x : v[c].w);
+            }
+        }
+        {
+            const int z = z0 + gz, y = y0 + gy;
+            const bool rin = z < S && y < S;
+            const float *row = gb + (rin ? ((long long)z * S + y) * S : 0);
+            T *d = sG + go * GCH + gq * 4;
+            constexpr int GB = GN < 16 ? GN : 16;             // loads in flight
 #pragma unroll
-                        for (int f = 0; f < FR; ++f) acc[q][f] = MT<T>::mma(af[f], bf, acc[q][f]);
-                    }
+            for (int q0 = 0; q0 < GN; q0 += GB) {
+                float4 v[GB];
+#pragma unroll
+                for (int q = 0; q < GB; ++q) {
+                    const int o = go + GP * (q0 + q);
+                    v[q] = row4<V4>(row + (long long)(o < Co ? o : 0) * V, x0 + gx, S, rin && o < Co);
+                }
+#pragma unroll
+                for (int q = 0; q < GB; ++q) {
+                    bs[q0 + q] += (v[q].x + v[q].y) + (v[q].z + v[q].w);
+                    st_two(d + GP * (q0 + q) * GCH, v[q].x, v[q].y);
+                    st_two(d + GP * (q0 + q) * GCH + 2, v[q].z, v[q].w);
+                }
+            }
+        }
+        __syncthreads();
+        // segments of four rows and 16 columns of one plane; the six windows of the next (segment, dz) are read while
+        // the 36 products of this one run
+        constexpr int NS = TZ * (TX / 16);
+        typename WgWin<T>::av av[4];
+        WgWin<T> win[2][6];
+        auto rows = [&](int sg) { return (sg / (TX / 16)) * WHY * ROW + (sg % (TX / 16)) * 16; };
+#pragma unroll
+        for (int y = 0; y < 6; ++y) win[0][y].load(wrow + rows(ks) + y * ROW);
+#pragma unroll 1
+        for (int sg = ks; sg < NS; sg += KS) {
+            const T *a = arow + (sg / (TX / 16)) * WY * TX + (sg % (TX / 16)) * 16;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) av[y] = WgWin<T>::load_a(a + y * TX);
+            const T *w = wrow + rows(sg), *wn = wrow + rows(sg + KS < NS ? sg + KS : sg);
+#pragma unroll
+            for (int dz = 0; dz < 3; ++dz) {
+                const T *nx = dz < 2 ? w + (dz + 1) * WHY * ROW : wn;
+#pragma unroll
+                for (int y = 0; y < 6; ++y) win[(dz + 1) & 1][y].load(nx + y * ROW);
+#pragma unroll
+                for (int y = 0; y < 4; ++y)
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy) win[dz & 1][y + dy].mul(av[y], acc + (dz * 3 + dy) * 3);
+            }
+#pragma unroll
+            for (int y = 0; y < 6; ++y) win[0][y] = win[1][y];
+        }
+    }
+    // add the K parts of a row block in order (nine taps a round), then write it
+    if constexpr (KS > 1) {
+        float *red = reinterpret_cast<float *>(sm);
+#pragma unroll
+        for (int rnd = 0; rnd < 3; ++rnd) {
+            __syncthreads();
+            // KS - 1 slots per row block: FR (KS - 1) <= 3
+            if (ks > 0) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) red[((rg * (KS - 1) + ks - 1) * 36 + q * 4 + r) * 64 + lane] = acc[rnd * 9 + q][r];
+            }
+            __syncthreads();
+            if (ks == 0) {
+#pragma unroll
+                for (int k = 0; k < KS - 1; ++k)
+#pragma unroll
+                    for (int q = 0; q < 9; ++q)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[rnd * 9 + q][r] += red[((rg * (KS - 1) + k) * 36 + q * 4 + r) * 64 + lane];
+            }
+        }
+    }
+    if (ks == 0) {
+        float *pp = part + ((long long)tg * nch + ch) * 27 * COP * DCC + (rg * 16 + k4) * DCC + (lane & 15);
+#pragma unroll
+        for (int q = 0; q < 27; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pp[(q * COP + r) * DCC] = acc[q][r];
+    }
+    if (ch == 0) {                                            // the bias: every channel's sums over its GQ threads
+        float *red = reinterpret_cast<float *>(sm);
+#pragma unroll
+        for (int q = 0; q < GN; ++q) {
+            float v = bs[q];
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+            if constexpr (GQ == 64) {
+                if (lane == 0) bpart[(long long)tg * COP + go + GP * q] = v;
+            } else {
+                __syncthreads();
+                if (lane == 0) red[wave] = v;
+                __syncthreads();
+                if (tid < GP) {
+                    float s = red[tid * (GQ / 64)];
+                    for (int k = 1; k < GQ / 64; ++k) s += red[tid * (GQ / 64) + k];
+                    bpart[(long long)tg * COP + tid + GP * q] = s;
                 }
             }
         }
     }
-    // acc[q][f][r] = dW[o = 16 f + 4 (lane/16) + r][i = lane % 16][tap = wave + 4 q]
-    const int i = ch * DCC + (lane & 15);
-#pragma unroll
-    for (int q = 0; q < NT; ++q) {
-        const int tap = wave + 4 * q;
-        if (tap >= 27 || i >= Ci) continue;
-#pragma unroll
-        for (int f = 0; f < FR; ++f)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int o = f * 16 + 4 * (lane >> 4) + r;
-                if (o < Co) part[(((long long)tg * Co + o) * Ci + i) * 27 + tap] = acc[q][f][r];
-            }
+}
+
+// dW and db from the tile groups' partial sums: a block takes 16 consecutive partial values e (64 B rows), thread
+// (e, j) adds the groups j, j + 16, ..., and the 16 sums are added in order. The last blocks take the bias.
+__global__ __launch_bounds__(256) void k_wgrad_sum(const float *__restrict__ part, const float *__restrict__ bpart,
+                                                   int G, int Co, int COP, int Ci, float *__restrict__ dW,
+                                                   float *__restrict__ db) {
+    __shared__ float sm[16][17];
+    const int el = threadIdx.x & 15, j = threadIdx.x >> 4;
+    const int nch = (Ci + DCC - 1) / DCC;
+    const int nb = nch * 27 * COP;                            // blocks of weights, one (chunk, tap, o) each
+    const bool bias = (int)blockIdx.x >= nb;
+    const long long n = bias ? COP : (long long)nb * DCC;
+    const float *src = bias ? bpart + ((int)blockIdx.x - nb) * 16 + el : part + (long long)blockIdx.x * 16 + el;
+    float s = 0.f;
+    int q = j;
+    for (; q + 48 < G; q += 64) {
+        const float a = src[q * n], b = src[(q + 16) * n], c = src[(q + 32) * n], d = src[(q + 48) * n];
+        s += a;
+        s += b;
+        s += c;
+        s += d;
     }
+    for (; q < G; q += 16) s += src[q * n];
+    sm[j][el] = s;
+    __syncthreads();
+    if (j) return;
+    s = sm[0][el];
+    for (int k = 1; k < 16; ++k) s += sm[k][el];
+    if (bias) {
+        const int o = ((int)blockIdx.x - nb) * 16 + el;
+        if (o < Co) db[o] = s;
+        return;
+    }
+    const int o = blockIdx.x % COP, tap = (blockIdx.x / COP) % 27, i = blockIdx.x / (COP * 27) * DCC + el;
+    if (o < Co && i < Ci) dW[((long long)o * Ci + i) * 27 + tap] = s;
 }
 
 // dW[e] = sum_q part[q][e], q = 0..G-1: a block takes 64 consecutive e; thread (e, j) adds q = j, j + 4, ...
@@ -858,27 +1060,58 @@ hipError_t cnn_conv_direct(int use_bf16, const float *in, long long in_bs, int C
                     : cnn_conv_direct_t<float>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, part, part_elems, s);
 }
 
-template <typename T>
-hipError_t cnn_wgrad_direct_t(const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci, int S,
-                              int B, float *part, long long part_elems, float *dW, hipStream_t s) {
-    const int tiles = ((S + DT_X - 1) / DT_X) * ((S + DT_Y - 1) / DT_Y) * ((S + DT_Z - 1) / DT_Z);
-    const int nchunk = (Ci + DCC - 1) / DCC;
-    const long long per = (long long)Co * Ci * 27;
-    long long G = std::max<long long>(1, std::min<long long>((long long)B * tiles, (1024 + nchunk - 1) / nchunk));
-    G = std::min<long long>(G, part_elems / per);
+// Tile groups of a weight gradient: about 512 workgroups (two per CU are resident), every group with the same number of
+// consecutive tiles up to one. A group writes partial sums as large as the layer's weights, which the last kernel reads
+// again: so at least two tiles per group where there are enough, and half as many groups for few tiles and many chunks
+// (128 -> 64 channels at 16^3: 56 MB of partial sums with 512 workgroups).
+int cnn_wgrad_groups(int Ci, int B, int tiles_of_one) {
+    const int tiles = B * tiles_of_one;
+    const int nch = (Ci + DCC - 1) / DCC;
+    const int want = std::max(1, (nch <= 2 || tiles >= 512 ? 512 : 256) / nch);
+    const int each = std::max(tiles >= 512 ? 2 : 1, (tiles + want - 1) / want);
+    return (tiles + each - 1) / each;
+}
+
+template <typename T, int FR, int TX>
+hipError_t wgrad_launch(hipStream_t s, const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci,
+                        int S, int B, float *part, long long part_elems, float *bpart, float *dW, float *db) {
+    constexpr int COP = FR * 16, TZ = WgTile<T, TX>::TZ;
+    const int nch = (Ci + DCC - 1) / DCC;
+    const int tiles = ((S + TX - 1) / TX) * ((S + WY - 1) / WY) * ((S + TZ - 1) / TZ);
+    const long long per = (long long)nch * 27 * COP * DCC;
+    const int G = (int)std::min<long long>(cnn_wgrad_groups(Ci, B, tiles), part_elems / per);
     if (G < 1) return hipErrorInvalidValue;
-    const int COP = (Co + 15) / 16 * 16;
-    const unsigned grid = (unsigned)(nchunk * G);
-    switch (COP / 16) {
-    case 1: hipLaunchKernelGGL((k_wgrad_direct<T, 1>), dim3(grid), dim3(256), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, (int)G, part); break;
-    case 2: hipLaunchKernelGGL((k_wgrad_direct<T, 2>), dim3(grid), dim3(256), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, (int)G, part); break;
-    case 4: hipLaunchKernelGGL((k_wgrad_direct<T, 4>), dim3(grid), dim3(256), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, (int)G, part); break;
-    default: return hipErrorInvalidValue;
-    }
+    const unsigned grid = (unsigned)((nch * G + 7) / 8 * 8);
+    // 16-byte loads need every row 16-byte aligned
+    if (S % 4 == 0 && ((uintptr_t)g | (uintptr_t)in) % 16 == 0 && (g_bs | in_bs) % 4 == 0)
+        hipLaunchKernelGGL((k_wgrad_direct<T, FR, TX, true>), dim3(grid), dim3(256), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, G, part, bpart);
+    else
+        hipLaunchKernelGGL((k_wgrad_direct<T, FR, TX, false>), dim3(grid), dim3(256), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, G, part, bpart);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad_direct_sum, dim3((unsigned)((per + 63) / 64)), dim3(256), 0, s, part, (int)G, per, dW);
+    hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)(nch * 27 * COP + COP / 16)), dim3(256), 0, s, part, bpart, G, Co, COP,
+                       Ci, dW, db);
     return hipGetLastError();
+}
+
+template <typename T, int FR>
+hipError_t wgrad_width(hipStream_t s, const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci,
+                       int S, int B, float *part, long long part_elems, float *bpart, float *dW, float *db) {
+    if (S > 32) return wgrad_launch<T, FR, 64>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+    if (S > 16) return wgrad_launch<T, FR, 32>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+    return wgrad_launch<T, FR, 16>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+}
+
+template <typename T>
+hipError_t cnn_wgrad_direct_t(const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci, int S,
+                              int B, float *part, long long part_elems, float *bpart, float *dW, float *db,
+                              hipStream_t s) {
+    switch ((Co + 15) / 16) {
+    case 1: return wgrad_width<T, 1>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+    case 2: return wgrad_width<T, 2>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+    case 4: return wgrad_width<T, 4>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t cnn_wgrad_1x1(const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci, int V, int B,
@@ -896,9 +1129,10 @@ hipError_t cnn_wgrad_1x1(const float *g, long long g_bs, int Co, const float *in
 }
 
 hipError_t cnn_wgrad_direct(int use_bf16, const float *g, long long g_bs, int Co, const float *in, long long in_bs,
-                            int Ci, int S, int B, float *part, long long part_elems, float *dW, hipStream_t s) {
-    return use_bf16 ? cnn_wgrad_direct_t<bf16>(g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, dW, s)
-                    : cnn_wgrad_direct_t<float>(g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, dW, s);
+                            int Ci, int S, int B, float *part, long long part_elems, float *bpart, float *dW, float *db,
+                            hipStream_t s) {
+    return use_bf16 ? cnn_wgrad_direct_t<bf16>(g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db, s)
+                    : cnn_wgrad_direct_t<float>(g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db, s);
 }
 
 long long cnn_direct_size(int Co, int Ci) { return (long long)((Ci + DCC - 1) / DCC) * 27 * ((Co + 15) / 16 * 16) * DCC; }
