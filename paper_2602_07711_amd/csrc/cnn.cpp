@@ -30,8 +30,7 @@ hipError_t cnn_adam(float *w, const float *g, float *m, float *v, long long n, f
 hipError_t cnn_prolong(const float *coarse, int nc, double scale, double gre, double gim, int cubic, double2 *fine,
                        int nf, double2 *work, hipStream_t s);
 hipError_t cnn_conv_direct(int use_bf16, const float *in, long long in_bs, int Ci, int S, const void *wt, int COP,
-                           const float *bias, int Co, float *out, long long out_bs, int relu, int B, float *part,
-                           long long part_elems, hipStream_t s);
+                           const float *bias, int Co, float *out, long long out_bs, int relu, int B, hipStream_t s);
 long long cnn_direct_size(int Co, int Ci);
 hipError_t cnn_wgrad_1x1(const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci, int V, int B,
                          float *part, long long part_elems, float *dW, hipStream_t s);
@@ -136,7 +135,7 @@ helm_status conv_fwd(helm_cnn &n, int l, View in, View out, int B) {
     const int ci = LAYERS[l][0], co = LAYERS[l][1], taps = LAYERS[l][2], relu = LAYERS[l][3];
     if (taps == 27)
         NTRY(cnn_conv_direct(n.bf16, in.p, in.bs, ci, S_of(n, LAYERS[l][4]), n.wt[l], n.COP[l], n.params + n.boff[l],
-                             co, out.p, out.bs, relu, B, n.part, n.part_elems, n.stream));
+                             co, out.p, out.bs, relu, B, n.stream));
     else
         NTRY(cnn_conv_fwd(n.bf16, in.p, in.bs, ci, S_of(n, LAYERS[l][4]), taps, n.wt[l], n.Kp[l], n.COP[l],
                           n.params + n.boff[l], co, out.p, out.bs, relu, B, n.stream));
@@ -157,7 +156,7 @@ helm_status conv_bwd(helm_cnn &n, int l, View in, View g, View *gin, int B) {
     }
     if (gin && taps == 27)
         NTRY(cnn_conv_direct(n.bf16, g.p, g.bs, co, S, n.wtT[l], n.COPt[l], nullptr, ci, gin->p, gin->bs, 0, B,
-                             n.part, n.part_elems, n.stream));
+                             n.stream));
     else if (gin)
         NTRY(cnn_conv_fwd(n.bf16, g.p, g.bs, co, S, taps, n.wtT[l], n.Kpt[l], n.COPt[l], nullptr, ci, gin->p, gin->bs,
                           0, B, n.stream));

@@ -470,172 +470,6 @@ __global__ void k_features(const double *__restrict__ k2h, const double2 *__rest
 }
 
 
-// ---------------------------------------------------------------------------------------------- direct 3x3x3
-// Direct convolution for the 27-tap layers: a workgroup owns an 8 x 8 x 4 output tile (one 8 x 8 plane per wave,
-// four 16-voxel MFMA column blocks each) and all output channels (COP rows). Per chunk of 16 input channels the
-// input tile with its one-voxel halo (10 x 10 x 6) is staged once in LDS, channel-last in the operand type, so the
-// B fragment of tap (dz, dy, dx) is one LDS read at the shifted voxel. Weights are packed as
-// wt[chunk][tap][COP][16] and read as A fragments straight from global memory (each 64-lane read is one
-// contiguous 512 B block shared by every wave and workgroup).
-constexpr int DT_X = 8, DT_Y = 8, DT_Z = 4;
-constexpr int DH_X = DT_X + 2, DH_Y = DT_Y + 2, DH_Z = DT_Z + 2;
-constexpr int DH_V = DH_X * DH_Y * DH_Z;
-constexpr int DCC = 16;                    // input channels per chunk
-constexpr int DPAD = 4;                    // LDS row padding (elements)
-
-// Work split: a workgroup covers one tile, FR row blocks (16 output channels each) starting at row block rg*FR,
-// and the input-channel chunks [ks*cpb, (ks+1)*cpb). With one K split (nsplit = 1) it applies bias and ReLU and
-// writes the output; otherwise it writes FP32 partial sums part[ks][b][co][v] that k_conv_split_sum adds in order.
-template <typename T, int FR>
-__global__ __launch_bounds__(256) void k_conv_direct(const float *__restrict__ in, long long in_bs, int Ci, int S,
-                                                     const T *__restrict__ wt, int COP, const float *__restrict__ bias,
-                                                     int Co, float *__restrict__ out, long long out_bs, int relu,
-                                                     int rowgroups, int nsplit, int cpb, float *__restrict__ part,
-                                                     int B) {
-    constexpr int KL = MT<T>::KL;
-    __shared__ __attribute__((aligned(16))) T sIn[DH_V][DCC + DPAD];
-    const int ntx = (S + DT_X - 1) / DT_X, nty = (S + DT_Y - 1) / DT_Y, ntz = (S + DT_Z - 1) / DT_Z;
-    const int tiles = ntx * nty * ntz;
-    int idx = blockIdx.x;
-    const int ks = idx % nsplit;
-    idx /= nsplit;
-    const int rg = idx % rowgroups;
-    idx /= rowgroups;
-    const int t = idx % tiles, b = idx / tiles;
-    const int x0 = (t % ntx) * DT_X, y0 = ((t / ntx) % nty) * DT_Y, z0 = (t / (ntx * nty)) * DT_Z;
-    const int row0 = rg * FR * 16;
-    const float *inb = in + (long long)b * in_bs;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int V = S * S * S;
-    v4f acc[FR][4];
-#pragma unroll
-    for (int f = 0; f < FR; ++f)
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) acc[f][nb] = v4f{0, 0, 0, 0};
-    const int nchunk = (Ci + DCC - 1) / DCC;
-    const int c_lo = ks * cpb, c_hi = min(nchunk, c_lo + cpb);
-    for (int ch = c_lo; ch < c_hi; ++ch) {
-        __syncthreads();
-        // the tile's loads are issued in groups of eight before their LDS stores, so they overlap
-        constexpr int NIT = (DCC * DH_V + 255) / 256;
-#pragma unroll 8
-        for (int it = 0; it < NIT; ++it) {
-            const int e = tid + it * 256;
-            if (e < DCC * DH_V) {
-                const int c = e / DH_V, v = e - c * DH_V;
-                const int hx = v % DH_X, hy = (v / DH_X) % DH_Y, hz = v / (DH_X * DH_Y);
-                const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
-                const int ci = ch * DCC + c;
-                float val = 0.f;
-                if (ci < Ci && (unsigned)gx < (unsigned)S && (unsigned)gy < (unsigned)S && (unsigned)gz < (unsigned)S)
-                    val = inb[(long long)ci * V + (gz * S + gy) * S + gx];
-                sIn[v][c] = MT<T>::cvt(val);
-            }
-        }
-        __syncthreads();
-        const T *wc = wt + (long long)ch * 27 * COP * DCC;
-        for (int tap = 0; tap < 27; ++tap) {
-            const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-#pragma unroll
-            for (int kk = 0; kk < DCC; kk += 4 * KL) {
-                const int kofs = kk + KL * (lane >> 4);
-                typename MT<T>::op af[FR];
-#pragma unroll
-                for (int f = 0; f < FR; ++f)
-                    af[f] = load_op<T>(wc + ((long long)tap * COP + row0 + f * 16 + (lane & 15)) * DCC + kofs);
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb) {
-                    const int n = nb * 16 + (lane & 15);
-                    const int hv = ((wave + dz) * DH_Y + (n / DT_X + dy)) * DH_X + (n % DT_X + dx);
-                    const typename MT<T>::op bf = load_op<T>(&sIn[hv][kofs]);
-#pragma unroll
-                    for (int f = 0; f < FR; ++f) acc[f][nb] = MT<T>::mma(af[f], bf, acc[f][nb]);
-                }
-            }
-        }
-    }
-    const int gz = z0 + wave;
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-        const int n = nb * 16 + (lane & 15);
-        const int gx = x0 + n % DT_X, gy = y0 + n / DT_X;
-        const bool ok = gx < S && gy < S && gz < S;
-        const long long vo = ((long long)gz * S + gy) * S + gx;
-#pragma unroll
-        for (int f = 0; f < FR; ++f)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int co = row0 + f * 16 + 4 * (lane >> 4) + r;
-                if (!ok || co >= Co) continue;
-                if (nsplit == 1) {
-                    float y = acc[f][nb][r] + (bias ? bias[co] : 0.f);
-                    if (relu) y = fmaxf(y, 0.f);
-                    out[(long long)b * out_bs + (long long)co * V + vo] = y;
-                } else {
-                    part[(((long long)ks * B + b) * Co + co) * V + vo] = acc[f][nb][r];
-                }
-            }
-    }
-}
-
-// out[b][co][v] = act(bias[co] + sum_ks part[ks][b][co][v]) in split order
-__global__ void k_conv_split_sum(const float *__restrict__ part, int nsplit, int B, int Co, int V,
-                                 const float *__restrict__ bias, int relu, float *__restrict__ out, long long out_bs) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    const long long per = (long long)Co * V;
-    if (i >= per * B) return;
-    const int b = (int)(i / per);
-    const long long o = i - (long long)b * per;
-    const int co = (int)(o / V);
-    float s = bias ? bias[co] : 0.f;
-    for (int k = 0; k < nsplit; ++k) s += part[((long long)k * B + b) * per + o];
-    if (relu) s = fmaxf(s, 0.f);
-    out[(long long)b * out_bs + o] = s;
-}
-
-// direct-format weights wt[chunk][tap][COP][16] of a conv with Co outputs and Ci inputs; transpose = 1 takes
-// them from a layer W[Ci][Co][27] with the tap mirrored (the data-gradient convolution of that layer)
-template <typename T>
-__global__ void k_pack_direct(const float *__restrict__ W, int Co, int Ci, int transpose, int COP, long long total,
-                              T *__restrict__ wt) {
-    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (e >= total) return;
-    const int cc = (int)(e % DCC);
-    long long r = e / DCC;
-    const int o = (int)(r % COP);
-    r /= COP;
-    const int tap = (int)(r % 27);
-    const int ch = (int)(r / 27);
-    const int i = ch * DCC + cc;
-    float v = 0.f;
-    if (o < Co && i < Ci)
-        v = transpose ? W[((long long)i * Co + o) * 27 + (26 - tap)] : W[((long long)o * Ci + i) * 27 + tap];
-    wt[e] = MT<T>::cvt(v);
-}
-
-
-// Weight and bias gradient of a 27-tap layer, dW[o][i][tap] = sum_{b,v} g[b][o][v] in[b][i][v + off(tap)] and
-// db[o] = sum_{b,v} g[b][o][v]. Per tap this is a product with M = output channels, N = 16 input channels and
-// K = voxels. A workgroup (input-channel chunk ch, tile group tg) loops over consecutive TX x 4 x TZ tiles of all samples
-// and stages g and the input tile with its halo channel-first in LDS, so that a lane's four consecutive voxels are one
-// 8-byte read. A wave owns one block of 16 output rows and all 27 taps (4 / FR waves share the K rows of such a
-// block): the operands of the three taps of one (dz, dy) come from one 16-byte window of the input row, shifted in
-// registers, and the windows of six rows serve four output rows: 22 LDS reads for 108 products.
-// Bound: bringing g and the input to the CUs. The tiles take whole rows (TX = 64, 32 or 16 by the volume's width): with
-// rows of 16 voxels every 128-byte line was fetched for a part of it, and the 48 -> 16 layer at 4 x 64^3 read 1.7 GB
-// for its 268 MB.
-// At 4 x 64^3 in BF16 (the launch that sums the parts included): 48 -> 16 channels 232 us (before: one 8 x 8 x 4 tile at
-// a time with every load waiting for its own result, 4-byte loads and a scalar reduction, 720 us), 16 -> 16 at 84 us
-// (175 us), 96 -> 32 at 32^3 101 us (250 us), all layers of a training step 0.70 ms (1.95 ms).
-// Partial sums per tile group, part[tg][ch][tap][COP][16] and bpart[tg][o], are added in order by k_wgrad_sum.
-constexpr int WY = 4, WHY = WY + 2;                           // tile height, rows with halo
-template <typename T, int TX> struct WgTile {
-    static constexpr int TZ = (MT<T>::KL == 4 && TX == 64 ? 128 : 64) / TX, HZ = TZ + 2;   // 256 voxels, 512 in the widest
-    static constexpr int ROW = TX + 4;                        // stored row: halo at 1 and TX + 2, interior from 2
-    static constexpr int XCH = HZ * WHY * ROW + 8;            // channel strides: 4 mod 8 banks, so that the 16 channels
-    static constexpr int GCH = TX * WY * TZ + 8;              // of a quarter wave's reads share no bank
-};
-
 // pair (a, b) of operand values as stored
 __device__ __forceinline__ unsigned bf_pair(float a, float b) {
     typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
@@ -670,6 +504,328 @@ template <bool V4> __device__ __forceinline__ float4 row4(const float *row, int 
         return make_float4(row1(row, x, S, in), row1(row, x + 1, S, in), row1(row, x + 2, S, in), row1(row, x + 3, S, in));
     }
 }
+
+// ---------------------------------------------------------------------------------------------- direct 3x3x3
+// Direct convolution for the 27-tap layers. A workgroup owns a tile of TX x 4 x TZ voxels and FR blocks of 16 output
+// channels. Per chunk of 16 input channels the tile with its one-voxel halo is staged once in LDS, channel-last in the
+// operand type; a wave owns the four rows of 16-voxel column blocks of a plane and reads, per dz, the 18 operands of
+// their six input rows and three shifts, which serve 36 products per row block. Weights are packed as
+// wt[chunk][tap][COP][16] and read as A fragments from global memory (512 contiguous bytes that every wave shares).
+// The tiles take whole rows (TX = 64, 32 or 16 by the volume's width), so that a 128-byte line is fetched for all of
+// its voxels, and a thread stages four voxels of four channels with loads that are all in flight.
+// At 4 x 64^3 in BF16: 16 -> 16 channels 73 us (before: 8 x 8 x 4 tiles staged element by element and every product's
+// weights waited for, 110 us), 48 -> 16 at 168 us (319 us), 96 -> 32 at 32^3 62 us (168 us); bound by the staging's
+// latency and its reads (1.8 TB/s of input at 16 -> 16), not by the products (12 us there).
+// Every output's products are added in the order chunk, tap, channel.
+constexpr int DCC = 16;                    // input channels per chunk
+constexpr int CY = 4, CHY = CY + 2;        // tile height, rows with halo
+// LDS place, in groups of four channels, of voxel v (halo at 3 and TX + 4, interior from 4) of a row, quarter q: eight
+// bytes of padding after every four voxels spread the staging's stores over the banks
+__host__ __device__ constexpr int c_at(int v, int q) { return 4 * v + (v >> 2) + q - 12; }
+template <int TX, int TZ> struct ConvTile {
+    static constexpr int ROWS = (TZ + 2) * CHY, PITCH = c_at(TX + 4, 3) + 1, QUADS = ROWS * PITCH;
+};
+
+// four channels of a voxel in the operand type. BF16: group q holds channels 4q .. 4q + 3, the operand of one product
+// over 16 channels. FP32: group q holds channels q, 4 + q, 8 + q, 12 + q, the operands of four products of four.
+template <typename T> struct Chan;
+template <> struct Chan<bf16> {
+    typedef uint2 t;
+    __device__ __forceinline__ static int ch(int q, int j) { return 4 * q + j; }
+    __device__ __forceinline__ static t make(float a, float b, float c, float d) { return make_uint2(bf_pair(a, b), bf_pair(c, d)); }
+    __device__ __forceinline__ static v4f mul(const t &a, const t &b, v4f acc) {
+        v4s x, y;
+        __builtin_memcpy(&x, &a, 8);
+        __builtin_memcpy(&y, &b, 8);
+        return MT<bf16>::mma(x, y, acc);
+    }
+};
+template <> struct Chan<float> {
+    typedef float4 t;
+    __device__ __forceinline__ static int ch(int q, int j) { return 4 * j + q; }
+    __device__ __forceinline__ static t make(float a, float b, float c, float d) { return make_float4(a, b, c, d); }
+    __device__ __forceinline__ static v4f mul(const t &a, const t &b, v4f acc) {
+        acc = MT<float>::mma(a.x, b.x, acc);
+        acc = MT<float>::mma(a.y, b.y, acc);
+        acc = MT<float>::mma(a.z, b.z, acc);
+        return MT<float>::mma(a.w, b.w, acc);
+    }
+};
+
+// Stage one chunk of the tile at (x0, y0, z0), by NT threads (t = 0 .. NT - 1): units of four voxels and four channels
+// of a row, then the halo ends of the rows. nc: channels of the chunk that exist. V4: rows are 16-byte aligned and
+// a multiple of four voxels.
+template <typename T, int TX, int TZ, int NT, bool V4>
+__device__ __forceinline__ void conv_stage_rows(typename Chan<T>::t *sI, const float *in, int nc, int S, int V, int x0,
+                                                int y0, int z0, int t) {
+    typedef Chan<T> C;
+    constexpr int ROWS = ConvTile<TX, TZ>::ROWS, PITCH = ConvTile<TX, TZ>::PITCH, NQ = TX / 4;
+    constexpr int NI = ROWS * NQ * 4, NH = ROWS * 2 * 4;
+#pragma unroll 3
+    for (int p = 0; p < (NI + NT - 1) / NT; ++p) {
+        const int u = t + NT * p;
+        if (NI % NT && u >= NI) break;
+        const int q = u & 3, xq = (u >> 2) % NQ, r = (u >> 2) / NQ;
+        const int z = z0 + r / CHY - 1, y = y0 + r % CHY - 1, x = x0 + 4 * xq;
+        const bool rin = (unsigned)z < (unsigned)S && (unsigned)y < (unsigned)S;
+        const float *row = in + (rin ? ((long long)z * S + y) * S : 0);
+        float4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = C::ch(q, j);
+            const float *rc = row + (long long)(c < nc ? c : 0) * V;
+            v[j] = row4<V4>(rc, x, S, rin && c < nc);
+        }
+        typename C::t *d = sI + r * PITCH + c_at(4 + 4 * xq, q);
+        d[0] = C::make(v[0].x, v[1].x, v[2].x, v[3].x);
+        d[4] = C::make(v[0].y, v[1].y, v[2].y, v[3].y);
+        d[8] = C::make(v[0].z, v[1].z, v[2].z, v[3].z);
+        d[12] = C::make(v[0].w, v[1].w, v[2].w, v[3].w);
+    }
+#pragma unroll 2
+    for (int p = 0; p < (NH + NT - 1) / NT; ++p) {
+        const int u = t + NT * p;
+        if (NH % NT && u >= NH) break;
+        const int q = u & 3, e = (u >> 2) & 1, r = u >> 3;
+        const int z = z0 + r / CHY - 1, y = y0 + r % CHY - 1, x = e ? x0 + TX : x0 - 1;
+        const bool rin = (unsigned)z < (unsigned)S && (unsigned)y < (unsigned)S;
+        const float *row = in + (rin ? ((long long)z * S + y) * S : 0);
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = C::ch(q, j);
+            v[j] = row1(row + (long long)(c < nc ? c : 0) * V, x, S, rin && c < nc);
+        }
+        sI[r * PITCH + c_at(e ? TX + 4 : 3, q)] = C::make(v[0], v[1], v[2], v[3]);
+    }
+}
+
+template <typename T, int TX, int TZ, int NT>
+__device__ __forceinline__ void conv_stage(typename Chan<T>::t *sI, const float *in, int nc, int S, int V, int x0, int y0,
+                                           int z0, bool vec, int t) {
+    if (vec) conv_stage_rows<T, TX, TZ, NT, true>(sI, in, nc, S, V, x0, y0, z0, t);
+    else conv_stage_rows<T, TX, TZ, NT, false>(sI, in, nc, S, V, x0, y0, z0, t);
+}
+
+// the products of one dz for the four rows of a column block: b0 the lane's operands of the six input rows (PITCH
+// apart) at the three shifts, a the weights of the nine taps
+template <typename T, int FR, int PITCH>
+__device__ __forceinline__ void conv_dz(v4f (&acc)[FR][4], const typename Chan<T>::t (&a)[9][FR],
+                                        const typename Chan<T>::t *b0, const typename Chan<T>::t *b1,
+                                        const typename Chan<T>::t *b2) {
+    typename Chan<T>::t b[CHY][3];
+#pragma unroll
+    for (int y = 0; y < CHY; ++y) {
+        b[y][0] = b0[y * PITCH];
+        b[y][1] = b1[y * PITCH];
+        b[y][2] = b2[y * PITCH];
+    }
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int y = 0; y < CY; ++y)
+#pragma unroll
+                for (int f = 0; f < FR; ++f) acc[f][y] = Chan<T>::mul(a[dy * 3 + dx][f], b[y + dy][dx], acc[f][y]);
+}
+
+// All chunks by one workgroup of four waves: bias and ReLU in the epilogue.
+template <typename T, int FR, int TX, int TZ>
+__global__ __launch_bounds__(256) void k_conv_direct(const float *__restrict__ in, long long in_bs, int Ci, int S,
+                                                     const T *__restrict__ wt, int COP, const float *__restrict__ bias,
+                                                     int Co, float *__restrict__ out, long long out_bs, int relu,
+                                                     int rowgroups, int vec, int blocks) {
+    typedef typename Chan<T>::t CT4;
+    constexpr int PITCH = ConvTile<TX, TZ>::PITCH, NXB = TX / 16, NJ = NXB * TZ / 4;   // column blocks of a wave
+    static_assert(NJ >= 1 && NJ * 4 == NXB * TZ, "four waves share the tile's column blocks");
+    __shared__ __attribute__((aligned(16))) CT4 sI[ConvTile<TX, TZ>::QUADS];
+    const int ntx = (S + TX - 1) / TX, nty = (S + CY - 1) / CY, ntz = (S + TZ - 1) / TZ;
+    const int tiles = ntx * nty * ntz;
+    const int per = (blocks + 7) / 8;
+    int idx = (blockIdx.x % 8) * per + blockIdx.x / 8;        // neighbouring tiles on one XCD
+    if (idx >= blocks) return;
+    const int rg = idx % rowgroups;
+    idx /= rowgroups;
+    const int t = idx % tiles, b = idx / tiles;
+    const int x0 = (t % ntx) * TX, y0 = ((t / ntx) % nty) * CY, z0 = (t / (ntx * nty)) * TZ;
+    const int row0 = rg * FR * 16;
+    const float *inb = in + (long long)b * in_bs;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int V = S * S * S;
+    v4f acc[NJ][FR][4];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int f = 0; f < FR; ++f)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) acc[j][f][y] = v4f{0, 0, 0, 0};
+    const CT4 *lb[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) lb[dx] = sI + c_at(3 + (lane & 15) + dx, lane >> 4);
+    const int nchunk = (Ci + DCC - 1) / DCC;
+    for (int ch = 0; ch < nchunk; ++ch) {
+        const CT4 *wc = reinterpret_cast<const CT4 *>(wt + ((long long)ch * 27 * COP + row0 + (lane & 15)) * DCC) + (lane >> 4);
+        // the weights of a dz are loaded before the products of the one before (the first: before the tile)
+        CT4 a[2][9][FR];
+        auto weights = [&](CT4 (&w)[9][FR], int dz) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k)
+#pragma unroll
+                for (int f = 0; f < FR; ++f) w[k][f] = wc[((long long)(dz * 9 + k) * COP + f * 16) * (DCC / 4)];
+        };
+        weights(a[0], 0);
+        __syncthreads();
+        conv_stage<T, TX, TZ, 256>(sI, inb + (long long)ch * DCC * V, min(DCC, Ci - ch * DCC), S, V, x0, y0, z0, vec != 0, tid);
+        __syncthreads();
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz) {
+            if (dz < 2) weights(a[(dz + 1) & 1], dz + 1);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int cb = wave * NJ + j, o = (cb / NXB + dz) * CHY * PITCH + (cb % NXB) * (16 * 4 + 4);
+                conv_dz<T, FR, PITCH>(acc[j], a[dz & 1], lb[0] + o, lb[1] + o, lb[2] + o);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int cb = wave * NJ + j;
+        const int gz = z0 + cb / NXB, gx = x0 + (cb % NXB) * 16 + (lane & 15);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            const int gy = y0 + y;
+            const bool ok = gx < S && gy < S && gz < S;
+            float *o = out + (long long)b * out_bs + ((long long)gz * S + gy) * S + gx;
+#pragma unroll
+            for (int f = 0; f < FR; ++f)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int co = row0 + f * 16 + 4 * (lane >> 4) + r;
+                    if (!ok || co >= Co) continue;
+                    float v = acc[j][f][y][r] + (bias ? bias[co] : 0.f);
+                    if (relu) v = fmaxf(v, 0.f);
+                    o[(long long)co * V] = v;
+                }
+        }
+    }
+}
+
+// The chunks summed in parts, for the levels with few voxels (16 x 4 of one plane and 16 output channels per workgroup):
+// part p takes chunks [p cpb, (p + 1) cpb), a wave one part (FP32 operands: two, for the LDS), and the parts are added in
+// their order, bias first.
+constexpr int PARTS_MAX = 8;
+template <typename T> constexpr int deep_per() { return MT<T>::KL == 4 ? 1 : 2; }
+template <typename T>
+__global__ __launch_bounds__(64 * PARTS_MAX) void k_conv_deep(const float *__restrict__ in, long long in_bs, int Ci, int S,
+                                                              const T *__restrict__ wt, int COP,
+                                                              const float *__restrict__ bias, int Co,
+                                                              float *__restrict__ out, long long out_bs, int relu,
+                                                              int rowgroups, int vec, int nsplit, int cpb) {
+    typedef typename Chan<T>::t CT4;
+    constexpr int TX = 16, TZ = 1, PITCH = ConvTile<TX, TZ>::PITCH, QUADS = ConvTile<TX, TZ>::QUADS, PER = deep_per<T>();
+    extern __shared__ __attribute__((aligned(16))) unsigned char dsm[];
+    const int ntx = (S + TX - 1) / TX, nty = (S + CY - 1) / CY, tiles = ntx * nty * S;
+    int idx = blockIdx.x;
+    const int rg = idx % rowgroups;
+    idx /= rowgroups;
+    const int t = idx % tiles, b = idx / tiles;
+    const int x0 = (t % ntx) * TX, y0 = ((t / ntx) % nty) * CY, z0 = t / (ntx * nty);
+    const int row0 = rg * 16;
+    const float *inb = in + (long long)b * in_bs;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int V = S * S * S;
+    CT4 *sI = reinterpret_cast<CT4 *>(dsm) + wave * QUADS;
+    v4f acc[PER][1][4];
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) acc[i][0][y] = v4f{0, 0, 0, 0};
+    const CT4 *lb[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) lb[dx] = sI + c_at(3 + (lane & 15) + dx, lane >> 4);
+    const int nchunk = (Ci + DCC - 1) / DCC;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        for (int k = 0; k < cpb; ++k) {
+            const int part = wave * PER + i, ch = part * cpb + k;
+            const bool have = part < nsplit && ch < nchunk;
+            __syncthreads();
+            if (have)
+                conv_stage<T, TX, TZ, 64>(sI, inb + (long long)ch * DCC * V, min(DCC, Ci - ch * DCC), S, V, x0, y0, z0, vec != 0, lane);
+            __syncthreads();
+            if (!have) continue;
+            const CT4 *wc = reinterpret_cast<const CT4 *>(wt + ((long long)ch * 27 * COP + row0 + (lane & 15)) * DCC) + (lane >> 4);
+#pragma unroll
+            for (int dz = 0; dz < 3; ++dz) {
+                CT4 a[9][1];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) a[q][0] = wc[(long long)(dz * 9 + q) * COP * (DCC / 4)];
+                conv_dz<T, 1, PITCH>(acc[i], a, lb[0] + dz * CHY * PITCH, lb[1] + dz * CHY * PITCH, lb[2] + dz * CHY * PITCH);
+            }
+        }
+    __syncthreads();
+    float *red = reinterpret_cast<float *>(dsm);              // [part][row y][channel][x]
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                red[(((wave * PER + i) * 4 + y) * 16 + 4 * (lane >> 4) + r) * 16 + (lane & 15)] = acc[i][0][y][r];
+    __syncthreads();
+    for (int e = tid; e < 1024; e += blockDim.x) {
+        const int gx = x0 + (e & 15), co = row0 + ((e >> 4) & 15), gy = y0 + (e >> 8);
+        if (gx >= S || gy >= S || co >= Co) continue;
+        float v = bias ? bias[co] : 0.f;
+        for (int k = 0; k < nsplit; ++k) v += red[k * 1024 + e];
+        if (relu) v = fmaxf(v, 0.f);
+        out[(long long)b * out_bs + (long long)co * V + ((long long)z0 * S + gy) * S + gx] = v;
+    }
+}
+
+// direct-format weights wt[chunk][tap][COP][16] (channels in the order of Chan<T>) of a conv with Co outputs and Ci inputs; transpose = 1 takes
+// them from a layer W[Ci][Co][27] with the tap mirrored (the data-gradient convolution of that layer)
+template <typename T>
+__global__ void k_pack_direct(const float *__restrict__ W, int Co, int Ci, int transpose, int COP, long long total,
+                              T *__restrict__ wt) {
+    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (e >= total) return;
+    const int cc = (int)(e % DCC);
+    long long r = e / DCC;
+    const int o = (int)(r % COP);
+    r /= COP;
+    const int tap = (int)(r % 27);
+    const int ch = (int)(r / 27);
+    const int i = ch * DCC + Chan<T>::ch(cc / 4, cc % 4);
+    float v = 0.f;
+    if (o < Co && i < Ci)
+        v = transpose ? W[((long long)i * Co + o) * 27 + (26 - tap)] : W[((long long)o * Ci + i) * 27 + tap];
+    wt[e] = MT<T>::cvt(v);
+}
+
+
+// Weight and bias gradient of a 27-tap layer, dW[o][i][tap] = sum_{b,v} g[b][o][v] in[b][i][v + off(tap)] and
+// db[o] = sum_{b,v} g[b][o][v]. Per tap this is a product with M = output channels, N = 16 input channels and
+// K = voxels. A workgroup (input-channel chunk ch, tile group tg) loops over consecutive TX x 4 x TZ tiles of all samples
+// and stages g and the input tile with its halo channel-first in LDS, so that a lane's four consecutive voxels are one
+// 8-byte read. A wave owns one block of 16 output rows and all 27 taps (4 / FR waves share the K rows of such a
+// block): the operands of the three taps of one (dz, dy) come from one 16-byte window of the input row, shifted in
+// registers, and the windows of six rows serve four output rows: 22 LDS reads for 108 products.
+// Bound: bringing g and the input to the CUs. The tiles take whole rows (TX = 64, 32 or 16 by the volume's width): with
+// rows of 16 voxels every 128-byte line was fetched for a part of it, and the 48 -> 16 layer at 4 x 64^3 read 1.7 GB
+// for its 268 MB.
+// At 4 x 64^3 in BF16 (the launch that sums the parts included): 48 -> 16 channels 232 us (before: one 8 x 8 x 4 tile at
+// a time with every load waiting for its own result, 4-byte loads and a scalar reduction, 720 us), 16 -> 16 at 84 us
+// (175 us), 96 -> 32 at 32^3 101 us (250 us), all layers of a training step 0.70 ms (1.95 ms).
+// Partial sums per tile group, part[tg][ch][tap][COP][16] and bpart[tg][o], are added in order by k_wgrad_sum.
+constexpr int WY = 4, WHY = WY + 2;                           // tile height, rows with halo
+template <typename T, int TX> struct WgTile {
+    static constexpr int TZ = (MT<T>::KL == 4 && TX == 64 ? 128 : 64) / TX, HZ = TZ + 2;   // 256 voxels, 512 in the widest
+    static constexpr int ROW = TX + 4;                        // stored row: halo at 1 and TX + 2, interior from 2
+    static constexpr int XCH = HZ * WHY * ROW + 8;            // channel strides: 4 mod 8 banks, so that the 16 channels
+    static constexpr int GCH = TX * WY * TZ + 8;              // of a quarter wave's reads share no bank
+};
 
 // A lane's window of an input row, from two elements before its four voxels of the output row to two after, and the
 // products of one K step of 16 voxels (a: the lane's four values of g) for the three taps dx on it
@@ -999,65 +1155,80 @@ hipError_t cnn_conv_fwd_t(const float *in, long long in_bs, int Ci, int S, int t
     return hipGetLastError();
 }
 
-// split the launch until it has about 1024 workgroups: first by output-row groups, then over input-channel chunks
-void cnn_direct_split(int Ci, int S, int COP, int B, int &fr, int &rowgroups, int &nsplit, int &cpb) {
-    const long long tiles = (long long)((S + DT_X - 1) / DT_X) * ((S + DT_Y - 1) / DT_Y) * ((S + DT_Z - 1) / DT_Z);
+// Whether a layer's chunks are summed in parts (few 8 x 8 x 4 boxes of voxels times 16 output channels, several
+// chunks) and by how many chunks each. It fixes the order of the sums, not the launch.
+void cnn_direct_split(int Ci, int S, int COP, int B, int &nsplit, int &cpb) {
+    const long long boxes = (long long)((S + 7) / 8) * ((S + 7) / 8) * ((S + 3) / 4) * B;
     const int nchunk = (Ci + DCC - 1) / DCC;
-    const long long target = 1024;
-    fr = COP / 16;
-    rowgroups = 1;
+    const long long target = 1024, wg = boxes * (COP / 16);
     nsplit = 1;
     cpb = nchunk;
-    if (tiles * B >= target) return;
-    fr = 1;
-    rowgroups = COP / 16;
-    long long wg = tiles * B * rowgroups;
-    if (wg >= target || nchunk == 1) return;
-    int want = (int)std::min<long long>(nchunk, (target + wg - 1) / wg);
+    if (boxes >= target || wg >= target || nchunk == 1) return;
+    const int want = (int)std::min<long long>(nchunk, (target + wg - 1) / wg);
     cpb = (nchunk + want - 1) / want;
     nsplit = (nchunk + cpb - 1) / cpb;
 }
 
-template <typename T>
-hipError_t cnn_conv_direct_t(const float *in, long long in_bs, int Ci, int S, const void *wt, int COP, const float *bias,
-                             int Co, float *out, long long out_bs, int relu, int B, float *part, long long part_elems,
-                             hipStream_t s) {
-    int fr, rowgroups, nsplit, cpb;
-    cnn_direct_split(Ci, S, COP, B, fr, rowgroups, nsplit, cpb);
-    const long long V = (long long)S * S * S;
-    if (nsplit > 1 && (!part || (long long)nsplit * B * Co * V > part_elems)) {
-        nsplit = 1;                                         // no room for partial sums: one K split
-        cpb = (Ci + DCC - 1) / DCC;
-    }
-    const int tiles = ((S + DT_X - 1) / DT_X) * ((S + DT_Y - 1) / DT_Y) * ((S + DT_Z - 1) / DT_Z);
-    const unsigned grid = (unsigned)((long long)B * tiles * rowgroups * nsplit);
-    const T *w = (const T *)wt;
-#define DLAUNCH(F)                                                                                                   \
-    hipLaunchKernelGGL((k_conv_direct<T, F>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, w, COP, bias, Co, out,   \
-                       out_bs, relu, rowgroups, nsplit, cpb, part, B)
-    switch (fr) {
-    case 1: DLAUNCH(1); break;
-    case 2: DLAUNCH(2); break;
-    case 3: DLAUNCH(3); break;
-    case 4: DLAUNCH(4); break;
-    case 6: DLAUNCH(6); break;
-    case 8: DLAUNCH(8); break;
-    default: return hipErrorInvalidValue;
-    }
-#undef DLAUNCH
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || nsplit == 1) return e;
-    const long long n = (long long)B * Co * V;
-    hipLaunchKernelGGL(k_conv_split_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, part, nsplit, B, Co, (int)V,
-                       bias, relu, out, out_bs);
+struct ConvArgs {
+    const float *in;
+    long long in_bs;
+    int Ci, S;
+    const void *wt;
+    int COP;
+    const float *bias;
+    int Co;
+    float *out;
+    long long out_bs;
+    int relu, B, vec;
+};
+
+template <typename T, int FR, int TX, int TZ> hipError_t conv_launch(const ConvArgs &a, hipStream_t s) {
+    const int tiles = ((a.S + TX - 1) / TX) * ((a.S + CY - 1) / CY) * ((a.S + TZ - 1) / TZ);
+    const int rowgroups = a.COP / 16 / FR, blocks = a.B * tiles * rowgroups;
+    hipLaunchKernelGGL((k_conv_direct<T, FR, TX, TZ>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, s, a.in, a.in_bs,
+                       a.Ci, a.S, (const T *)a.wt, a.COP, a.bias, a.Co, a.out, a.out_bs, a.relu, rowgroups, a.vec, blocks);
     return hipGetLastError();
 }
 
+// Output rows per workgroup and tile: as many row blocks as divide the layer's, up to three (they share the staged
+// input), and 512 voxels; 256 voxels, then one row block, where that leaves fewer than 512 workgroups (two per CU)
+template <typename T, int TX> hipError_t conv_shape(const ConvArgs &a, hipStream_t s) {
+    constexpr int Z2 = 512 / 4 / TX, Z1 = Z2 / 2;
+    const int fr = a.COP / 16;
+    const long long vox = (long long)a.B * a.S * a.S * a.S;
+    const int best = fr % 3 == 0 ? 3 : fr % 2 == 0 ? 2 : 1;
+    const bool wide = vox / 512 * (fr / best) >= 512;
+    const int take = wide || vox / 256 * (fr / best) >= 512 ? best : 1;
+    if (wide) return take == 3 ? conv_launch<T, 3, TX, Z2>(a, s) : take == 2 ? conv_launch<T, 2, TX, Z2>(a, s) : conv_launch<T, 1, TX, Z2>(a, s);
+    return take == 3 ? conv_launch<T, 3, TX, Z1>(a, s) : take == 2 ? conv_launch<T, 2, TX, Z1>(a, s) : conv_launch<T, 1, TX, Z1>(a, s);
+}
+
+template <typename T>
+hipError_t cnn_conv_direct_t(const float *in, long long in_bs, int Ci, int S, const void *wt, int COP, const float *bias,
+                             int Co, float *out, long long out_bs, int relu, int B, hipStream_t s) {
+    const int vec = S % 4 == 0 && (uintptr_t)in % 16 == 0 && in_bs % 4 == 0;
+    int nsplit, cpb;
+    cnn_direct_split(Ci, S, COP, B, nsplit, cpb);
+    if (nsplit > 1) {
+        if (nsplit > PARTS_MAX) return hipErrorInvalidValue;
+        constexpr int PER = deep_per<T>();
+        const int rowgroups = COP / 16, tiles = ((S + 15) / 16) * ((S + CY - 1) / CY) * S, waves = (nsplit + PER - 1) / PER;
+        const size_t lds = sizeof(typename Chan<T>::t) * ConvTile<16, 1>::QUADS * waves;
+        static_assert(sizeof(typename Chan<T>::t) * ConvTile<16, 1>::QUADS >= 4096 * PER, "the parts fit the staging area");
+        hipLaunchKernelGGL(k_conv_deep<T>, dim3((unsigned)((long long)B * tiles * rowgroups)), dim3(64 * waves), lds, s, in,
+                           in_bs, Ci, S, (const T *)wt, COP, bias, Co, out, out_bs, relu, rowgroups, vec, nsplit, cpb);
+        return hipGetLastError();
+    }
+    const ConvArgs a{in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, vec};
+    if (S > 32) return conv_shape<T, 64>(a, s);
+    if (S > 16) return conv_shape<T, 32>(a, s);
+    return conv_shape<T, 16>(a, s);
+}
+
 hipError_t cnn_conv_direct(int use_bf16, const float *in, long long in_bs, int Ci, int S, const void *wt, int COP,
-                           const float *bias, int Co, float *out, long long out_bs, int relu, int B, float *part,
-                           long long part_elems, hipStream_t s) {
-    return use_bf16 ? cnn_conv_direct_t<bf16>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, part, part_elems, s)
-                    : cnn_conv_direct_t<float>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, part, part_elems, s);
+                           const float *bias, int Co, float *out, long long out_bs, int relu, int B, hipStream_t s) {
+    return use_bf16 ? cnn_conv_direct_t<bf16>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, s)
+                    : cnn_conv_direct_t<float>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, s);
 }
 
 // Tile groups of a weight gradient: about 512 workgroups (two per CU are resident), every group with the same number of
