@@ -804,12 +804,6 @@ helm_status setup_impl(helm_ctx **out, helm_grid g, const double h[3], const voi
     }
     p.tiles_x = (c.nx + 63) / 64;
     p.tiles_y = (c.ny + STENCIL_TY - 1) / STENCIL_TY;
-    const int blocks = STENCIL_WAVES / STENCIL_TY;   // blocks of STENCIL_TY waves
-    int want = (blocks + p.tiles_x * p.tiles_y - 1) / (p.tiles_x * p.tiles_y);
-    want = std::max(1, std::min(want, c.nz));
-    p.zchunk = std::max((c.nz + want - 1) / want, std::min(c.nz, STENCIL_MINZ));
-    p.zchunks = (c.nz + p.zchunk - 1) / p.zchunk;
-
     // derived fields
     helm_status st;
     if ((st = dalloc(c, &c.k2, (size_t)c.n)) != HELM_OK) return bail(st);
@@ -825,6 +819,10 @@ helm_status setup_impl(helm_ctx **out, helm_grid g, const double h[3], const voi
         he = launch_derived_fields((const double *)k2_dev, k2_halo, c.k2, c.fld, p, c.hx, c.stream);
     }
     if (he == hipErrorInvalidValue) { c.err = "k^2 contains NaN or Inf"; return bail(HELM_EINVAL); }
+    {
+        StencilParams *sp = &p;
+        stencil_split(&sp, 1);
+    }
     if (he != hipSuccess) { c.err = std::string("derived fields: ") + hipGetErrorString(he); return bail(HELM_EDEVICE); }
 
     // EigT Step 1: 1D eigen-decompositions of Lambda-bar_x and Lambda-bar_y

@@ -106,23 +106,21 @@ helm_status helm_batch_create(helm_batch **out, helm_ctx *const *ctxs, int np, i
     int tri_lx = 16;
     while (tri_lx > 1 && tri_lx * tri_pb > 1024) tri_lx /= 2;
     // per-problem descriptors, work buffers and launch offsets
-    long long tot_blocks_mv_target = 32768 / STENCIL_TY;   // about 32768 waves over all problems
     std::vector<int> omv(1, 0), otri(1, 0), odot(1, 0), olc(1, 0);
     std::vector<long long> og[4];
     for (auto &v : og) v.assign(1, 0);
     b->hP.resize(np);
+    {
+        std::vector<StencilParams *> sps;
+        for (int p = 0; p < np; ++p) {
+            b->hP[p].sp = ctxs[p]->c.sp;
+            sps.push_back(&b->hP[p].sp);
+        }
+        stencil_split(sps.data(), np);
+    }
     for (int p = 0; p < np; ++p) {
         Ctx &c = ctxs[p]->c;
         BProb &q = b->hP[p];
-        q.sp = c.sp;
-        // z-chunking for the batch: about tot_blocks_mv_target matvec blocks over all problems
-        {
-            int txy = q.sp.tiles_x * q.sp.tiles_y;
-            long long want = std::max<long long>(1, tot_blocks_mv_target / np / txy);
-            want = std::min<long long>(want, c.nz);
-            q.sp.zchunk = (int)((c.nz + want - 1) / want);
-            q.sp.zchunks = (c.nz + q.sp.zchunk - 1) / q.sp.zchunk;
-        }
         q.k2 = c.k2;
         q.fld = c.fld;
         if (b->fp32) {
@@ -168,14 +166,15 @@ helm_status helm_batch_create(helm_batch **out, helm_ctx *const *ctxs, int np, i
         og[2].push_back(og[2].back() + fold_tile_count(FOLD_YI, q.fy, bm[2], bn[2]));
         og[3].push_back(og[3].back() + fold_tile_count(FOLD_XI, q.fx, bm[3], bn[3]));
     }
-    // step-matvec units: consecutive problems of one context share a block (their operator is read once)
+    // matvec units: runs of problems of one context, whose blocks alternate over the run's right-hand sides
     std::vector<int2> units;
     std::vector<int> omvp(1, 0);
-    for (int p = 0; p < np; ++p) {
-        const bool pair = p + 1 < np && ctxs[p + 1] == ctxs[p];
-        units.push_back(make_int2(p, pair ? p + 1 : -1));
-        omvp.push_back(omvp.back() + (omv[p + 1] - omv[p]));
-        if (pair) ++p;
+    for (int p = 0; p < np;) {
+        int e = p + 1;
+        while (e < np && ctxs[e] == ctxs[p]) ++e;
+        units.push_back(make_int2(p, e - p));
+        omvp.push_back(omv[e]);
+        p = e;
     }
     BLaunch &L = b->L;
     if (balloc(*b, &b->dP, np) != hipSuccess || balloc(*b, &b->dst, np) != hipSuccess ||
@@ -186,21 +185,19 @@ helm_status helm_batch_create(helm_batch **out, helm_ctx *const *ctxs, int np, i
         balloc(*b, &L.a.coef, (size_t)np * (m + 1)) != hipSuccess)
         return fail(HELM_ENOMEM, "state allocation failed");
     int2 *dunits = nullptr;
-    if (balloc(*b, &dunits, units.size()) != hipSuccess || balloc(*b, &L.off.mvp, omvp.size()) != hipSuccess)
+    if (balloc(*b, &dunits, units.size()) != hipSuccess || balloc(*b, &L.off.mv, omvp.size()) != hipSuccess)
         return fail(HELM_ENOMEM, "offset allocation failed");
     if (hipMemcpy(dunits, units.data(), units.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(L.off.mvp, omvp.data(), omvp.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
+        hipMemcpy(L.off.mv, omvp.data(), omvp.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
         return fail(HELM_EDEVICE, "offset upload failed");
     L.units = dunits;
     L.nunits = (int)units.size();
-    L.tot_mvp = omvp.back();
-    if (balloc(*b, &L.off.mv, np + 1) != hipSuccess || balloc(*b, &L.off.tri, np + 1) != hipSuccess ||
+    if (balloc(*b, &L.off.tri, np + 1) != hipSuccess ||
         balloc(*b, &L.off.dot, np + 1) != hipSuccess || balloc(*b, &L.off.lc, np + 1) != hipSuccess ||
         balloc(*b, &L.off.g[0], np + 1) != hipSuccess || balloc(*b, &L.off.g[1], np + 1) != hipSuccess ||
         balloc(*b, &L.off.g[2], np + 1) != hipSuccess || balloc(*b, &L.off.g[3], np + 1) != hipSuccess)
         return fail(HELM_ENOMEM, "offset allocation failed");
-    if (hipMemcpy(L.off.mv, omv.data(), omv.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(L.off.tri, otri.data(), otri.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
+    if (hipMemcpy(L.off.tri, otri.data(), otri.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(L.off.dot, odot.data(), odot.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(L.off.lc, olc.data(), olc.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(L.off.g[0], og[0].data(), og[0].size() * sizeof(long long), hipMemcpyHostToDevice) != hipSuccess ||

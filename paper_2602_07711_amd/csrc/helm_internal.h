@@ -27,11 +27,8 @@ bool eig_lambda_bar_folded(int n, cd gamma, double zeta, EigFold &f, std::string
 void eig_fold_dense(const EigFold &f, std::vector<cd> &d, std::vector<cd> &V, std::vector<cd> &Vinv);
 
 // Stencil coefficients that depend only on the grid (the k^2-dependent parts are per node).
-// Matvec thread block: 64 x STENCIL_TY threads, one output column each; the z-chunk length is chosen so that a
-// launch holds about STENCIL_WAVES waves in total, but no shorter than STENCIL_MINZ planes.
+// Matvec thread block: 64 x STENCIL_TY threads, one output column each, zchunk planes (stencil_split).
 constexpr int STENCIL_TY = 8;
-constexpr int STENCIL_WAVES = 8192;
-constexpr int STENCIL_MINZ = 8;   // shortest z-chunk: each chunk reads two halo planes
 
 struct StencilParams {
     int nx, ny, nz;
@@ -320,9 +317,8 @@ struct BArrays {                  // per-problem small arrays, problem p at p * 
     double2 *sn, *g, *coef;       // m, m+1, m+1
 };
 struct BOffsets {                 // prefix sums of blocks/tiles per problem for each grouped launch
-    int *mv, *tri, *dot, *lc;     // np + 1 each
-    int *mvp;                     // nunits + 1: blocks of the step matvec per unit (one problem or two sharing an
-                                  // operator)
+    int *tri, *dot, *lc;          // np + 1 each
+    int *mv;                      // nunits + 1: blocks of the matvec per unit
     long long *g[4];              // tiles of the x forward, y forward, y inverse and x inverse transforms
 };
 
@@ -332,6 +328,8 @@ hipError_t launch_derived_fields_c(const double2 *k2_halo, int halo, double *k2,
                                    double4 *fldi, const StencilParams &p, double h, hipStream_t s);
 hipError_t launch_derived_fields(const double *k2_halo, int halo, double *k2, double4 *fld, const StencilParams &p,
                                  double h, hipStream_t s);
+// z-chunks of one launch over `count` problems (same order; complex k^2 or not)
+void stencil_split(StencilParams *const *ps, int count);
 hipError_t launch_matvec(const StencilParams &p, const double2 *x, const double *k2, const double4 *fld,
                          const double2 *F, double2 *y, hipStream_t s);
 // the same with a complex64 input (widened exactly to complex128 on load)
@@ -401,10 +399,9 @@ struct BLaunch {
     BArrays a;
     BOffsets off;                 // device arrays
     int np, m, order, fp32;
-    const int2 *units;                          // device: the step matvec's units (p, p2), p2 = -1 when alone
+    const int2 *units;                          // device: the matvec's units (first problem, count) of one context each
     int nunits;
     int tot_mv, tot_tri, tot_dot, tot_lc;       // total blocks per grouped launch
-    int tot_mvp;                                // total blocks of the step matvec over the units
     long long tot_g[4];                         // total transform tiles per role
     int gemm_grid;                              // persistent GEMM grid size
     int cfg[4];                                 // tile configurations of the four transform roles

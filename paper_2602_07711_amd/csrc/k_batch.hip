@@ -87,50 +87,27 @@ __global__ __launch_bounds__(1024) void k_b_tridiag(const BProb *__restrict__ P,
 
 // ---------------------------------------------------------------------------------------------- matvec
 // mode 0: restart, V_0 = F - A x (problems not done); mode 1: step j, V_{j+1} = V_j - A Z_j (active problems);
-// ZT: element type of the Z basis (complex64 with the FP32 preconditioner)
+// ZT: element type of the Z basis (complex64 with the FP32 preconditioner).
+// A unit is a run of problems of one context (same k^2 and field block, e.g. incident directions on one medium): the
+// blocks of one XCD take the unit's right-hand sides of a tile one after another, so the operator comes from that
+// XCD's L2 for all but the first (16 x 128^3 FP32 form: 420 us a step; with two right-hand sides computed by one block,
+// whose registers left one wave per SIMD, 614 us).
 template <int ORDER, typename ZT>
 __global__ __launch_bounds__(NT) void k_b_matvec(const BProb *__restrict__ P, const BState *__restrict__ st,
-                                                  const int *__restrict__ off, int np, int mode, int j) {
-    const int p = find_prob(off, np, blockIdx.x);
-    if (mode == 0 ? st[p].done : !st[p].active) return;
-    const BProb &q = P[p];
-    const int lb = blockIdx.x - off[p];
-    if (mode == 0)
-        matvec_tile<ORDER, true>(q.x, q.k2, q.fld, q.F, q.V, q.sp, lb);
-    else
-        matvec_tile<ORDER, true, ZT>((const ZT *)q.Z + (long long)j * q.n, q.k2, q.fld, q.V + (long long)j * q.n,
-                                     q.V + (long long)(j + 1) * q.n, q.sp, lb);
-}
-
-// step j with right-hand sides paired on a shared operator: a unit is one problem or two problems of the same
-// context (same k^2 and field block, e.g. two incident directions on one medium); the block reads the operator's
-// planes once for both. Problems that are not active are left out of their unit.
-template <int ORDER, typename ZT>
-__global__ __launch_bounds__(NT) void k_b_matvec_pair(const BProb *__restrict__ P, const BState *__restrict__ st,
-                                                       const int2 *__restrict__ units, const int *__restrict__ off,
-                                                       int nunits, int j) {
+                                                  const int2 *__restrict__ units, const int *__restrict__ off,
+                                                  int nunits, int mode, int j) {
     const int u = find_prob(off, nunits, blockIdx.x);
     const int2 pu = units[u];
-    const bool a1 = st[pu.x].active != 0;
-    const bool a2 = pu.y >= 0 && st[pu.y].active != 0;
-    if (!a1 && !a2) return;
-    const ZT *xs[2];
-    const double2 *Fs[2];
-    double2 *ys[2];
-    int nr = 0;
-    const int ps[2] = {pu.x, pu.y};
-    const bool as[2] = {a1, a2};
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-        if (as[r]) {
-            const BProb &q = P[ps[r]];
-            xs[nr] = (const ZT *)q.Z + (long long)j * q.n;
-            Fs[nr] = q.V + (long long)j * q.n;
-            ys[nr] = q.V + (long long)(j + 1) * q.n;
-            ++nr;
-        }
-    const BProb &q = P[a1 ? pu.x : pu.y];
-    matvec_tile_n<ORDER, true, ZT, false, 2>(xs, q.k2, q.fld, Fs, ys, q.sp, blockIdx.x - off[u], nr);
+    const int lb = blockIdx.x - off[u], slot = lb / 8;       // every unit starts at a multiple of 8 blocks
+    const int p = pu.x + slot % pu.y;
+    if (mode == 0 ? st[p].done : !st[p].active) return;
+    const BProb &q = P[p];
+    const int bid = slot / pu.y * 8 + lb % 8;
+    if (mode == 0)
+        matvec_tile<ORDER, true>(q.x, q.k2, q.fld, q.F, q.V, q.sp, bid);
+    else
+        matvec_tile<ORDER, true, ZT>((const ZT *)q.Z + (long long)j * q.n, q.k2, q.fld, q.V + (long long)j * q.n,
+                                     q.V + (long long)(j + 1) * q.n, q.sp, bid);
 }
 
 // ---------------------------------------------------------------------------------------------- inner products
@@ -475,24 +452,12 @@ template <typename T> hipError_t precond_steps(const BLaunch &L, hipStream_t s, 
 }
 
 template <typename ZT> hipError_t matvec_step_t(const BLaunch &L, hipStream_t s, int mode, int j) {
-    if (mode == 1) {
-        if (L.order == 6)
-            hipLaunchKernelGGL((k_b_matvec_pair<6, ZT>), dim3(L.tot_mvp), dim3(64, TY), 0, s, L.P, L.st, L.units,
-                               L.off.mvp, L.nunits, j);
-        else if (L.order == 4)
-            hipLaunchKernelGGL((k_b_matvec_pair<4, ZT>), dim3(L.tot_mvp), dim3(64, TY), 0, s, L.P, L.st, L.units,
-                               L.off.mvp, L.nunits, j);
-        else
-            hipLaunchKernelGGL((k_b_matvec_pair<2, ZT>), dim3(L.tot_mvp), dim3(64, TY), 0, s, L.P, L.st, L.units,
-                               L.off.mvp, L.nunits, j);
-        return hipGetLastError();
-    }
     if (L.order == 6)
-        hipLaunchKernelGGL((k_b_matvec<6, ZT>), dim3(L.tot_mv), dim3(64, TY), 0, s, L.P, L.st, L.off.mv, L.np, mode, j);
+        hipLaunchKernelGGL((k_b_matvec<6, ZT>), dim3(L.tot_mv), dim3(64, TY), 0, s, L.P, L.st, L.units, L.off.mv, L.nunits, mode, j);
     else if (L.order == 4)
-        hipLaunchKernelGGL((k_b_matvec<4, ZT>), dim3(L.tot_mv), dim3(64, TY), 0, s, L.P, L.st, L.off.mv, L.np, mode, j);
+        hipLaunchKernelGGL((k_b_matvec<4, ZT>), dim3(L.tot_mv), dim3(64, TY), 0, s, L.P, L.st, L.units, L.off.mv, L.nunits, mode, j);
     else
-        hipLaunchKernelGGL((k_b_matvec<2, ZT>), dim3(L.tot_mv), dim3(64, TY), 0, s, L.P, L.st, L.off.mv, L.np, mode, j);
+        hipLaunchKernelGGL((k_b_matvec<2, ZT>), dim3(L.tot_mv), dim3(64, TY), 0, s, L.P, L.st, L.units, L.off.mv, L.nunits, mode, j);
     return hipGetLastError();
 }
 hipError_t matvec_step(const BLaunch &L, hipStream_t s, int mode, int j) {

@@ -228,6 +228,47 @@ hipError_t launch_derived_fields_c(const double2 *k2_halo, int halo, double *k2,
     return hbad ? hipErrorInvalidValue : hipSuccess;
 }
 
+// Blocks of the step matvec that run at once (one per CU at order 6: 200 VGPRs, eight waves)
+template <int ORDER, bool KC> int matvec_resident() {
+    static const int cap = [] {
+        int dev = 0, cus = 0, nb = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_matvec<ORDER, true, double2, KC>, NT, 0) != hipSuccess)
+            return 256;
+        return nb * cus > 0 ? nb * cus : 256;
+    }();
+    return cap;
+}
+
+// A block of zc planes streams zc + 2 of them and costs about two more to start, and blocks run in rounds of the
+// resident ones, so the length that makes rounds (zc + 4) least is taken, plus zc / 3 for the last round, which
+// finishes unevenly. Measured (order 6, one product): 32^3 11.7 -> 5.6 us (1 plane per block instead of 8), 64^3 12.3 ->
+// 6.9 (2), 128^3 33.0 -> 30.8 (16), 200^3 174 -> 152 (40 instead of 19), 250 x 190 x 217 194 -> 170 (28 instead of 20),
+// 256^3 unchanged (32; 64 planes: 270 against 253).
+void stencil_split(StencilParams *const *ps, int count) {
+    const StencilParams &p0 = *ps[0];
+    const bool kc = p0.k2i != nullptr;
+    const int cap = p0.order == 6 ? (kc ? matvec_resident<6, true>() : matvec_resident<6, false>())
+                  : p0.order == 4 ? (kc ? matvec_resident<4, true>() : matvec_resident<4, false>())
+                                  : (kc ? matvec_resident<2, true>() : matvec_resident<2, false>());
+    int nzmax = 1;
+    for (int i = 0; i < count; ++i) nzmax = ps[i]->nz > nzmax ? ps[i]->nz : nzmax;
+    int best = 1;
+    double cost = 1e300;
+    for (int zc = 1; zc <= nzmax; ++zc) {
+        long long blocks = 0;
+        for (int i = 0; i < count; ++i)
+            blocks += (long long)ps[i]->tiles_x * ps[i]->tiles_y * ((ps[i]->nz + zc - 1) / zc);
+        const double c = (double)((blocks + cap - 1) / cap) * (zc + 4) + zc / 3.0;
+        if (c < cost) { cost = c; best = zc; }
+    }
+    for (int i = 0; i < count; ++i) {
+        ps[i]->zchunk = best < ps[i]->nz ? best : ps[i]->nz;
+        ps[i]->zchunks = (ps[i]->nz + ps[i]->zchunk - 1) / ps[i]->zchunk;
+    }
+}
+
 hipError_t launch_matvec(const StencilParams &p, const double2 *x, const double *k2, const double4 *fld,
                          const double2 *F, double2 *y, hipStream_t s) {
     return launch_matvec_t<double2>(p, x, k2, fld, F, y, s);
