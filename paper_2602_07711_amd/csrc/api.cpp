@@ -994,8 +994,7 @@ helm_status helm_rhs(helm_ctx *ctx, const void *f_dev, void *F_dev) {
         return HELM_EUNSUPPORTED;
     }
     if (!f_dev || !F_dev) { c.err = "NULL pointer"; return HELM_EINVAL; }
-    double h3[3] = {c.hx, c.hy, c.hz};
-    HIP_TRY(launch_rhs(c.sp, (const double2 *)f_dev, c.k2, c.fld, h3, (double2 *)F_dev, c.stream));
+    HIP_TRY(launch_rhs(c.sp, (const double2 *)f_dev, c.k2, c.fld, c.hx, (double2 *)F_dev, c.stream));
     return HELM_OK;
 }
 

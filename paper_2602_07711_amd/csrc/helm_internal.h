@@ -335,8 +335,8 @@ hipError_t launch_matvec(const StencilParams &p, const double2 *x, const double 
 // the same with a complex64 input (widened exactly to complex128 on load)
 hipError_t launch_matvec(const StencilParams &p, const float2 *x, const double *k2, const double4 *fld,
                          const double2 *F, double2 *y, hipStream_t s);   // F != nullptr: y = F - A x
-hipError_t launch_rhs(const StencilParams &p, const double2 *f_halo, const double *k2, const double4 *fld,
-                      double h3[3], double2 *F, hipStream_t s);
+hipError_t launch_rhs(const StencilParams &p, const double2 *f_halo, const double *k2, const double4 *fld, double h,
+                      double2 *F, hipStream_t s);   // h: the uniform step of order 6
 
 // Transform tile configurations 0..GEMM_NCFG-1 = (BM, BN, BK) of (64,64,16), (64,64,32), (128,64,16), (64,128,16).
 constexpr int GEMM_NCFG = 4;

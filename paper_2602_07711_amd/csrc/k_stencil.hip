@@ -89,68 +89,85 @@ __global__ void k_derived_c(const double2 *__restrict__ k2h, int halo, double *_
 }
 
 // --------------------------------------------------------------------------- right-hand side
-// k2i, fldi: imaginary parts for complex k^2 (NULL for real k^2)
-__global__ void k_rhs(const double2 *__restrict__ f, const double *__restrict__ k2, const double4 *__restrict__ fld,
-                      const double *__restrict__ k2i, const double4 *__restrict__ fldi, double2 *__restrict__ F,
-                      int nx, int ny, int nz, int order, double hx, double hy, double hz) {
-    long long n = (long long)nx * ny * nz;
-    long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+// F = R_h f. order 4: f + sum_a h_a^2/12 T_a f. order 6, uniform h: f + h^2/12 Lap_h f - h^4/240 sum delta^4 f +
+// h^4/90 P_h f - h^2/20 k^2 f + h^4/60 sum (k^2)_nu delta_nu f, the last with (k^2)_nu = 120 g_nu / h.
+// A thread owns a column of outputs over ZC planes and carries the centre values of five planes and the sums of the
+// x and y neighbours of three, so a node costs 13 reads of f (5 at order 4), which the rows of a block share through
+// L1, instead of 25. Bound by HBM (f, k^2 and the field block read, F written: 72 B): 250 x 190 x 217, order 6,
+// 236 us (3.1 TB/s; one thread per node with 25 reads 329 us), 64^3 6.5 (8.5), 128^3 42 (60), 256^3 335 (518).
+constexpr int RHS_Y = 4;
+// order 2: the samples themselves, without the halo
+__global__ void k_rhs2(const double2 *__restrict__ f, double2 *__restrict__ F, int nx, int ny, long long n) {
+    const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
     if (p >= n) return;
-    int i = (int)(p % nx);
-    int j = (int)((p / nx) % ny);
-    int l = (int)(p / ((long long)nx * ny));
-    const int px = nx + 4, py = ny + 4;
-    auto at = [&](int di, int dj, int dl) -> double2 {
-        return f[((long long)(l + 2 + dl) * py + (j + 2 + dj)) * px + (i + 2 + di)];
-    };
-    double2 c = at(0, 0, 0);
-    if (order == 2) { F[p] = c; return; }
-    double hs[3] = {hx, hy, hz};
-    double2 d2[3];
-    for (int a = 0; a < 3; ++a) {
-        int dx = (a == 0), dy = (a == 1), dz = (a == 2);
-        double2 s = cadd(at(dx, dy, dz), at(-dx, -dy, -dz));
-        d2[a] = cscale(csub(s, cscale(c, 2.0)), 1.0 / (hs[a] * hs[a]));
+    const int i = (int)(p % nx), j = (int)((p / nx) % ny);
+    const long long l = p / ((long long)nx * ny);
+    F[p] = f[((l + 2) * (ny + 4) + (j + 2)) * (nx + 4) + (i + 2)];
+}
+template <int ORDER, bool KC, int ZC>
+__global__ __launch_bounds__(64 * RHS_Y) void k_rhs(const double2 *__restrict__ f, const double *__restrict__ k2,
+                                                    const double4 *__restrict__ fld, const double *__restrict__ k2i,
+                                                    const double4 *__restrict__ fldi, double2 *__restrict__ F, int nx,
+                                                    int ny, int nz, double h) {
+    const int tx = (nx + 63) / 64, ty = (ny + RHS_Y - 1) / RHS_Y;
+    const int T = tx * ty * ((nz + ZC - 1) / ZC);
+    const int per = (T + 7) / 8;
+    const int tile = (int)(blockIdx.x % 8) * per + blockIdx.x / 8;   // consecutive tiles on one XCD
+    if (tile >= T) return;
+    const int io = tile % tx * 64 + threadIdx.x, jo = (tile / tx) % ty * RHS_Y + threadIdx.y;
+    const int z0 = tile / (tx * ty) * ZC, z1 = min(z0 + ZC, nz);
+    const bool ok = io < nx && jo < ny;
+    const int i = min(io, nx - 1), j = min(jo, ny - 1);
+    const long long px = nx + 4, pp = px * (ny + 4), plane = (long long)nx * ny;
+    const double2 *c = f + (long long)(z0 + 2) * pp + (long long)(j + 2) * px + (i + 2);   // centre of plane z0
+    long long o = (long long)z0 * plane + (long long)j * nx + i;
+    double2 cm2, cm, c0 = c[0], cp = c[pp], Fxm, Fym, xm = c[-1], xp = c[1], ym = c[-px], yp = c[px];
+    if (ORDER == 6) {
+        cm2 = c[-2 * pp];
+        Fxm = cadd(c[-pp - 1], c[-pp + 1]);
+        Fym = cadd(c[-pp - px], c[-pp + px]);
     }
-    if (order == 4) {
-        double2 out = c;
-        for (int a = 0; a < 3; ++a) out = cfma(hs[a] * hs[a] / 12.0, d2[a], out);
-        F[p] = out;
-        return;
-    }
-    // order 6, uniform h: f + h^2/12 Lap_h f - h^4/240 sum delta^4 f + h^4/90 P_h f - h^2/20 k^2 f
-    //                    + h^4/60 sum (k^2)_nu delta_nu f      (the last uses (k^2)_nu = 120 g_nu / h)
-    double h = hx, h2 = h * h;
-    double2 out = c;
-    out = cfma(h2 / 12.0, cadd(cadd(d2[0], d2[1]), d2[2]), out);
-    const double4 fl = fld[p];
-    const double4 fli = fldi ? fldi[p] : make_double4(0, 0, 0, 0);
-    const double2 gg[3] = {make_double2(fl.y, fli.y), make_double2(fl.z, fli.z), make_double2(fl.w, fli.w)};
-    for (int a = 0; a < 3; ++a) {
-        int dx = (a == 0), dy = (a == 1), dz = (a == 2);
-        double2 p1 = at(dx, dy, dz), m1 = at(-dx, -dy, -dz);
-        double2 p2 = at(2 * dx, 2 * dy, 2 * dz), m2 = at(-2 * dx, -2 * dy, -2 * dz);
-        double2 d4 = cadd(cadd(cadd(p2, m2), cscale(cadd(p1, m1), -4.0)), cscale(c, 6.0));
-        out = cfma(-1.0 / 240.0, d4, out);                       // h^4/240 * delta^4 f (delta^4 carries 1/h^4)
-        double2 d1 = csub(p1, m1);                               // 2 h delta f
-        out = cadd(out, cscale(cmul(gg[a], d1), h2));            // h^4/60 * (120 g/h) * d1/(2h) = h^2 g d1
-    }
-    const int pairs[3][2] = {{0, 1}, {0, 2}, {1, 2}};
-    for (int q = 0; q < 3; ++q) {
-        double2 acc = make_double2(0.0, 0.0);
-        for (int sa = -1; sa <= 1; ++sa)
-            for (int sb = -1; sb <= 1; ++sb) {
-                int d[3] = {0, 0, 0};
-                d[pairs[q][0]] += sa;
-                d[pairs[q][1]] += sb;
-                double w = (sa == 0 ? -2.0 : 1.0) * (sb == 0 ? -2.0 : 1.0);
-                acc = cfma(w, at(d[0], d[1], d[2]), acc);
+    cm = c[-pp];
+    const double h2 = h * h;
+    for (int l = z0; l < z1; ++l, c += pp, o += plane) {
+        // plane l + 1: the neighbours; plane l + 2: the centre (order 4: both of plane l + 1)
+        const double2 xmn = c[pp - 1], xpn = c[pp + 1], ymn = c[pp - px], ypn = c[pp + px];
+        const double2 Fx = cadd(xm, xp), Fy = cadd(ym, yp), Fz = cadd(cm, cp);
+        double2 out, cn = c[2 * pp];
+        if (ORDER == 4) {
+            out = cfma(1.0 / 12.0, csub(cadd(cadd(Fx, Fy), Fz), cscale(c0, 6.0)), c0);
+        } else {
+            const double2 x2 = cadd(c[-2], c[2]), y2 = cadd(c[-2 * px], c[2 * px]), z2 = cadd(cm2, cn);
+            const double2 dg = cadd(cadd(c[-px - 1], c[-px + 1]), cadd(c[px - 1], c[px + 1]));
+            const double4 fl = fld[o], fli = KC ? fldi[o] : make_double4(0, 0, 0, 0);
+            const double2 kk = make_double2(k2[o], KC ? k2i[o] : 0.0);
+            const double2 Fxp = cadd(xmn, xpn), Fyp = cadd(ymn, ypn);
+            const double2 E = cadd(cadd(Fx, Fy), Fz);
+            out = cfma(1.0 / 12.0, csub(E, cscale(c0, 6.0)), c0);
+            out = cfma(-1.0 / 240.0, cadd(csub(cadd(cadd(x2, y2), z2), cscale(E, 4.0)), cscale(c0, 18.0)), out);
+            // P: the xy, xz and yz products of second differences; every face enters two of them with -2
+            const double2 P = cadd(cadd(dg, cadd(cadd(Fxm, Fxp), cadd(Fym, Fyp))), csub(cscale(c0, 12.0), cscale(E, 4.0)));
+            out = cfma(1.0 / 90.0, P, out);
+            double2 gd;
+            if (KC) {
+                gd = cadd(cmul(make_double2(fl.y, fli.y), csub(xp, xm)), cmul(make_double2(fl.z, fli.z), csub(yp, ym)));
+                gd = cadd(gd, cmul(make_double2(fl.w, fli.w), csub(cp, cm)));
+                gd = csub(gd, cscale(cmul(kk, c0), 1.0 / 20.0));
+            } else {
+                gd = cfma(fl.w, csub(cp, cm), cfma(fl.z, csub(yp, ym), cscale(csub(xp, xm), fl.y)));
+                gd = cfma(-kk.x / 20.0, c0, gd);
             }
-        out = cfma(1.0 / 90.0, acc, out);                        // h^4/90 * P_h f (P_h carries 1/h^4)
+            out = cfma(h2, gd, out);
+            cm2 = cm;
+            Fxm = Fx;
+            Fym = Fy;
+        }
+        if (ok) F[o] = out;
+        cm = c0;
+        c0 = cp;
+        cp = cn;
+        xm = xmn; xp = xpn; ym = ymn; yp = ypn;
     }
-    const double2 kk = make_double2(k2[p], k2i ? k2i[p] : 0.0);
-    out = csub(out, cscale(cmul(kk, c), h2 / 20.0));
-    F[p] = out;
 }
 
 template <int ORDER, bool RESID, typename XT, bool KC>
@@ -279,13 +296,35 @@ hipError_t launch_matvec(const StencilParams &p, const float2 *x, const double *
     return launch_matvec_t<float2>(p, x, k2, fld, F, y, s);
 }
 
-hipError_t launch_rhs(const StencilParams &p, const double2 *f_halo, const double *k2, const double4 *fld,
-                      double h3[3], double2 *F, hipStream_t s) {
-    long long n = (long long)p.nx * p.ny * p.nz;
-    int blocks = (int)((n + 255) / 256);
-    hipLaunchKernelGGL(k_rhs, dim3(blocks), dim3(256), 0, s, f_halo, k2, fld, p.k2i, p.fldi, F, p.nx, p.ny, p.nz,
-                       p.order, h3[0], h3[1], h3[2]);
+namespace {
+template <int ORDER, bool KC, int ZC>
+hipError_t rhs_launch(const StencilParams &p, const double2 *f, const double *k2, const double4 *fld, double h, double2 *F,
+                      hipStream_t s) {
+    const long long T = (long long)((p.nx + 63) / 64) * ((p.ny + RHS_Y - 1) / RHS_Y) * ((p.nz + ZC - 1) / ZC);
+    hipLaunchKernelGGL((k_rhs<ORDER, KC, ZC>), dim3((unsigned)(8 * ((T + 7) / 8))), dim3(64, RHS_Y), 0, s, f, k2, fld, p.k2i,
+                       p.fldi, F, p.nx, p.ny, p.nz, h);
     return hipGetLastError();
+}
+// the planes of a column follow one another at about 1 us each: long columns only where 1024 blocks remain
+template <int ORDER, bool KC>
+hipError_t rhs_columns(const StencilParams &p, const double2 *f, const double *k2, const double4 *fld, double h, double2 *F,
+                       hipStream_t s) {
+    const long long planes = (long long)((p.nx + 63) / 64) * ((p.ny + RHS_Y - 1) / RHS_Y) * p.nz;
+    if (planes >= 16 * 1024) return rhs_launch<ORDER, KC, 16>(p, f, k2, fld, h, F, s);
+    if (planes >= 4 * 1024) return rhs_launch<ORDER, KC, 4>(p, f, k2, fld, h, F, s);
+    return rhs_launch<ORDER, KC, 1>(p, f, k2, fld, h, F, s);
+}
+}  // namespace
+
+hipError_t launch_rhs(const StencilParams &p, const double2 *f, const double *k2, const double4 *fld, double h, double2 *F,
+                      hipStream_t s) {
+    if (p.order == 2) {
+        const long long n = (long long)p.nx * p.ny * p.nz;
+        hipLaunchKernelGGL(k_rhs2, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, f, F, p.nx, p.ny, n);
+        return hipGetLastError();
+    }
+    if (p.order == 4) return rhs_columns<4, false>(p, f, k2, fld, h, F, s);
+    return p.k2i ? rhs_columns<6, true>(p, f, k2, fld, h, F, s) : rhs_columns<6, false>(p, f, k2, fld, h, F, s);
 }
 
 }  // namespace helm
