@@ -90,7 +90,7 @@ __global__ __launch_bounds__(1024) void k_b_tridiag(const BProb *__restrict__ P,
 // ZT: element type of the Z basis (complex64 with the FP32 preconditioner).
 // A unit is a run of problems of one context (same k^2 and field block, e.g. incident directions on one medium): the
 // blocks of one XCD take the unit's right-hand sides of a tile one after another, so the operator comes from that
-// XCD's L2 for all but the first (16 x 128^3 FP32 form: 420 us a step; with two right-hand sides computed by one block,
+// XCD's L2 for all but the first (16 x 128^3 FP32 form: 490 us a step; with two right-hand sides computed by one block,
 // whose registers left one wave per SIMD, 614 us).
 template <int ORDER, typename ZT>
 __global__ __launch_bounds__(NT) void k_b_matvec(const BProb *__restrict__ P, const BState *__restrict__ st,
