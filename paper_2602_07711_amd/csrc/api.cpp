@@ -77,17 +77,18 @@ helm_status upload_fold(Ctx &c, const EigFold &f, bool xaxis, FoldMats<double2> 
     const double r = 1.0 / std::sqrt(2.0);
     auto block = [&](int nb, const std::vector<cd> &Vi, const std::vector<cd> &V, bool sym, double2 **f64,
                      float2 **f32, double2 **i64, float2 **i32) -> helm_status {
-        std::vector<cd> fw((size_t)nb * nb), iv((size_t)nb * nb);
+        const int P = fold_pad(nb);
+        std::vector<cd> fw((size_t)P * P, 0.0), iv((size_t)P * P, 0.0);
         for (int k = 0; k < nb; ++k)
             for (int i = 0; i < nb; ++i) {
                 const bool mid = sym && i >= f.ma;            // middle of an odd axis: no mirror partner
                 const cd vf = Vi[(size_t)k * nb + i] * (mid ? 0.5 : r);   // mode k from position i
                 const cd vi = V[(size_t)i * nb + k] * (mid ? 1.0 : r);    // position i from mode k
-                fw[xaxis ? (size_t)i * nb + k : (size_t)k * nb + i] = vf;
-                iv[xaxis ? (size_t)k * nb + i : (size_t)i * nb + k] = vi;
+                fw[xaxis ? (size_t)i * P + k : (size_t)k * P + i] = vf;
+                iv[xaxis ? (size_t)k * P + i : (size_t)i * P + k] = vi;
             }
-        ST_TRY(upload_matrix(c, fw, nb, false, f64, f32));
-        ST_TRY(upload_matrix(c, iv, nb, false, i64, i32));
+        ST_TRY(upload_matrix(c, fw, P, false, f64, f32));
+        ST_TRY(upload_matrix(c, iv, P, false, i64, i32));
         return HELM_OK;
     };
     ST_TRY(block(f.ms, f.Vsi, f.Vs, true, &m64.fs, &m32.fs, &m64.is, &m32.is));

@@ -1,5 +1,7 @@
 // Device code of the complex MFMA GEMM, shared by the single-problem and the grouped (batched) kernels.
 #pragma once
+#include <type_traits>
+
 #include "helm_internal.h"
 
 namespace helm {
@@ -90,6 +92,34 @@ __device__ __forceinline__ void mma_kstep(typename cplx<T>::acc (&t)[NS][FM][FN]
                 t[1][i][j] = mfma(fa[i].y, fb[j].x, t[1][i][j]);
             }
     }
+}
+
+// The same for the first NX mode blocks only: along the columns (X) or the rows of the tile.
+template <typename T, bool X, int NX, int RW, int NS, int FM, int FN>
+__device__ __forceinline__ void fold_kstep(typename cplx<T>::acc (&t)[NS][FM][FN], const typename cplx<T>::t (&fa)[FM],
+                                           const typename cplx<T>::t (&fb)[FN]) {
+    typedef typename cplx<T>::t CT;
+    typedef typename cplx<T>::acc ACC;
+    constexpr int M = X ? FM : NX, N = X ? NX : FN;
+    CT a[M], b[N];
+    ACC u[NS][M][N];
+#pragma unroll
+    for (int i = 0; i < M; ++i) a[i] = fa[i];
+#pragma unroll
+    for (int j = 0; j < N; ++j) b[j] = fb[j];
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int i = 0; i < M; ++i)
+#pragma unroll
+            for (int j = 0; j < N; ++j) u[q][i][j] = t[q][i][j];
+    mma_kstep<T, RW, NS>(u, a, b);
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int i = 0; i < M; ++i)
+#pragma unroll
+            for (int j = 0; j < N; ++j) t[q][i][j] = u[q][i][j];
 }
 
 // Complex value held in accumulator register r of block (i, j): 3M (T1, T2, T3) -> (T1 - T2, T3 - T1 - T2).
@@ -230,6 +260,17 @@ __device__ __forceinline__ void gemm_tile(const TA *__restrict__ A, const TB *__
 //   FOLD_YI  y inverse:  P = sum_{k < ms} M_s[j][k] D[k][x],  M = sum_{k < ma} M_a[j][k] D[ms + k][x]
 // with p = s (sign +, K_s = ms, o_s = 0) or a (sign -, K_a = ma, o_a = ms); in the inverse, i (j) < ms and the
 // middle of an odd axis (i = ma, no skew partner: M = 0 there) is written once.
+//
+// Tiles. The long dimension of a transform is its lines (x) or the columns of all its slices in a row (y); the short one
+// its modes (inverse: positions). A workgroup of four waves takes BL lines by BX modes (BM x BN for x, BN x BM for y), a
+// wave BL / 4 lines by all of the tile's modes, so every wave has the same work whatever the number of modes, and a
+// tile computes 64, 48 or 32 modes (BX = 64; 128, 96 or 64 for BX = 128), whichever its half still needs (with waves of
+// 32 x 32 a 200-long axis took 128 modes for its 100, now 112; columns took whole tiles per slice, 256 for its 200).
+// Bound by the matrix cores where they are many (FP64 MFMAs busy 70% of the time at 200^3), by latency where few.
+// One transform, before and after: FP64 200^3 x 168 -> 163 us, y 203 -> 163, y inverse 215 -> 161; 256^3 x 317 -> 304;
+// 32^3 5.2 -> 3.8, inverse 9.1 -> 6.3; FP32 256^3 x 159 -> 152, y inverse 136 -> 130, 64^3 inverse 10.3 -> 7.3.
+// The block matrices are zero-padded to whole tiles (fold_pad), which makes their loads unconditional and lets the
+// data's run past the end of the half: they are clamped to the line's own values, which then meet zeros.
 
 template <int MODE, int BM, int BN> __host__ __device__ inline long long fold_tiles(const FoldDesc &f) {
     return fold_tile_count(MODE, f, BM, BN);
@@ -256,38 +297,31 @@ template <typename T, typename S> __device__ __forceinline__ typename cplx<T>::t
 
 template <typename S> struct Pair { S a, b; };
 
-// The K loop of one tile: raw operands come from loadA(local row, k) and loadB(k, local column) (zero outside) and
-// are staged through LDS double buffered in registers, as in gemm_tile. finA / finB turn a raw operand into the
-// arithmetic type (conversion, the butterfly's sum or difference) only when it is written to LDS, one chunk later:
-// doing it at load time would make every chunk wait for its own loads before the MFMAs that should hide them.
-template <typename T, int BM, int BN, int BK, int NS, int RW, typename LA, typename LB, typename FA, typename FB>
-__device__ __forceinline__ void fold_kloop(typename cplx<T>::acc (&t)[NS][BM / 32][BN / 32], int K, LA loadA,
-                                           LB loadB, FA finA, FB finB, typename cplx<T>::t (*sA)[BM + 1],
-                                           typename cplx<T>::t (*sB)[BN]) {
+// The K loop of one tile: raw operands of chunk k0 come from fetchA(k0, e) and fetchB(k0, e), element e of this thread
+// (e * 256 + thread, A: consecutive threads walk k, B: consecutive threads walk the columns), and are staged through LDS
+// double buffered in registers, as in gemm_tile. finA / finB turn a raw operand into the arithmetic type (conversion, the
+// butterfly's sum or difference) only when it is written to LDS, one chunk later: doing it at load time would make
+// every chunk wait for its own loads before the MFMAs that should hide them. X: the modes are the columns (else the
+// rows); NX: the 16-wide mode blocks that are computed, fixed for the loop (a branch around each block's MFMAs would
+// move accumulators between registers, and the compiler then read some before they were written).
+template <typename T, bool X, int NX, int BM, int BN, int BK, int NS, int RW, int FM, int FN, typename LA, typename LB,
+          typename FA, typename FB>
+__device__ __forceinline__ void fold_kloop(typename cplx<T>::acc (&t)[NS][FM][FN], int K, LA fetchA, LB fetchB, FA finA,
+                                           FB finB, typename cplx<T>::t (*sA)[BM + 1],
+                                           typename cplx<T>::t (*sB)[BN], int tid) {
     typedef typename cplx<T>::t CT;
-    constexpr int FM = BM / 32, FN = BN / 32, EA = BM * BK / 256, EB = BK * BN / 256;
-    // an opaque copy of the thread index: the index arithmetic of two K loops in one kernel (the inverse
-    // transforms) is then not shared between them and held in registers across the first
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
+    constexpr int EA = BM * BK / 256, EB = BK * BN / 256;
     const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    decltype(loadA(0, 0)) ra[EA];
-    decltype(loadB(0, 0)) rb[EB];
+    decltype(fetchA(0, 0)) ra[EA];
+    decltype(fetchB(0, 0)) rb[EB];
     auto fetch = [&](int k0) {
 #pragma unroll
-        for (int e = 0; e < EA; ++e) {
-            const int idx = tid + e * 256;
-            ra[e] = loadA(idx / BK, k0 + idx % BK);       // consecutive threads walk k
-        }
+        for (int e = 0; e < EA; ++e) ra[e] = fetchA(k0, e);
 #pragma unroll
-        for (int e = 0; e < EB; ++e) {
-            const int idx = tid + e * 256;
-            rb[e] = loadB(k0 + idx / BN, idx % BN);       // consecutive threads walk n
-        }
+        for (int e = 0; e < EB; ++e) rb[e] = fetchB(k0, e);
     };
-    const int rowA = wm * (BM / 2) + (lane & 15);
-    const int colB = wn * (BN / 2) + (lane & 15);
+    const int rowA = (X ? wave * FM * 16 : 0) + (lane & 15);
+    const int colB = (X ? 0 : wave * FN * 16) + (lane & 15);
     const int kl = lane >> 4;
     fetch(0);
     for (int k0 = 0; k0 < K; k0 += BK) {
@@ -308,10 +342,10 @@ __device__ __forceinline__ void fold_kloop(typename cplx<T>::acc (&t)[NS][BM / 3
         for (int kk = 0; kk < BK; kk += 4) {
             CT fa[FM], fb[FN];
 #pragma unroll
-            for (int i = 0; i < FM; ++i) fa[i] = sA[kk + kl][rowA + i * 16];
+            for (int i = 0; i < (X ? FM : NX); ++i) fa[i] = sA[kk + kl][rowA + i * 16];
 #pragma unroll
-            for (int j = 0; j < FN; ++j) fb[j] = sB[kk + kl][colB + j * 16];
-            mma_kstep<T, RW, NS>(t, fa, fb);
+            for (int j = 0; j < (X ? NX : FN); ++j) fb[j] = sB[kk + kl][colB + j * 16];
+            fold_kstep<T, X, NX, RW, NS>(t, fa, fb);
         }
     }
 }
@@ -322,15 +356,19 @@ __device__ __forceinline__ void fold_tile(const TD *__restrict__ D, const TM *__
                                           TC *__restrict__ C, const FoldDesc &f, long long tile) {
     typedef typename cplx<T>::t CT;
     typedef typename cplx<T>::acc ACC;
-    constexpr int FM = BM / 32, FN = BN / 32;
+    constexpr bool X = MODE == FOLD_XF || MODE == FOLD_XI, FWD = MODE == FOLD_XF || MODE == FOLD_YF;
+    constexpr int BL = X ? BM : BN, BX = X ? BN : BM;         // lines and modes of a tile
+    constexpr int FM = X ? BM / 64 : BM / 16, FN = X ? BN / 16 : BN / 64;
     constexpr int NS = (sizeof(T) == 4 && RW == 0) ? 3 : 2;
     __shared__ CT sA[BK][BM + 1];
     __shared__ CT sB[BK][BN];
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int n = f.n, ms = f.ms, ma = f.ma, rows = f.rows;
+    const int n = f.n, ms = f.ms, ma = f.ma;
+    const int lines = f.rows * f.batch;                       // x: lines (batch = 1); y: columns of all slices
     const long long ld = f.ld;
+    const int hs = (ms + BX - 1) / BX, ha = FWD ? (ma + BX - 1) / BX : 0;
+    const int lt = (int)(tile / (hs + ha)), r = (int)(tile % (hs + ha));   // the tiles of the same lines are neighbours
+    const int l0 = lt * BL;
 
     ACC t[NS][FM][FN];
     auto zero = [&]() {
@@ -341,172 +379,134 @@ __device__ __forceinline__ void fold_tile(const TD *__restrict__ D, const TM *__
 #pragma unroll
                 for (int j = 0; j < FN; ++j) t[q][i][j] = ACC{0, 0, 0, 0};
     };
-    zero();
+    // the product of half `skew`, mode block x0: the data of the forward transforms is folded, that of the inverse ones
+    // starts at mode `off`, stride mst
+    auto product = [&](bool skew, int x0) {
+        // an opaque copy of the thread index: the index arithmetic of two K loops in one kernel (the inverse
+        // transforms) is then not shared between them and held in registers across the first
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int K = skew ? ma : ms, P = fold_pad(K), off = skew ? f.moff : 0, mst = f.mstep;
+        const int nblk = (min(K, x0 + BX) - x0 + 15) / 16;
+        const TM *Mp = (skew ? Ma : Ms) + (X ? x0 : (long long)x0 * P);
+        const int last = FWD ? n - 1 : K - 1;
+        auto run = [&](auto loop) {
+            constexpr int FX = BX / 16;
+            if (nblk > FX * 3 / 4) loop(std::integral_constant<int, FX>());
+            else if (nblk > FX / 2) loop(std::integral_constant<int, FX * 3 / 4>());
+            else loop(std::integral_constant<int, FX / 2>());
+        };
+        auto fmat = [](const TM &v) { return cvt<T>(v); };
+        auto fdat = [&](const auto &v) {
+            if constexpr (FWD) return fold2<T>(v.a, v.b, skew);
+            else return cvt<T>(v);
+        };
+        if constexpr (X) {
+            const TD *base = D + l0 * ld;
+            auto la = [&](int k0, int e) {
+                const int idx = tid + e * 256, gk = min(k0 + idx % BK, last);
+                const int line = min(idx / BK, lines - 1 - l0);
+                const unsigned row = (unsigned)line * (unsigned)ld;
+                if constexpr (FWD) return Pair<TD>{base[row + gk], base[row + (n - 1 - gk)]};
+                else return base[row + off + mst * gk];
+            };
+            auto lb = [&](int k0, int e) { return (Mp + (long long)k0 * P)[(unsigned)((tid + e * 256) / BN * P + (tid + e * 256) % BN)]; };
+            run([&](auto nx) { fold_kloop<T, X, decltype(nx)::value, BM, BN, BK, NS, RW>(t, K, la, lb, fdat, fmat, sA, sB, tid); });
+        } else {
+            const int col = min(l0 + tid % BN, lines - 1);
+            const TD *base = D + (long long)(col / f.rows) * f.sD + col % f.rows + (FWD ? 0 : off * ld);
+            // positions as 32-bit offsets (an axis times its stride is at most the vector's 2^31 entries)
+            const unsigned uld = (unsigned)ld, top = (unsigned)(n - 1) * uld, end = (unsigned)last * uld;
+            const unsigned first = (unsigned)(tid / BN) * uld;
+            auto la = [&](int k0, int e) { return (Mp + k0)[(unsigned)((tid + e * 256) / BK * P + (tid + e * 256) % BK)]; };
+            auto lb = [&](int k0, int e) {
+                const unsigned o = min(first + (unsigned)(k0 + e * (256 / BN)) * uld, end);
+                if constexpr (FWD) return Pair<TD>{base[o], base[top - o]};
+                else return base[mst == 1 ? o : 2 * o];
+            };
+            run([&](auto nx) { fold_kloop<T, X, decltype(nx)::value, BM, BN, BK, NS, RW>(t, K, la, lb, fmat, fdat, sA, sB, tid); });
+        }
+    };
+    // line and mode (position) of accumulator register r of block (i, j), and the line's offset
+    const int lane0 = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto place = [&](int lane, int i, int j, int r, int &line, int &x) {
+        const int row = i * 16 + acc_row<T>(lane, r), col = j * 16 + (lane & 15);
+        line = l0 + (X ? wave * FM * 16 + row : wave * FN * 16 + col);
+        x = X ? col : row;
+    };
+    auto at = [&](int line) -> long long {                    // x: start of the line; y: the column's first element
+        if constexpr (X) return line * ld;
+        else return (long long)(line / f.rows) * f.sD + line % f.rows;
+    };
+    const long long step = X ? 1 : ld;                        // between modes (positions) of a line
 
-    if constexpr (MODE == FOLD_XF || MODE == FOLD_YF) {
-        int mt, nt;
-        bool skew;
-        if constexpr (MODE == FOLD_XF) {
-            const int hs = (ms + BN - 1) / BN, ha = (ma + BN - 1) / BN;
-            mt = (int)(tile / (hs + ha));
-            const int r = (int)(tile % (hs + ha));
-            skew = r >= hs;
-            nt = skew ? r - hs : r;
-        } else {
-            const int hs = (ms + BM - 1) / BM, ha = (ma + BM - 1) / BM, tn = (rows + BN - 1) / BN;
-            const long long per_slice = (long long)(hs + ha) * tn;
-            const long long b = tile / per_slice;
-            const int rem = (int)(tile % per_slice);
-            const int r = rem / tn;
-            nt = rem % tn;
-            skew = r >= hs;
-            mt = skew ? r - hs : r;
-            D += b * f.sD;
-            C += b * f.sD;
-        }
+    if constexpr (FWD) {
+        const bool skew = r >= hs;
+        const int x0 = (skew ? r - hs : r) * BX;
         const int K = skew ? ma : ms, off = skew ? f.moff : 0, mst = f.mstep;
-        const TM *Mp = skew ? Ma : Ms;
-        const int m0 = mt * BM, n0 = nt * BN;
-        if constexpr (MODE == FOLD_XF) {
-            auto la = [&](int mm, int gk) -> Pair<TD> {
-                const int gm = m0 + mm;
-                if (gm >= rows || gk >= K) return Pair<TD>{TD{0, 0}, TD{0, 0}};
-                const TD *row = D + (long long)gm * ld;
-                return Pair<TD>{row[gk], row[n - 1 - gk]};
-            };
-            auto lb = [&](int gk, int nn) -> TM {
-                const int gn = n0 + nn;
-                return (gk < K && gn < K) ? Mp[(long long)gk * K + gn] : TM{0, 0};
-            };
-            auto fa = [&](const Pair<TD> &p) { return fold2<T>(p.a, p.b, skew); };
-            auto fb = [](const TM &v) { return cvt<T>(v); };
-            fold_kloop<T, BM, BN, BK, NS, RW>(t, K, la, lb, fa, fb, sA, sB);
-        } else {
-            auto la = [&](int mm, int gk) -> TM {
-                const int gm = m0 + mm;
-                return (gm < K && gk < K) ? Mp[(long long)gm * K + gk] : TM{0, 0};
-            };
-            auto lb = [&](int gk, int nn) -> Pair<TD> {
-                const int gn = n0 + nn;
-                if (gk >= K || gn >= rows) return Pair<TD>{TD{0, 0}, TD{0, 0}};
-                return Pair<TD>{D[(long long)gk * ld + gn], D[(long long)(n - 1 - gk) * ld + gn]};
-            };
-            auto fa = [](const TM &v) { return cvt<T>(v); };
-            auto fb = [&](const Pair<TD> &p) { return fold2<T>(p.a, p.b, skew); };
-            fold_kloop<T, BM, BN, BK, NS, RW>(t, K, la, lb, fa, fb, sA, sB);
-        }
+        zero();
+        product(skew, x0);
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int gn = n0 + wn * (BN / 2) + j * 16 + (lane & 15);
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int gm = m0 + wm * (BM / 2) + i * 16 + acc_row<T>(lane, r);
+                for (int q = 0; q < 4; ++q) {
+                    int line, x;
+                    place(lane0, i, j, q, line, x);
                     T re, im;
-                    acc_value<T>(t, i, j, r, re, im);
-                    if constexpr (MODE == FOLD_XF) {
-                        if (gm < rows && gn < K) C[(long long)gm * ld + off + mst * gn] = pack<TC, T>(re, im);
-                    } else {
-                        if (gm < K && gn < rows) C[(long long)(off + mst * gm) * ld + gn] = pack<TC, T>(re, im);
-                    }
+                    acc_value<T>(t, i, j, q, re, im);
+                    if (line < lines && x0 + x < K) C[at(line) + (off + mst * (x0 + x)) * step] = pack<TC, T>(re, im);
                 }
-            }
     } else {
         // FP32 64 x 64 tiles park P in LDS (32 KiB per block, read back only by the thread that wrote it)
         constexpr bool PLDS = sizeof(T) == 4 && FM * FN * 4 * 256 * sizeof(CT) <= 32768;
         __shared__ CT sP[PLDS ? FM * FN * 4 * 256 : 1];
-        int mt, nt;
-        if constexpr (MODE == FOLD_XI) {
-            const int tn = (ms + BN - 1) / BN;
-            mt = (int)(tile / tn);
-            nt = (int)(tile % tn);
-        } else {
-            const int tm = (ms + BM - 1) / BM, tn = (rows + BN - 1) / BN;
-            const long long b = tile / ((long long)tm * tn);
-            const int rem = (int)(tile % ((long long)tm * tn));
-            mt = rem / tn;
-            nt = rem % tn;
-            D += b * f.sD;
-            C += b * f.sD;
-        }
-        const int m0 = mt * BM, n0 = nt * BN;
-        // output slot (position i or j < ms, the other index) of accumulator register r of block (i, j)
-        auto slot = [&](int ln, int i, int j, int r, int &gm, int &gn) -> bool {
-            gm = m0 + wm * (BM / 2) + i * 16 + acc_row<T>(ln, r);
-            gn = n0 + wn * (BN / 2) + j * 16 + (ln & 15);
-            return MODE == FOLD_XI ? (gm < rows && gn < ms) : (gm < ms && gn < rows);
-        };
+        const int x0 = r * BX;
+        zero();
+        product(false, x0);
+        // park P in this thread's own output slots (first half of the axis; the skew results go to the disjoint second
+        // half), or for the FP32 64 x 64 tile in a per-thread LDS area, instead of holding a second accumulator set in
+        // registers
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int K = q ? ma : ms, off = q ? f.moff : 0, mst = f.mstep;
-            const TM *Mq = q ? Ma : Ms;
-            if constexpr (MODE == FOLD_XI) {
-                auto la = [&](int mm, int gk) -> TD {
-                    const int gm = m0 + mm;
-                    return (gm < rows && gk < K) ? D[(long long)gm * ld + off + mst * gk] : TD{0, 0};
-                };
-                auto lb = [&](int gk, int nn) -> TM {
-                    const int gn = n0 + nn;
-                    return (gk < K && gn < K) ? Mq[(long long)gk * K + gn] : TM{0, 0};
-                };
-                auto fa = [](const TD &v) { return cvt<T>(v); };
-                auto fb = [](const TM &v) { return cvt<T>(v); };
-                fold_kloop<T, BM, BN, BK, NS, RW>(t, K, la, lb, fa, fb, sA, sB);
-            } else {
-                auto la = [&](int mm, int gk) -> TM {
-                    const int gm = m0 + mm;
-                    return (gm < K && gk < K) ? Mq[(long long)gm * K + gk] : TM{0, 0};
-                };
-                auto lb = [&](int gk, int nn) -> TD {
-                    const int gn = n0 + nn;
-                    return (gk < K && gn < rows) ? D[(long long)(off + mst * gk) * ld + gn] : TD{0, 0};
-                };
-                auto fa = [](const TM &v) { return cvt<T>(v); };
-                auto fb = [](const TD &v) { return cvt<T>(v); };
-                fold_kloop<T, BM, BN, BK, NS, RW>(t, K, la, lb, fa, fb, sA, sB);
-            }
-            if (q == 0) {
-                // park P in this thread's own output slots (first half of the axis; the skew results go to the
-                // disjoint second half), or for the FP32 64 x 64 tile in a per-thread LDS area, instead of holding a
-                // second accumulator set in registers
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-                    for (int j = 0; j < FN; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            int gm, gn;
-                            if (!slot(lane, i, j, r, gm, gn)) continue;
-                            T re, im;
-                            acc_value<T>(t, i, j, r, re, im);
-                            if constexpr (PLDS) sP[((i * FN + j) * 4 + r) * 256 + threadIdx.x] = pack<CT, T>(re, im);
-                            else C[(long long)gm * ld + gn] = pack<TC, T>(re, im);
-                        }
-                zero();
-                // a compiler memory barrier: the epilogue reloads P instead of the stored values being
-                // forwarded to it in registers through the second K loop
-                asm volatile("" ::: "memory");
-            }
-        }
+                for (int q = 0; q < 4; ++q) {
+                    int line, x;
+                    place(lane0, i, j, q, line, x);
+                    T re, im;
+                    acc_value<T>(t, i, j, q, re, im);
+                    if constexpr (PLDS) sP[((i * FN + j) * 4 + q) * 256 + threadIdx.x] = pack<CT, T>(re, im);
+                    else if (line < lines && x0 + x < ms) C[at(line) + (x0 + x) * step] = pack<TC, T>(re, im);
+                }
+        zero();
+        // a compiler memory barrier: the epilogue reloads P instead of the stored values being forwarded to it in
+        // registers through the second K loop
+        asm volatile("" ::: "memory");
+        if (x0 < ma) product(true, x0);
         // the epilogue recomputes the slot addresses (an opaque copy of the lane index) rather than keeping the
         // park step's addresses alive through the second K loop
-        int lane_e = lane;
+        int lane_e = lane0;
         asm volatile("" : "+v"(lane_e));
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    int gm, gn;
-                    if (!slot(lane_e, i, j, r, gm, gn)) continue;
+                for (int q = 0; q < 4; ++q) {
+                    int line, x;
+                    place(lane_e, i, j, q, line, x);
+                    const int pos = x0 + x;                   // position along the transformed axis
+                    if (line >= lines || pos >= ms) continue;
                     T re, im;
-                    acc_value<T>(t, i, j, r, re, im);
-                    TC *c = C + (long long)gm * ld + gn;
+                    acc_value<T>(t, i, j, q, re, im);
+                    const long long o = at(line);
+                    TC *c = C + o + pos * step;
                     T p0, p1;
                     if constexpr (PLDS) {
-                        const CT pv = sP[((i * FN + j) * 4 + r) * 256 + threadIdx.x];
+                        const CT pv = sP[((i * FN + j) * 4 + q) * 256 + threadIdx.x];
                         p0 = pv.x;
                         p1 = pv.y;
                     } else {
@@ -514,14 +514,11 @@ __device__ __forceinline__ void fold_tile(const TD *__restrict__ D, const TM *__
                         p0 = (T)pv.x;
                         p1 = (T)pv.y;
                     }
-                    const int h = MODE == FOLD_XI ? gn : gm;     // position along the transformed axis
-                    if (h < ma) {
+                    if (pos < ma) {
                         *c = pack<TC, T>(p0 + re, p1 + im);
-                        TC *mirror = MODE == FOLD_XI ? C + (long long)gm * ld + (n - 1 - gn)
-                                                     : C + (long long)(n - 1 - gm) * ld + gn;
-                        *mirror = pack<TC, T>(p0 - re, p1 - im);
+                        C[o + (n - 1 - pos) * step] = pack<TC, T>(p0 - re, p1 - im);
                     } else if constexpr (PLDS) {
-                        *c = pack<TC, T>(p0, p1);                 // the middle of an odd axis: P alone
+                        *c = pack<TC, T>(p0, p1);             // the middle of an odd axis: P alone
                     }
                 }
     }

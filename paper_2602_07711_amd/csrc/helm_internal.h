@@ -70,23 +70,24 @@ struct FoldDesc {
                                  // k * mstep ([symmetric | skew]: moff = ms, mstep = 1; the sine basis keeps its
                                  // natural order, even modes symmetric and odd ones skew: moff = 1, mstep = 2)
 };
-// the blocks of one axis, row-major: forward (x: [position][mode], y: [mode][position]) and inverse
+// the blocks of one axis, row-major and zero-padded (fold_pad): forward (x: [position][mode], y: [mode][position]) and inverse
 // (x: [mode][position], y: [position][mode]), each for the symmetric (ms x ms) and skew (ma x ma) half
 template <typename CT> struct FoldMats {
     CT *fs = nullptr, *fa = nullptr, *is = nullptr, *ia = nullptr;
 };
 enum { FOLD_XF = 0, FOLD_YF = 1, FOLD_XI = 2, FOLD_YI = 3 };
-// tiles of a folded transform with bm x bn output tiles: the forward ones cover both halves' outputs, the inverse
-// ones the first half of the positions (each writes its mirror too)
+// tiles of a folded transform with bm x bn tiles (rows x columns of its product; x: lines x modes, y: modes x columns of
+// all slices): the forward ones cover both halves' modes, the inverse ones the first half of the positions (each writes
+// its mirror too)
 __host__ __device__ inline long long fold_tile_count(int mode, const FoldDesc &f, int bm, int bn) {
-    const long long tm = (f.rows + bm - 1) / bm, tn = (f.rows + bn - 1) / bn;
-    const long long hs_m = (f.ms + bm - 1) / bm, ha_m = (f.ma + bm - 1) / bm;
-    const long long hs_n = (f.ms + bn - 1) / bn, ha_n = (f.ma + bn - 1) / bn;
-    if (mode == FOLD_XF) return tm * (hs_n + ha_n);
-    if (mode == FOLD_YF) return (long long)f.batch * (hs_m + ha_m) * tn;
-    if (mode == FOLD_XI) return tm * hs_n;
-    return (long long)f.batch * hs_m * tn;
+    const bool x = mode == FOLD_XF || mode == FOLD_XI;
+    const int bl = x ? bm : bn, bx = x ? bn : bm;
+    const long long tl = ((long long)f.rows * f.batch + bl - 1) / bl, hs = (f.ms + bx - 1) / bx, ha = (f.ma + bx - 1) / bx;
+    return tl * (mode == FOLD_XF || mode == FOLD_YF ? hs + ha : hs);
 }
+// the blocks are stored zero-padded to whole tiles: leading dimension and rows of the block of a half with m modes
+constexpr int FOLD_PAD = 128;
+__host__ __device__ inline int fold_pad(int m) { return (m + FOLD_PAD - 1) / FOLD_PAD * FOLD_PAD; }
 hipError_t launch_fold_z64(int mode, const FoldDesc &f, const double2 *D, const double2 *Ms, const double2 *Ma,
                            double2 *C, hipStream_t s, int cfg, bool real = false);
 hipError_t launch_fold_z32(int mode, const FoldDesc &f, const float2 *D, const float2 *Ms, const float2 *Ma, float2 *C,
