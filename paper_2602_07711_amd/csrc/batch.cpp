@@ -99,11 +99,12 @@ helm_status helm_batch_create(helm_batch **out, helm_ctx *const *ctxs, int np, i
     const int rcfg[4] = {c0.gemm_cfg[kx], c0.gemm_cfg[ky], c0.gemm_cfg_inv[ky], c0.gemm_cfg_inv[kx]};
     int bm[4], bn[4];
     for (int r = 0; r < 4; ++r) gemm_cfg_tile(rcfg[r], bm[r], bn[r]);
-    // z-solve block shape: 16 lines x the largest problem's chunk count (at most 1024 threads)
+    // z-solve block shape: 16 lines (FP32: 32, as in the single solve) x the largest problem's chunk count (at most 1024
+    // threads)
     int tri_pb = 1;
     for (int p = 0; p < np; ++p) tri_pb = std::max(tri_pb, tri_chunks(ctxs[p]->c.nz));
     if (tri_pb > 1024) return fail(HELM_EUNSUPPORTED, "z-extent too large for the partitioned z-solve");
-    int tri_lx = 16;
+    int tri_lx = b->fp32 ? 32 : 16;
     while (tri_lx > 1 && tri_lx * tri_pb > 1024) tri_lx /= 2;
     // per-problem descriptors, work buffers and launch offsets
     std::vector<int> omv(1, 0), otri(1, 0), odot(1, 0), olc(1, 0);
@@ -158,7 +159,7 @@ helm_status helm_batch_create(helm_batch **out, helm_ctx *const *ctxs, int np, i
         q.F = nullptr;
         int T = q.sp.tiles_x * q.sp.tiles_y * q.sp.zchunks;
         omv.push_back(omv.back() + 8 * ((T + 7) / 8));
-        otri.push_back(otri.back() + (int)(((long long)c.nx * c.ny + tri_lx - 1) / tri_lx));
+        otri.push_back(otri.back() + 8 * (int)((((long long)c.nx * c.ny + tri_lx - 1) / tri_lx + 7) / 8));
         odot.push_back(odot.back() + q.nblk_dots);
         olc.push_back(olc.back() + (int)((c.n + 1023) / 1024));
         og[0].push_back(og[0].back() + fold_tile_count(FOLD_XF, q.fx, bm[0], bn[0]));

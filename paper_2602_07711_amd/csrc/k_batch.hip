@@ -77,12 +77,13 @@ __global__ __launch_bounds__(1024) void k_b_tridiag(const BProb *__restrict__ P,
     const int p = find_prob(off, np, blockIdx.x);
     if (!st[p].active) return;                 // uniform over the block
     const BProb &q = P[p];
+    const long long blk = tri_place<CT>(blockIdx.x - off[p], ((long long)q.nx * q.ny + LX - 1) / LX, (long long)q.nx * q.ny);
     if constexpr (std::is_same<T, float>::value)
         tri_chunk_block<T, float2>((const CT *)q.t2, (CT *)q.t2, q.tpiv32, q.dxe, q.dye, q.nx, q.ny, q.nz,
-                                   (q.nz + TL - 1) / TL, LX, q.ax, q.ay, q.c0, q.gz, q.hz2, blockIdx.x - off[p], smraw);
+                                   (q.nz + TL - 1) / TL, LX, q.ax, q.ay, q.c0, q.gz, q.hz2, blk, smraw);
     else
         tri_chunk_block<T, double2>((const CT *)q.t2, (CT *)q.t2, q.tpiv, q.dxe, q.dye, q.nx, q.ny, q.nz,
-                                    (q.nz + TL - 1) / TL, LX, q.ax, q.ay, q.c0, q.gz, q.hz2, blockIdx.x - off[p], smraw);
+                                    (q.nz + TL - 1) / TL, LX, q.ax, q.ay, q.c0, q.gz, q.hz2, blk, smraw);
 }
 
 // ---------------------------------------------------------------------------------------------- matvec

@@ -218,15 +218,23 @@ __global__ __launch_bounds__(256) void k_ring_fwd_write(const typename c2<T>::t 
     const CT *WyN = WyT + (long long)(ny - 1) * ny, *WxN = WxT + (long long)(nx - 1) * nx;
     for (int i = threadIdx.x; i < nx; i += 256) {
         const CT s0 = S[i], sN = S[nx + i], x0 = WxT[i], xN = WxN[i];
-        for (int j = j0; j < j1; ++j) {
-            const long long e = (long long)l * plane + (long long)j * nx + i;
-            CT acc = cz<CT>();
-            if (base) { acc = base[e]; acc.x *= base_scale; acc.y *= base_scale; }
-            acc = cfma(WyT[j], s0, acc);
-            acc = cfma(WyN[j], sN, acc);
-            acc = cfma(Tc[j], x0, acc);
-            acc = cfma(Tc[ny + j], xN, acc);
-            out[e] = acc;
+        // four rows of `base` in flight
+        for (int j = j0; j < j1; j += 4) {
+            CT acc[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[u] = base ? base[(long long)l * plane + (long long)min(j + u, j1 - 1) * nx + i] : cz<CT>();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (j + u >= j1) break;
+                CT a = acc[u];
+                a.x *= base_scale;
+                a.y *= base_scale;
+                a = cfma(WyT[j + u], s0, a);
+                a = cfma(WyN[j + u], sN, a);
+                a = cfma(Tc[j + u], x0, a);
+                a = cfma(Tc[ny + j + u], xN, a);
+                out[(long long)l * plane + (long long)(j + u) * nx + i] = a;
+            }
         }
     }
 }

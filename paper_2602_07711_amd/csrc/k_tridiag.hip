@@ -58,7 +58,9 @@ __global__ __launch_bounds__(1024) void k_tridiag_chunk(const typename c2<T>::t 
                                                         int nx, int ny, int nz, int P, int LX, double ax, double ay,
                                                         double c0, double2 gz, double scale, double zi) {
     extern __shared__ unsigned char smraw[];
-    tri_chunk_block<T, PT>(in, out, piv, dx, dy, nx, ny, nz, P, LX, ax, ay, c0, gz, scale, blockIdx.x, smraw, zi);
+    tri_chunk_block<T, PT>(in, out, piv, dx, dy, nx, ny, nz, P, LX, ax, ay, c0, gz, scale,
+                           tri_place<typename c2<T>::t>(blockIdx.x, ((long long)nx * ny + LX - 1) / LX, (long long)nx * ny),
+                           smraw, zi);
 }
 
 template <typename T, typename PT>
@@ -71,7 +73,7 @@ hipError_t launch_chunk(const typename c2<T>::t *in, typename c2<T>::t *out, con
     int LX = sizeof(T) == 4 ? 32 : 16;
     while (LX > 1 && LX * P > 1024) LX /= 2;
     const long long lines = (long long)nx * ny;
-    const unsigned grid = (unsigned)((lines + LX - 1) / LX);
+    const unsigned grid = (unsigned)(8 * (((lines + LX - 1) / LX + 7) / 8));
     const size_t sm = 2 * sizeof(typename c2<T>::t) * (size_t)P * LX;
     hipLaunchKernelGGL((k_tridiag_chunk<T, PT>), dim3(grid), dim3(LX * P), sm, s, in, out, piv, dx, dy, nx, ny, nz, P,
                        LX, ax, ay, c0, gz, scale, zi);
