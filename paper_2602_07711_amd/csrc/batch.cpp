@@ -139,7 +139,7 @@ helm_status helm_batch_create(helm_batch **out, helm_ctx *const *ctxs, int np, i
         q.fy = FoldDesc{c.ny, c.ny - c.ny / 2, c.ny / 2, c.nx, c.nx, (long long)c.nx * c.ny, c.nz, c.ny - c.ny / 2, 1};
         q.n = c.n;
         q.nx = c.nx; q.ny = c.ny; q.nz = c.nz;
-        q.nblk_dots = dots_blocks(c.n);
+        q.nblk_dots = batch_dots_blocks(c.n);
         void *zb = nullptr;
         if (balloc(*b, &q.V, (size_t)(m + 1) * c.n) != hipSuccess || hipMalloc(&zb, esz * m * c.n) != hipSuccess)
             return fail(HELM_ENOMEM, "Krylov workspace allocation failed");

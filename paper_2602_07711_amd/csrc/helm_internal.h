@@ -377,7 +377,8 @@ hipError_t launch_ring_forward_z32(const float2 *ra, const float2 *rb, const flo
                                    int nz, float2 *rbuf, float2 *fvec, hipStream_t s);
 
 // Krylov helpers
-int dots_blocks(long long n);
+int dots_blocks(long long n);         // of a single solve
+int batch_dots_blocks(long long n);   // of a problem in a batch
 hipError_t launch_dots(const double2 *V, long long ldv, int nv, const double2 *w, long long n, double2 *partials,
                        int nblocks, double2 *red, hipStream_t s);   // red[0..nv-1] = V_i^H w, red[nv] = (|w|^2, 0)
 hipError_t launch_lincomb(double2 *out, const double2 *base, double2 alpha, const double2 *V, long long ldv, int nv,

@@ -122,9 +122,9 @@ __global__ __launch_bounds__(256) void k_b_dots(const BProb *__restrict__ P, con
     if (mode == 3 && !(st[p].active && st[p].reo)) return;
     const BProb &q = P[p];
     const long long lb = blockIdx.x - off[p];
-    if (mode == 0) dots_chunk(nullptr, q.n, 0, q.F, q.n, q.part, lb);
-    else if (mode == 1) dots_chunk(nullptr, q.n, 0, q.V, q.n, q.part, lb);
-    else dots_chunk(q.V, q.n, j + 1, q.V + (long long)(j + 1) * q.n, q.n, q.part, lb);
+    if (mode == 0) dots_chunk<DOT_EPT>(nullptr, q.n, 0, q.F, q.n, q.part, lb);
+    else if (mode == 1) dots_chunk<DOT_EPT>(nullptr, q.n, 0, q.V, q.n, q.part, lb);
+    else dots_chunk<DOT_EPT>(q.V, q.n, j + 1, q.V + (long long)(j + 1) * q.n, q.n, q.part, lb);
 }
 
 // fixed-order block reduction of the partials of output t (nout outputs); result valid in thread 0

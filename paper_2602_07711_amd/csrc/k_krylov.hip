@@ -9,10 +9,15 @@ namespace helm {
 
 namespace {
 
+constexpr int DOT_GROUP = 8;   // short vectors: basis vectors per block
+
 // partials of output t are contiguous: part[t * gridDim.x + block], so the reduction reads them coalesced
+template <int EPT>
 __global__ __launch_bounds__(256) void k_dots(const double2 *__restrict__ V, long long ldv, int nv,
                                               const double2 *__restrict__ w, long long n, double2 *__restrict__ part) {
-    dots_chunk(V, ldv, nv, w, n, part, blockIdx.x, 1, gridDim.x);
+    const int t0 = blockIdx.y * DOT_GROUP, cnt = EPT == DOT_EPT ? nv : min(nv - t0, DOT_GROUP);
+    dots_chunk<EPT>(V + t0 * ldv, ldv, cnt, w, n, part + (long long)t0 * gridDim.x, blockIdx.x, 1, gridDim.x,
+                    t0 + cnt == nv);
 }
 
 __global__ __launch_bounds__(256) void k_reduce(const double2 *__restrict__ part, int nblocks, int nout,
@@ -106,45 +111,53 @@ __global__ __launch_bounds__(256) void k_lincomb(double2 *out, const double2 *ba
 // products red[0..nv-1] = V_i^H w and red[nv] = ||w||^2: eta^2 = ||w||^2 - sum |h_i|^2 and, when no severe
 // cancellation happened (eta^2 > reorth ||w||^2), w <- -(w - V h) / eta; otherwise w <- -(w - V h) unscaled, for
 // the host's second Gram-Schmidt pass. Every block recomputes the (uniform) coefficients, so no host round trip sits between the
-// inner products and the update.
+// inner products and the update. Four elements per thread where that still gives a block per CU (128^3: bandwidth, 6.3 TB/s),
+// one below (32^3: 32 blocks -> 128; dots and update together take a 32^3 solve from 884 to 848 us).
+template <int EPT>
 __global__ __launch_bounds__(256) void k_lincomb_cgs(double2 *w, const double2 *__restrict__ V, long long ldv, int nv,
                                                      const double2 *__restrict__ red, long long n, double reorth) {
+    constexpr int NV = EPT == 1 ? 8 : 4;   // vectors per round
+    const long long start = (long long)blockIdx.x * (256 * EPT) + threadIdx.x;
+    long long idx[EPT];                    // past the end: the last element, read and not written
+    double2 acc[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        idx[e] = start + (long long)e * 256 < n ? start + (long long)e * 256 : n - 1;
+        acc[e] = ld_stream(w + idx[e]);
+    }
     double hh = 0.0;
-    for (int i = 0; i < nv; ++i) {
+    int i = 0;
+    for (; i + 8 <= nv; i += 8) {          // eight products in flight; summed one after another, as the host does
+        double2 r[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r[q] = red[i + q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            hh = fma(r[q].x, r[q].x, hh);
+            hh = fma(r[q].y, r[q].y, hh);
+        }
+    }
+    for (; i < nv; ++i) {
         const double2 r = red[i];
         hh = fma(r.x, r.x, hh);
         hh = fma(r.y, r.y, hh);
     }
     const double ww = red[nv].x, eta2 = ww - hh;
     const double inv = eta2 > reorth * ww ? 1.0 / sqrt(eta2) : 1.0;
-    const long long start = (long long)blockIdx.x * (256 * LC_EPT) + threadIdx.x;
-    double2 acc[LC_EPT];
-    bool ok[LC_EPT];
 #pragma unroll
-    for (int e = 0; e < LC_EPT; ++e) {
-        const long long idx = start + (long long)e * 256;
-        ok[e] = idx < n;
-        acc[e] = make_double2(0.0, 0.0);
-        if (ok[e]) {
-            const double2 b = ld_stream(w + idx);
-            acc[e] = make_double2(-inv * b.x, -inv * b.y);
-        }
-    }
-    int i = 0;
-    for (; i + 4 <= nv; i += 4) {
-        double2 v[4][LC_EPT];
+    for (int e = 0; e < EPT; ++e) acc[e] = make_double2(-inv * acc[e].x, -inv * acc[e].y);
+    i = 0;
+    for (; i + NV <= nv; i += NV) {
+        double2 v[NV][EPT];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < NV; ++q)
 #pragma unroll
-            for (int e = 0; e < LC_EPT; ++e) {
-                const long long idx = start + (long long)e * 256;
-                v[q][e] = ok[e] ? ld_stream(V + (long long)(i + q) * ldv + idx) : make_double2(0.0, 0.0);
-            }
+            for (int e = 0; e < EPT; ++e) v[q][e] = ld_stream(V + (long long)(i + q) * ldv + idx[e]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < NV; ++q) {
             const double2 c = make_double2(red[i + q].x * inv, red[i + q].y * inv);
 #pragma unroll
-            for (int e = 0; e < LC_EPT; ++e) {
+            for (int e = 0; e < EPT; ++e) {
                 acc[e].x += c.x * v[q][e].x - c.y * v[q][e].y;
                 acc[e].y += c.x * v[q][e].y + c.y * v[q][e].x;
             }
@@ -152,23 +165,18 @@ __global__ __launch_bounds__(256) void k_lincomb_cgs(double2 *w, const double2 *
     }
     for (; i < nv; ++i) {
         const double2 c = make_double2(red[i].x * inv, red[i].y * inv);
-        double2 v[LC_EPT];
+        double2 v[EPT];
 #pragma unroll
-        for (int e = 0; e < LC_EPT; ++e) {
-            const long long idx = start + (long long)e * 256;
-            v[e] = ok[e] ? ld_stream(V + (long long)i * ldv + idx) : make_double2(0.0, 0.0);
-        }
+        for (int e = 0; e < EPT; ++e) v[e] = ld_stream(V + (long long)i * ldv + idx[e]);
 #pragma unroll
-        for (int e = 0; e < LC_EPT; ++e) {
+        for (int e = 0; e < EPT; ++e) {
             acc[e].x += c.x * v[e].x - c.y * v[e].y;
             acc[e].y += c.x * v[e].y + c.y * v[e].x;
         }
     }
 #pragma unroll
-    for (int e = 0; e < LC_EPT; ++e) {
-        const long long idx = start + (long long)e * 256;
-        if (ok[e]) w[idx] = acc[e];
-    }
+    for (int e = 0; e < EPT; ++e)
+        if (start + (long long)e * 256 < n) w[start + (long long)e * 256] = acc[e];
 }
 
 __global__ void k_to_c64(const double2 *__restrict__ x, float2 *__restrict__ y, long long n) {
@@ -183,12 +191,27 @@ __global__ void k_zero(double2 *x, long long n) {
 
 }  // namespace
 
-int dots_blocks(long long n) { return (int)((n + DOT_CHUNK - 1) / DOT_CHUNK); }
+// 16 elements per thread where that still gives a block per CU, else 4 or 1, with eight basis vectors per block: a short
+// vector's pass is latency, and its blocks were few. 64^3: 64 blocks, 15.9 us -> 256 blocks of 4 elements per eight
+// vectors, 9.3 us; 32^3: 8 blocks, 6.6 us -> 128 of one element, 4.1 us. At 127^3 (500 blocks) 4 elements per thread made a
+// whole solve 0.4 % slower.
+static int dots_ept(long long n) { return n >= 256LL * 256 * 16 ? 16 : n >= 256LL * 256 * 4 ? 4 : 1; }
+int dots_blocks(long long n) {
+    const int chunk = 256 * dots_ept(n);
+    return (int)((n + chunk - 1) / chunk);
+}
+int batch_dots_blocks(long long n) { return (int)((n + 256 * DOT_EPT - 1) / (256 * DOT_EPT)); }
 
 hipError_t launch_dots(const double2 *V, long long ldv, int nv, const double2 *w, long long n, double2 *partials,
                        int nblocks, double2 *red, hipStream_t s) {
     if (nv + 1 > MAXV) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_dots, dim3(nblocks), dim3(256), 0, s, V, ldv, nv, w, n, partials);
+    if (nblocks != dots_blocks(n)) return hipErrorInvalidValue;
+    const dim3 grid(nblocks, nv > DOT_GROUP ? (nv + DOT_GROUP - 1) / DOT_GROUP : 1);
+    switch (dots_ept(n)) {
+    case 16: hipLaunchKernelGGL(k_dots<16>, dim3(nblocks), dim3(256), 0, s, V, ldv, nv, w, n, partials); break;
+    case 4: hipLaunchKernelGGL(k_dots<4>, grid, dim3(256), 0, s, V, ldv, nv, w, n, partials); break;
+    default: hipLaunchKernelGGL(k_dots<1>, grid, dim3(256), 0, s, V, ldv, nv, w, n, partials); break;
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_reduce, dim3(nv + 1), dim3(256), 0, s, partials, nblocks, nv + 1, red);
@@ -228,9 +251,13 @@ hipError_t launch_lincomb(double2 *out, const double2 *base, double2 alpha, cons
 
 hipError_t launch_lincomb_cgs(double2 *w, const double2 *V, long long ldv, int nv, const double2 *red, long long n,
                               double reorth, hipStream_t s) {
-    long long grid_ll = (n + 256 * LC_EPT - 1) / (256 * LC_EPT);
-    int grid = (int)(grid_ll < 1 ? 1 : grid_ll);
-    hipLaunchKernelGGL(k_lincomb_cgs, dim3(grid), dim3(256), 0, s, w, V, ldv, nv, red, n, reorth);
+    if (n < 1) return hipErrorInvalidValue;
+    if (n >= 256LL * 256 * LC_EPT)
+        hipLaunchKernelGGL(k_lincomb_cgs<LC_EPT>, dim3((unsigned)((n + 256 * LC_EPT - 1) / (256 * LC_EPT))), dim3(256), 0, s,
+                           w, V, ldv, nv, red, n, reorth);
+    else
+        hipLaunchKernelGGL(k_lincomb_cgs<1>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, V, ldv, nv, red, n,
+                           reorth);
     return hipGetLastError();
 }
 

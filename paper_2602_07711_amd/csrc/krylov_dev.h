@@ -20,8 +20,9 @@ __device__ __forceinline__ double2 ld_stream_wide(const float2 *p) {
     return make_double2((double)v.x, (double)v.y);
 }
 
-constexpr int DOT_EPT = 16;                // elements per thread (8: 0.35 ms slower per 256^3 solve; 32: spills)
-constexpr int DOT_CHUNK = 256 * DOT_EPT;   // elements per block
+// elements per thread: 16 for long vectors (8: 0.35 ms slower per 256^3 solve; 32: spills), fewer for short ones
+// (dots_ept)
+constexpr int DOT_EPT = 16;
 constexpr int MAXV = 260;                  // up to m + 2 outputs
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -30,19 +31,21 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Partial sums of V_i^H w (i < nv) and ||w||^2 over chunk `lb` (DOT_CHUNK elements), written to
+// Partial sums of V_i^H w (i < nv) and (with_norm) ||w||^2 over chunk `lb` (256 EPT elements), written to
 // part[lb * bstride + t * tstride] (t = 0..nv). Every thread of the block must call it.
+template <int EPT>
 __device__ __forceinline__ void dots_chunk(const double2 *__restrict__ V, long long ldv, int nv,
                                            const double2 *__restrict__ w, long long n, double2 *__restrict__ part,
-                                           long long lb, long long bstride = -1, long long tstride = 1) {
+                                           long long lb, long long bstride = -1, long long tstride = 1,
+                                           bool with_norm = true) {
     if (bstride < 0) bstride = nv + 1;
     __shared__ double2 red[4][MAXV];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long base = lb * DOT_CHUNK + tid;
-    double2 wr[DOT_EPT];
+    const long long base = lb * (256 * EPT) + tid;
+    double2 wr[EPT];
     double ww = 0.0;
 #pragma unroll
-    for (int e = 0; e < DOT_EPT; ++e) {
+    for (int e = 0; e < EPT; ++e) {
         long long idx = base + (long long)e * 256;
         wr[e] = idx < n ? ld_stream(w + idx) : make_double2(0.0, 0.0);
         ww += wr[e].x * wr[e].x + wr[e].y * wr[e].y;
@@ -55,7 +58,7 @@ __device__ __forceinline__ void dots_chunk(const double2 *__restrict__ V, long l
         for (int q = 0; q < 4; ++q) {
             const double2 *vi = V + (long long)(i + q) * ldv;
 #pragma unroll
-            for (int e = 0; e < DOT_EPT; ++e) {
+            for (int e = 0; e < EPT; ++e) {
                 long long idx = base + (long long)e * 256;
                 double2 v = idx < n ? ld_stream(vi + idx) : make_double2(0.0, 0.0);
                 re[q] += v.x * wr[e].x + v.y * wr[e].y;   // conj(v) * w
@@ -79,7 +82,7 @@ __device__ __forceinline__ void dots_chunk(const double2 *__restrict__ V, long l
         const double2 *vi = V + (long long)i * ldv;
         double re = 0.0, im = 0.0;
 #pragma unroll
-        for (int e = 0; e < DOT_EPT; ++e) {
+        for (int e = 0; e < EPT; ++e) {
             long long idx = base + (long long)e * 256;
             double2 v = idx < n ? ld_stream(vi + idx) : make_double2(0.0, 0.0);
             re += v.x * wr[e].x + v.y * wr[e].y;
@@ -92,7 +95,7 @@ __device__ __forceinline__ void dots_chunk(const double2 *__restrict__ V, long l
     ww = wave_sum(ww);
     if (lane == 0) red[wave][nv] = make_double2(ww, 0.0);
     __syncthreads();
-    for (int t = tid; t <= nv; t += 256) {
+    for (int t = tid; t < nv + with_norm; t += 256) {
         double2 s = red[0][t];
         for (int q = 1; q < 4; ++q) { s.x += red[q][t].x; s.y += red[q][t].y; }
         part[lb * bstride + t * tstride] = s;
