@@ -525,13 +525,10 @@ helm_status ensure_krylov(Ctx &c, int m, int flexible) {
     if (k.V && k.m == m && k.flexible == flexible) return HELM_OK;
     dfree(c, k.V); dfree(c, k.Z); dfree(c, k.Zf); dfree(c, k.tmp); dfree(c, k.partials); dfree(c, k.red);
     if (k.red_host) { (void)hipHostFree(k.red_host); k.red_host = nullptr; }
-    hipStream_t aux = k.aux;
-    hipEvent_t red_ev = k.red_ev, copy_ev = k.copy_ev;
+    hipEvent_t red_ev = k.red_ev;
     k = KrylovWork{};
-    k.aux = aux; k.red_ev = red_ev; k.copy_ev = copy_ev;
-    if (!k.aux) HIP_TRY(hipStreamCreateWithFlags(&k.aux, hipStreamNonBlocking));
+    k.red_ev = red_ev;
     if (!k.red_ev) HIP_TRY(hipEventCreateWithFlags(&k.red_ev, hipEventDisableTiming));
-    if (!k.copy_ev) HIP_TRY(hipEventCreateWithFlags(&k.copy_ev, hipEventDisableTiming));
     k.nblocks = dots_blocks(c.n);
     k.ld = c.n + KRYLOV_PAD;
     ST_TRY(dalloc(c, &k.V, (size_t)(m + 1) * k.ld));
@@ -540,45 +537,24 @@ helm_status ensure_krylov(Ctx &c, int m, int flexible) {
     ST_TRY(dalloc(c, &k.tmp, (size_t)c.n));
     ST_TRY(dalloc(c, &k.partials, (size_t)k.nblocks * (m + 2)));
     ST_TRY(dalloc(c, &k.red, (size_t)(m + 2)));
-    HIP_TRY(hipHostMalloc((void **)&k.red_host, (m + 2) * sizeof(double2), hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc((void **)&k.red_host, (m + 2) * sizeof(double2), hipHostMallocCoherent));
     k.m = m;
     k.flexible = flexible;
     return HELM_OK;
 }
 
-// out[0..nv-1] = V_i^H w, out[nv] = ||w||^2 (host values, after a stream sync)
-helm_status dots(Ctx &c, const double2 *V, int nv, const double2 *w, std::vector<cd> &out) {
-    KrylovWork &k = c.kw;
-    HIP_TRY(timed(c, HELM_K_DOTS, 16.0 * c.n * (nv + 1), [&] { return launch_dots(V, k.ld, nv, w, c.n, k.partials, k.nblocks, k.red, c.stream); }));
-    HIP_TRY(hipMemcpyAsync(k.red_host, k.red, (nv + 1) * sizeof(double2), hipMemcpyDeviceToHost, c.stream));
-    prof_gap(c);
-    HIP_TRY(hipStreamSynchronize(c.stream));
-    // (profiling events are read once per solve, not here: this is the point where the GPU waits for the host)
-    out.resize(nv + 1);
-    for (int i = 0; i <= nv; ++i) out[i] = cd(k.red_host[i].x, k.red_host[i].y);
-    for (int i = 0; i <= nv; ++i)
-        if (!std::isfinite(out[i].real()) || !std::isfinite(out[i].imag())) {
-            c.err = "non-finite value in a Krylov reduction";
-            return HELM_ENUMERIC;
-        }
-    return HELM_OK;
-}
-
-// The same reduction, with the values copied to the host on the auxiliary stream: the solve stream goes on with
-// whatever the caller queues next, and dots_wait returns the values.
+// out[0..nv-1] = V_i^H w, out[nv] = ||w||^2: queued here, read by dots_wait; the solve stream goes on with whatever the
+// caller queues in between. (Profiling events are read once per solve, not here.)
 helm_status dots_async(Ctx &c, const double2 *V, int nv, const double2 *w) {
     KrylovWork &k = c.kw;
-    HIP_TRY(timed(c, HELM_K_DOTS, 16.0 * c.n * (nv + 1), [&] { return launch_dots(V, k.ld, nv, w, c.n, k.partials, k.nblocks, k.red, c.stream); }));
+    HIP_TRY(timed(c, HELM_K_DOTS, 16.0 * c.n * (nv + 1), [&] { return launch_dots(V, k.ld, nv, w, c.n, k.partials, k.nblocks, k.red, k.red_host, c.stream); }));
     HIP_TRY(hipEventRecord(k.red_ev, c.stream));
-    HIP_TRY(hipStreamWaitEvent(k.aux, k.red_ev, 0));
-    HIP_TRY(hipMemcpyAsync(k.red_host, k.red, (nv + 1) * sizeof(double2), hipMemcpyDeviceToHost, k.aux));
-    HIP_TRY(hipEventRecord(k.copy_ev, k.aux));
     return HELM_OK;
 }
 
 helm_status dots_wait(Ctx &c, int nv, std::vector<cd> &out) {
     KrylovWork &k = c.kw;
-    HIP_TRY(hipEventSynchronize(k.copy_ev));
+    HIP_TRY(hipEventSynchronize(k.red_ev));
     out.resize(nv + 1);
     for (int i = 0; i <= nv; ++i) out[i] = cd(k.red_host[i].x, k.red_host[i].y);
     for (int i = 0; i <= nv; ++i)
@@ -587,6 +563,12 @@ helm_status dots_wait(Ctx &c, int nv, std::vector<cd> &out) {
             return HELM_ENUMERIC;
         }
     return HELM_OK;
+}
+
+helm_status dots(Ctx &c, const double2 *V, int nv, const double2 *w, std::vector<cd> &out) {
+    ST_TRY(dots_async(c, V, nv, w));
+    prof_gap(c);
+    return dots_wait(c, nv, out);
 }
 
 helm_status norm2(Ctx &c, const double2 *w, double &nrm) {
@@ -711,9 +693,7 @@ void helm_destroy(helm_ctx *ctx) {
     for (void *p : c.allocs) (void)hipFree(p);
     c.allocs.clear();
     if (c.kw.red_host) (void)hipHostFree(c.kw.red_host);
-    if (c.kw.aux) (void)hipStreamDestroy(c.kw.aux);
     if (c.kw.red_ev) (void)hipEventDestroy(c.kw.red_ev);
-    if (c.kw.copy_ev) (void)hipEventDestroy(c.kw.copy_ev);
     if (c.sg_host) (void)hipHostFree(c.sg_host);
     delete c.pfft;
     c.pfft = nullptr;
@@ -1033,10 +1013,10 @@ helm_status helm_scale_guess(helm_ctx *ctx, const void *F_dev, void *x_dev, doub
     prof_gap(c);
     // y = A x; (y^H F, ||F||^2) then ||y||^2
     HIP_TRY(timed(c, HELM_K_MATVEC, matvec_bytes(c, false), [&] { return launch_matvec(c.sp, x, c.k2, c.fld, nullptr, c.sg_y, c.stream); }));
-    HIP_TRY(timed(c, HELM_K_DOTS, 32.0 * c.n, [&] { return launch_dots(c.sg_y, c.n, 1, F, c.n, c.sg_part, nb, c.sg_red, c.stream); }));
+    HIP_TRY(timed(c, HELM_K_DOTS, 32.0 * c.n, [&] { return launch_dots(c.sg_y, c.n, 1, F, c.n, c.sg_part, nb, c.sg_red, nullptr, c.stream); }));
     HIP_TRY(hipMemcpyAsync(c.sg_host, c.sg_red, sizeof(double2), hipMemcpyDeviceToHost, c.stream));
     prof_gap(c);
-    HIP_TRY(timed(c, HELM_K_DOTS, 16.0 * c.n, [&] { return launch_dots(nullptr, c.n, 0, c.sg_y, c.n, c.sg_part, nb, c.sg_red, c.stream); }));
+    HIP_TRY(timed(c, HELM_K_DOTS, 16.0 * c.n, [&] { return launch_dots(nullptr, c.n, 0, c.sg_y, c.n, c.sg_part, nb, c.sg_red, nullptr, c.stream); }));
     HIP_TRY(hipMemcpyAsync(c.sg_host + 1, c.sg_red, sizeof(double2), hipMemcpyDeviceToHost, c.stream));
     HIP_TRY(hipStreamSynchronize(c.stream));
     prof_resolve(c);
@@ -1104,9 +1084,10 @@ helm_status helm_gmres_solve(helm_ctx *ctx, const void *F_dev, void *x_dev, cons
     const long long n = c.n;
     auto t_start = std::chrono::steady_clock::now();
 
-    // phase timers: 0 matvec, 1 preconditioner, 2 Arnoldi, 3 end-of-cycle update. The orthogonalisation update of
-    // step j is bracketed by ev[8 + 2 (j & 1)] and ev[9 + 2 (j & 1)], so that its timing is read one step later
-    // without the pair being recorded again in between; every timer is read after the next launch is queued.
+    // phase timers: 0 matvec, 1 preconditioner, 2 Arnoldi, 3 end-of-cycle update. Step j's four (before the
+    // preconditioner, the product, the inner products, and after the update) are ev[4 + 4 (j & 1)...]: they are read
+    // one step later, when everything that step queues is queued, so that nothing waits between the values' arrival
+    // and the next launches.
     hipEvent_t ev[12];
     for (auto &e : ev) HIP_TRY(timing_event(&e));
     struct EvGuard { hipEvent_t *e; ~EvGuard() { for (int i = 0; i < 12; ++i) (void)hipEventDestroy(e[i]); } } guard{ev};
@@ -1152,31 +1133,32 @@ helm_status helm_gmres_solve(helm_ctx *ctx, const void *F_dev, void *x_dev, cons
     int its = 0;
     helm_status result = HELM_ENOCONV;
     bool first = true;
-    bool pending_upd = false;   // the last orthogonalisation update's pair, not yet accumulated
-    hipEvent_t upd_a = nullptr, upd_b = nullptr;
-    auto flush_upd = [&]() {
-        if (pending_upd) inf.t_ms[2] += elapsed(upd_a, upd_b);
-        pending_upd = false;
+    hipEvent_t *pending = nullptr;   // the last step's timers, not yet accumulated
+    auto flush_step = [&]() {
+        if (!pending) return;
+        inf.t_ms[1] += elapsed(pending[0], pending[1]);
+        inf.t_ms[0] += elapsed(pending[1], pending[2]);
+        inf.t_ms[2] += elapsed(pending[2], pending[3]);
+        pending = nullptr;
     };
     for (;;) {
-        // restart: V_0 = F - A x
-        HIP_TRY(hipEventRecord(ev[0], c.stream));
-        if (first && opts->x0_given != 1) {
-            HIP_TRY(hipMemcpyAsync(k.V, F, n * sizeof(double2), hipMemcpyDeviceToDevice, c.stream));
-            prof_gap(c);
-        } else {
+        // restart: V_0 = F - A x (from x = 0: F itself, whose norm is known)
+        const bool from_zero = first && opts->x0_given != 1;
+        double beta = bnorm;
+        if (!from_zero) {
+            HIP_TRY(hipEventRecord(ev[0], c.stream));
             HIP_TRY(timed(c, HELM_K_MATVEC, matvec_bytes(c, true), [&] { return launch_matvec(c.sp, x, c.k2, c.fld, F, k.V, c.stream); }));
+            HIP_TRY(hipEventRecord(ev[1], c.stream));
+            ST_TRY(norm2(c, k.V, beta));
+            inf.t_ms[0] += elapsed(ev[0], ev[1]);
         }
-        HIP_TRY(hipEventRecord(ev[1], c.stream));
+        if (!first) inf.t_ms[3] += elapsed(ev[2], ev[3]);   // the last cycle's update of x
         first = false;
-        double beta = 0.0;
-        ST_TRY(norm2(c, k.V, beta));
-        inf.t_ms[0] += elapsed(ev[0], ev[1]);
         inf.relres_true = beta / bnorm;
         push_hist(inf.relres_true);
         if (beta <= opts->rtol * bnorm) { result = HELM_OK; inf.converged = 1; break; }
         if (its >= opts->maxit) { result = HELM_ENOCONV; break; }
-        HIP_TRY(timed(c, HELM_K_LINCOMB, 16.0 * c.n * 2, [&] { return launch_lincomb(k.V, k.V, make_double2(1.0 / beta, 0.0), (const double2 *)nullptr, n, 0, coef.data(), n, c.stream); }));
+        HIP_TRY(timed(c, HELM_K_LINCOMB, 16.0 * c.n * 2, [&] { return launch_lincomb(k.V, from_zero ? F : k.V, make_double2(1.0 / beta, 0.0), (const double2 *)nullptr, n, 0, coef.data(), n, c.stream); }));
         std::fill(H.begin(), H.end(), cd(0.0));
         std::fill(g.begin(), g.end(), cd(0.0));
         g[0] = beta;
@@ -1190,11 +1172,12 @@ helm_status helm_gmres_solve(helm_ctx *ctx, const void *F_dev, void *x_dev, cons
             double2 *w = k.V + (long long)(j + 1) * k.ld;
             double2 *z = zf32 ? nullptr : (flex ? k.Z + (long long)j * k.ld : k.tmp);
             float2 *zf = zf32 ? k.Zf + (long long)j * k.ld : nullptr;
-            HIP_TRY(hipEventRecord(ev[2], c.stream));
+            hipEvent_t *es = ev + 4 + 4 * (j & 1);
+            HIP_TRY(hipEventRecord(es[0], c.stream));
             if (aug && j == 0) { /* z_0 is the guess, already in place */ }
             else if (zf32) ST_TRY(precond32(c, vj, zf, opts->prec));
             else ST_TRY(precond(c, vj, z, opts->prec, opts->prec_fp32));
-            HIP_TRY(hipEventRecord(ev[3], c.stream));
+            HIP_TRY(hipEventRecord(es[1], c.stream));
             // Arnoldi on A M^{-1} - I (same Krylov space; column j of H gains +1 on its diagonal): the matvec in
             // residual form writes y = v_j - A z_j = -(A M^{-1} v_j - v_j). With a good preconditioner
             // A M^{-1} v_j is close to v_j, so orthogonalising the shifted vector avoids the cancellation that
@@ -1203,14 +1186,14 @@ helm_status helm_gmres_solve(helm_ctx *ctx, const void *F_dev, void *x_dev, cons
                 HIP_TRY(timed(c, HELM_K_MATVEC, matvec_bytes(c, true) - 8.0 * c.n, [&] { return launch_matvec(c.sp, zf, c.k2, c.fld, vj, w, c.stream); }));
             else
                 HIP_TRY(timed(c, HELM_K_MATVEC, matvec_bytes(c, true), [&] { return launch_matvec(c.sp, z, c.k2, c.fld, vj, w, c.stream); }));
-            HIP_TRY(hipEventRecord(ev[4], c.stream));
+            HIP_TRY(hipEventRecord(es[2], c.stream));
             // classical Gram-Schmidt: V^H y and ||y||^2 in one pass. The update takes its coefficients from the
             // reduced values on the device, so it follows the inner products without waiting for the host; the
-            // values reach the host on the auxiliary stream meanwhile (Hessenberg column, Givens rotation).
+            // values reach the host meanwhile (Hessenberg column, Givens rotation).
             ST_TRY(dots_async(c, k.V, j + 1, w));
-            hipEvent_t ua = ev[8 + 2 * (j & 1)], ub = ev[9 + 2 * (j & 1)];
-            HIP_TRY(hipEventRecord(ua, c.stream));
             HIP_TRY(timed(c, HELM_K_LINCOMB, 16.0 * c.n * (j + 3), [&] { return launch_lincomb_cgs(w, k.V, k.ld, j + 1, k.red, n, reorth, c.stream); }));
+            HIP_TRY(hipEventRecord(es[3], c.stream));
+            flush_step();
             ST_TRY(dots_wait(c, j + 1, hv));
             double hh = 0.0;
             for (int i = 0; i <= j; ++i) {        // the device's arithmetic, in the same order
@@ -1233,15 +1216,11 @@ helm_status helm_gmres_solve(helm_ctx *ctx, const void *F_dev, void *x_dev, cons
                     for (int i = 0; i <= j; ++i) coef[i] = make_double2(-hv2[i].real() / eta, -hv2[i].imag() / eta);
                     HIP_TRY(timed(c, HELM_K_LINCOMB, 16.0 * c.n * (j + 3), [&] { return launch_lincomb(w, w, make_double2(1.0 / eta, 0.0), k.V, k.ld, j + 1, coef.data(), n, c.stream); }));
                 }
+                HIP_TRY(hipEventRecord(es[3], c.stream));
             } else {
                 eta = std::sqrt(eta2);
             }
-            HIP_TRY(hipEventRecord(ub, c.stream));
-            // phase bookkeeping while the GPU runs the update
-            flush_upd();
-            inf.t_ms[1] += elapsed(ev[2], ev[3]);
-            inf.t_ms[0] += elapsed(ev[3], ev[4]);
-            inf.t_ms[2] += elapsed(ev[4], ua);
+            pending = es;
             // Hessenberg column j and Givens rotations
             for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = -hv[i];
             H[(size_t)js * m + j] += 1.0;
@@ -1267,9 +1246,6 @@ helm_status helm_gmres_solve(helm_ctx *ctx, const void *F_dev, void *x_dev, cons
                 g[j + 1] = -std::conj(sn[j]) * g[j];
                 g[j] = cs[j] * g[j];
             }
-            upd_a = ua;
-            upd_b = ub;
-            pending_upd = true;
             ++its;
             kk = j + 1;
             inf.relres_est = std::abs(g[j + 1]) / bnorm;
@@ -1301,8 +1277,7 @@ helm_status helm_gmres_solve(helm_ctx *ctx, const void *F_dev, void *x_dev, cons
             HIP_TRY(timed(c, HELM_K_LINCOMB, 16.0 * c.n * 3, [&] { return launch_lincomb(x, x, make_double2(1.0, 0.0), zz, n, 1, coef.data(), n, c.stream); }));
         }
         HIP_TRY(hipEventRecord(ev[3], c.stream));
-        inf.t_ms[3] += elapsed(ev[2], ev[3]);
-        flush_upd();
+        flush_step();
         ++inf.restarts;
         aug = false;
         if (breakdown) {

@@ -150,10 +150,9 @@ struct KrylovWork {
     double2 *tmp = nullptr;      // n
     double2 *partials = nullptr; // nblocks * (m + 2)
     double2 *red = nullptr;      // m + 2 reduced values
-    double2 *red_host = nullptr; // pinned host copy
+    double2 *red_host = nullptr; // the same in coherent host memory, written by the reduction itself
     int nblocks = 0;
-    hipStream_t aux = nullptr;   // copies the reduced values to the host while the solve stream runs on
-    hipEvent_t red_ev = nullptr, copy_ev = nullptr;
+    hipEvent_t red_ev = nullptr; // behind the reduction: the host reads the values while the solve stream runs on
 };
 
 struct ProfPending { int cls; double work; hipEvent_t a, b; bool own_a; };   // own_a: a is not the previous b
@@ -380,7 +379,8 @@ hipError_t launch_ring_forward_z32(const float2 *ra, const float2 *rb, const flo
 int dots_blocks(long long n);         // of a single solve
 int batch_dots_blocks(long long n);   // of a problem in a batch
 hipError_t launch_dots(const double2 *V, long long ldv, int nv, const double2 *w, long long n, double2 *partials,
-                       int nblocks, double2 *red, hipStream_t s);   // red[0..nv-1] = V_i^H w, red[nv] = (|w|^2, 0)
+                       int nblocks, double2 *red, double2 *host, hipStream_t s);   // red[0..nv-1] = V_i^H w, red[nv] =
+                                                                                   // (|w|^2, 0); host: null or a copy
 hipError_t launch_lincomb(double2 *out, const double2 *base, double2 alpha, const double2 *V, long long ldv, int nv,
                           const double2 *coef, long long n, hipStream_t s);
 // the same over complex64 vectors V (the complex64 Z basis of FGMRES with the FP32 preconditioner)
