@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -46,53 +47,97 @@ void dfree(Ctx &c, void *p) {
     (void)hipFree(p);
 }
 
+// Several arrays in one allocation, those with contents (put) first and uploaded by one copy. The pointers are set by commit.
+// hipMalloc of more than 1 MiB takes 30 to 240 us, hipFree of 8 MiB and more 225 us, and a copy from pageable memory 12 to
+// 60 us: a 64^3 context with one allocation and one copy per array spent 2 ms on them. Arrays of 1 MiB and more begin at
+// 2 MiB, as if allocated alone, and those of `alone` bytes and more are: their 260 us are little beside the work on them, and
+// at 255^3 the z-solve was 6 % slower with its vectors and pivot table in one allocation.
+struct Slab {
+    size_t alone = 16u << 20;
+    struct Slot { void **p; size_t bytes, off; };
+    std::vector<Slot> up, work;
+    std::vector<char> host;
+    static size_t aligned(size_t off, size_t bytes) {
+        const size_t a = bytes >= (1u << 20) ? 2u << 20 : 256;
+        return (off + a - 1) / a * a;
+    }
+    template <typename T> void put(T **p, const void *data, size_t count) {
+        const size_t bytes = count * sizeof(T), off = aligned(host.size(), bytes);
+        up.push_back({(void **)p, bytes, off});
+        host.resize(off + bytes);
+        std::memcpy(host.data() + off, data, bytes);
+    }
+    template <typename T> void take(T **p, size_t count) { work.push_back({(void **)p, count * sizeof(T), 0}); }
+    helm_status commit(Ctx &c);
+};
+
 #define ST_TRY(expr)                              \
     do {                                          \
         helm_status _s = (expr);                  \
         if (_s != HELM_OK) return _s;             \
     } while (0)
 
-inline double2 d2(cd v) { return make_double2(v.real(), v.imag()); }
-
-helm_status upload_matrix(Ctx &c, const std::vector<cd> &M, int n, bool transpose, double2 **d64, float2 **d32) {
-    std::vector<double2> h64((size_t)n * n);
-    std::vector<float2> h32((size_t)n * n);
-    for (int r = 0; r < n; ++r)
-        for (int k = 0; k < n; ++k) {
-            cd v = transpose ? M[(size_t)k * n + r] : M[(size_t)r * n + k];
-            h64[(size_t)r * n + k] = d2(v);
-            h32[(size_t)r * n + k] = make_float2((float)v.real(), (float)v.imag());
-        }
-    ST_TRY(dalloc(c, d64, (size_t)n * n));
-    ST_TRY(dalloc(c, d32, (size_t)n * n));
-    HIP_TRY(hipMemcpy(*d64, h64.data(), h64.size() * sizeof(double2), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(*d32, h32.data(), h32.size() * sizeof(float2), hipMemcpyHostToDevice));
+helm_status Slab::commit(Ctx &c) {
+    size_t end = host.size();
+    for (Slot &s : work) {
+        if (s.bytes >= alone) continue;
+        s.off = aligned(end, s.bytes);
+        end = s.off + s.bytes;
+    }
+    char *base = nullptr;
+    if (end) ST_TRY(dalloc(c, &base, end));
+    if (!host.empty()) HIP_TRY(hipMemcpy(base, host.data(), host.size(), hipMemcpyHostToDevice));
+    for (const Slot &s : up) *s.p = base + s.off;
+    for (const Slot &s : work) {
+        char *q = base + s.off;
+        if (s.bytes >= alone) ST_TRY(dalloc(c, &q, s.bytes));
+        *s.p = q;
+    }
     return HELM_OK;
 }
 
-// The half blocks of one axis for the folded transforms (k_gemm.hip), with the butterfly's 1/sqrt(2) folded in
-// (1/2 forward and 1 inverse at the middle position of an odd axis). Layouts: x forward [position][mode], x
-// inverse [mode][position]; y forward [mode][position], y inverse [position][mode].
-helm_status upload_fold(Ctx &c, const EigFold &f, bool xaxis, FoldMats<double2> &m64, FoldMats<float2> &m32) {
+inline double2 d2(cd v) { return make_double2(v.real(), v.imag()); }
+
+// The half blocks of the folded transforms (k_gemm.hip), with the butterfly's 1/sqrt(2) folded in (1/2 forward and 1
+// inverse at the middle position of an odd axis). Layouts: x forward [position][mode], x inverse [mode][position]; y
+// forward [mode][position], y inverse [position][mode]. The blocks go up without their padding and in FP64 only; a kernel
+// writes the padded FP64 and FP32 forms.
+struct FoldJob { const EigFold *f; bool xaxis; FoldMats<double2> *m64; FoldMats<float2> *m32; };
+
+helm_status upload_folds(Ctx &c, Slab &slab, std::initializer_list<FoldJob> jobs) {
     const double r = 1.0 / std::sqrt(2.0);
-    auto block = [&](int nb, const std::vector<cd> &Vi, const std::vector<cd> &V, bool sym, double2 **f64,
-                     float2 **f32, double2 **i64, float2 **i32) -> helm_status {
-        const int P = fold_pad(nb);
-        std::vector<cd> fw((size_t)P * P, 0.0), iv((size_t)P * P, 0.0);
-        for (int k = 0; k < nb; ++k)
-            for (int i = 0; i < nb; ++i) {
-                const bool mid = sym && i >= f.ma;            // middle of an odd axis: no mirror partner
-                const cd vf = Vi[(size_t)k * nb + i] * (mid ? 0.5 : r);   // mode k from position i
-                const cd vi = V[(size_t)i * nb + k] * (mid ? 1.0 : r);    // position i from mode k
-                fw[xaxis ? (size_t)i * P + k : (size_t)k * P + i] = vf;
-                iv[xaxis ? (size_t)k * P + i : (size_t)i * P + k] = vi;
+    FoldBlocks fb{};
+    std::vector<std::pair<double2 **, float2 **>> out;
+    for (const FoldJob &j : jobs) {
+        auto block = [&](int nb, const std::vector<cd> &Vi, const std::vector<cd> &V, bool sym, double2 **f64, float2 **f32,
+                         double2 **i64, float2 **i32) {
+            std::vector<cd> fw((size_t)nb * nb), iv((size_t)nb * nb);
+            for (int k = 0; k < nb; ++k)
+                for (int i = 0; i < nb; ++i) {
+                    const bool mid = sym && i >= j.f->ma;                     // middle of an odd axis: no mirror partner
+                    fw[j.xaxis ? (size_t)i * nb + k : (size_t)k * nb + i] = Vi[(size_t)k * nb + i] * (mid ? 0.5 : r);
+                    iv[j.xaxis ? (size_t)k * nb + i : (size_t)i * nb + k] = V[(size_t)i * nb + k] * (mid ? 1.0 : r);
+                }
+            const size_t P = fold_pad(nb);
+            for (int inv = 0; inv < 2; ++inv) {
+                FoldBlock &q = fb.b[fb.n++];
+                q.nb = nb;
+                q.P = (int)P;
+                slab.put(&q.src, (inv ? iv : fw).data(), (size_t)nb * nb);
+                slab.take(inv ? i64 : f64, P * P);
+                slab.take(inv ? i32 : f32, P * P);
+                out.push_back({inv ? i64 : f64, inv ? i32 : f32});
             }
-        ST_TRY(upload_matrix(c, fw, P, false, f64, f32));
-        ST_TRY(upload_matrix(c, iv, P, false, i64, i32));
-        return HELM_OK;
-    };
-    ST_TRY(block(f.ms, f.Vsi, f.Vs, true, &m64.fs, &m32.fs, &m64.is, &m32.is));
-    ST_TRY(block(f.ma, f.Vai, f.Va, false, &m64.fa, &m32.fa, &m64.ia, &m32.ia));
+        };
+        block(j.f->ms, j.f->Vsi, j.f->Vs, true, &j.m64->fs, &j.m32->fs, &j.m64->is, &j.m32->is);
+        block(j.f->ma, j.f->Vai, j.f->Va, false, &j.m64->fa, &j.m32->fa, &j.m64->ia, &j.m32->ia);
+    }
+    ST_TRY(slab.commit(c));
+    for (int q = 0; q < fb.n; ++q) { fb.b[q].d64 = *out[q].first; fb.b[q].d32 = *out[q].second; }
+    HIP_TRY(launch_fold_expand(fb, c.stream));
+    prof_gap(c);
+    // a batch applies the blocks on a stream of its own
+    HIP_TRY(hipStreamSynchronize(c.stream));
     return HELM_OK;
 }
 
@@ -129,14 +174,22 @@ double fold_flops(const FoldDesc &f) {
 }
 
 // pivots entering each z-chunk of the partitioned tridiagonal solve, per set of x-y eigenvalues and z closure
-helm_status ensure_tpiv(Ctx &c, const double2 *dx, const double2 *dy, TriPiv *piv, double2 gz, double zi = 1.0) {
-    if (piv->d) return HELM_OK;
+void take_tpiv(const Ctx &c, Slab &slab, TriPiv *piv) {
     const size_t cnt = (size_t)tri_chunks(c.nz) * c.nx * c.ny;
-    ST_TRY(dalloc(c, &piv->d, cnt));
-    ST_TRY(dalloc(c, &piv->f, cnt));
+    slab.take(&piv->d, cnt);
+    slab.take(&piv->f, cnt);
+}
+helm_status fill_tpiv(Ctx &c, const double2 *dx, const double2 *dy, TriPiv *piv, double2 gz, double zi) {
     HIP_TRY(launch_tri_pivots(dx, dy, c.nx, c.ny, c.nz, c.ax, c.ay, c.c0, gz, piv->d, piv->f, c.stream, zi));
     prof_gap(c);   // untimed set-up launch between timed ones
     return HELM_OK;
+}
+helm_status ensure_tpiv(Ctx &c, const double2 *dx, const double2 *dy, TriPiv *piv, double2 gz, double zi = 1.0) {
+    if (piv->d) return HELM_OK;
+    Slab slab;
+    take_tpiv(c, slab, piv);
+    ST_TRY(slab.commit(c));
+    return fill_tpiv(c, dx, dy, piv, gz, zi);
 }
 // the operator's own closure (gamma_z and, for the collocated closure, zeta)
 helm_status ensure_tpiv(Ctx &c, const double2 *dx, const double2 *dy, TriPiv *piv) {
@@ -145,9 +198,10 @@ helm_status ensure_tpiv(Ctx &c, const double2 *dx, const double2 *dy, TriPiv *pi
 
 helm_status ensure_fp32_work(Ctx &c) {
     if (c.t1f) return HELM_OK;
-    ST_TRY(dalloc(c, &c.t1f, (size_t)c.n));
-    ST_TRY(dalloc(c, &c.t2f, (size_t)c.n));
-    return HELM_OK;
+    Slab slab;
+    slab.take(&c.t1f, (size_t)c.n);
+    slab.take(&c.t2f, (size_t)c.n);
+    return slab.commit(c);
 }
 
 // z32 (FP32 form only): write the result as complex64 there instead of complex128 into z
@@ -197,7 +251,7 @@ std::vector<cd> sine_matrix(int n) {
     return S;
 }
 
-template <typename CT> helm_status upload_one(Ctx &c, const std::vector<cd> &M, int n, bool transpose, CT **d) {
+template <typename CT> void put_matrix(Slab &slab, const std::vector<cd> &M, int n, bool transpose, CT **d) {
     std::vector<CT> hbuf((size_t)n * n);
     for (int r = 0; r < n; ++r)
         for (int k = 0; k < n; ++k) {
@@ -205,9 +259,7 @@ template <typename CT> helm_status upload_one(Ctx &c, const std::vector<cd> &M, 
             hbuf[(size_t)r * n + k].x = (decltype(hbuf[0].x))v.real();
             hbuf[(size_t)r * n + k].y = (decltype(hbuf[0].x))v.imag();
         }
-    ST_TRY(dalloc(c, d, (size_t)n * n));
-    HIP_TRY(hipMemcpy(*d, hbuf.data(), hbuf.size() * sizeof(CT), hipMemcpyHostToDevice));
-    return HELM_OK;
+    slab.put(d, hbuf.data(), hbuf.size());
 }
 
 // The orthonormal sine matrix S (S[j][k] = sqrt(2/(N+1)) sin(pi (j+1)(k+1)/(N+1))) as folded real blocks: S is its
@@ -215,7 +267,7 @@ template <typename CT> helm_status upload_one(Ctx &c, const std::vector<cd> &M, 
 // S = Q diag(Vs, Va) in that mode order, Vs[i][k'] = sqrt(2) S[i][2k'] and Va[i][k'] = sqrt(2) S[i][2k'+1] (the middle
 // row of an odd axis unscaled), and the inverse blocks the same with S's rows. The modes stay in natural order
 // (FoldDesc moff = 1, mstep = 2).
-helm_status build_sine_fold(Ctx &c, int n, bool xaxis, FoldMats<double2> &m64, FoldMats<float2> &m32) {
+EigFold sine_fold(int n) {
     const std::vector<cd> S = sine_matrix(n);
     EigFold f;
     f.n = n;
@@ -238,7 +290,7 @@ helm_status build_sine_fold(Ctx &c, int n, bool xaxis, FoldMats<double2> &m64, F
             f.Va[(size_t)i * ma + k] = S[(size_t)i * n + 2 * k + 1] * r2;
             f.Vai[(size_t)k * ma + i] = S[(size_t)(2 * k + 1) * n + i] * r2;
         }
-    return upload_fold(c, f, xaxis, m64, m32);
+    return f;
 }
 
 FoldDesc sine_desc(const Ctx &c, int axis) {
@@ -287,27 +339,32 @@ helm_status sine_tf(Ctx &c, int axis, bool fwd, const TD *in, TC *out, const Pff
 
 template <typename CT> helm_status build_sine_mats(Ctx &c, PfftMats<CT> &m) {
     std::vector<cd> Sx = sine_matrix(c.nx), Sy = sine_matrix(c.ny);
-    ST_TRY(upload_one(c, Sx, c.nx, false, &m.Sx));
-    ST_TRY(upload_one(c, Sy, c.ny, false, &m.Sy));
-    return HELM_OK;
+    Slab slab;
+    put_matrix(slab, Sx, c.nx, false, &m.Sx);
+    put_matrix(slab, Sy, c.ny, false, &m.Sy);
+    return slab.commit(c);
 }
 
 template <typename CT> helm_status build_ring_mats(Ctx &c, PfftMats<CT> &m) {
-    ST_TRY(upload_one(c, c.hVxi, c.nx, false, &m.Vxi));
-    ST_TRY(upload_one(c, c.hVx, c.nx, false, &m.Vx));
-    ST_TRY(upload_one(c, c.hVyi, c.ny, true, &m.VyiT));
-    ST_TRY(upload_one(c, c.hVy, c.ny, true, &m.VyT));
-    ST_TRY(dalloc(c, &m.yhat, (size_t)c.n));
+    Slab slab;
+    put_matrix(slab, c.hVxi, c.nx, false, &m.Vxi);
+    put_matrix(slab, c.hVx, c.nx, false, &m.Vx);
+    put_matrix(slab, c.hVxi, c.nx, true, &m.VxiT);
+    put_matrix(slab, c.hVx, c.nx, true, &m.VxT);
+    put_matrix(slab, c.hVyi, c.ny, true, &m.VyiT);
+    put_matrix(slab, c.hVy, c.ny, false, &m.Vy);
+    put_matrix(slab, c.hVy, c.ny, true, &m.VyT);
+    slab.take(&m.yhat, (size_t)c.n);
     size_t ring = (size_t)c.nz * (2 * c.nx + 2 * c.ny);
     const size_t layers = c.zeta != 1.0 ? 2 : 1;     // the collocated closure reads a second layer per face
-    ST_TRY(dalloc(c, &m.ringT, layers * ring));
-    ST_TRY(dalloc(c, &m.ringW, layers * ring));
-    ST_TRY(dalloc(c, &m.rpart, (size_t)c.nz * ring_rowgroups() * 2 * c.nx));
-    ST_TRY(dalloc(c, &m.sv, (size_t)c.nz * 2 * c.ny));
-    ST_TRY(dalloc(c, &m.rsum, (size_t)c.nz * 2 * c.nx));
-    ST_TRY(dalloc(c, &m.rbuf, ring));
-    ST_TRY(dalloc(c, &m.fvec, ring));
-    return HELM_OK;
+    slab.take(&m.ringT, layers * ring);
+    slab.take(&m.ringW, layers * ring);
+    slab.take(&m.rpart, (size_t)c.nz * ring_rowgroups() * 2 * c.nx);
+    slab.take(&m.sv, (size_t)c.nz * 2 * c.ny);
+    slab.take(&m.rsum, (size_t)c.nz * 2 * c.nx);
+    slab.take(&m.rbuf, ring);
+    slab.take(&m.fvec, ring);
+    return slab.commit(c);
 }
 
 // Sine matrices and Dirichlet eigenvalues (shared by PFFT and FFT2); `ring` adds PFFT's face-correction data.
@@ -322,16 +379,17 @@ helm_status ensure_sine(Ctx &c, bool fp32, bool ring) {
         const double pi = 3.14159265358979323846;
         for (int i = 0; i < c.nx; ++i) fx[i] = make_double2(2.0 * std::cos(pi * (i + 1) / (c.nx + 1)), 0.0);
         for (int j = 0; j < c.ny; ++j) fy[j] = make_double2(2.0 * std::cos(pi * (j + 1) / (c.ny + 1)), 0.0);
-        ST_TRY(dalloc(c, &c.pfft->dFx, (size_t)c.nx));
-        ST_TRY(dalloc(c, &c.pfft->dFy, (size_t)c.ny));
-        HIP_TRY(hipMemcpy(c.pfft->dFx, fx.data(), fx.size() * sizeof(double2), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(c.pfft->dFy, fy.data(), fy.size() * sizeof(double2), hipMemcpyHostToDevice));
+        Slab slab;
+        slab.put(&c.pfft->dFx, fx.data(), fx.size());
+        slab.put(&c.pfft->dFy, fy.data(), fy.size());
+        ST_TRY(slab.commit(c));
     }
     PfftPlan &P = *c.pfft;
     if (!P.m64.Sx) ST_TRY(build_sine_mats(c, P.m64));
     if (!P.m64.fsx.fs) {
-        ST_TRY(build_sine_fold(c, c.nx, true, P.m64.fsx, P.m32.fsx));
-        ST_TRY(build_sine_fold(c, c.ny, false, P.m64.fsy, P.m32.fsy));
+        const EigFold fx = sine_fold(c.nx), fy = sine_fold(c.ny);
+        Slab slab;
+        ST_TRY(upload_folds(c, slab, {{&fx, true, &P.m64.fsx, &P.m32.fsx}, {&fy, false, &P.m64.fsy, &P.m32.fsy}}));
     }
     if (ring && !P.m64.ringT) ST_TRY(build_ring_mats(c, P.m64));
     if (fp32) {
@@ -359,7 +417,11 @@ helm_status ensure_fftk(Ctx &c, bool fp32) {
             HIP_TRY(hipMemcpy(*dst[a], t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice));
         }
     }
-    if (!P.m64.fsz.fs) ST_TRY(build_sine_fold(c, c.nz, false, P.m64.fsz, P.m32.fsz));
+    if (!P.m64.fsz.fs) {
+        const EigFold fz = sine_fold(c.nz);
+        Slab slab;
+        ST_TRY(upload_folds(c, slab, {{&fz, false, &P.m64.fsz, &P.m32.fsz}}));
+    }
     return HELM_OK;
 }
 
@@ -388,10 +450,10 @@ helm_status pfft_apply(Ctx &c, const double2 *y, double2 *z, bool fp32, float2 *
         HIP_TRY(timed(c, HELM_K_TRIDIAG64, 32.0 * c.n, [&] { return launch_tridiag_chunk_z64(m.yhat, c.t2, c.tpiv_dir.d, P.dFx, P.dFy, nx, ny, nz, c.ax, c.ay, c.c0, gz, hz2, c.stream, zi); }));
         for (int layer = 0; layer < (two ? 2 : 1); ++layer)
             HIP_TRY(timed(c, HELM_K_RING, 16.0 * c.n + ring_work / ring_pass, [&] { return launch_ring_inverse_z64(c.t2, m.ringT + layer * rsz, m.Sy, m.Sy, m.Sx, m.Sx, nx, ny, nz, layer, m.rpart, m.sv, m.rsum, c.stream); }));
-        HIP_TRY(timed(c, HELM_K_RING, 16.0 * c.n + ring_work, [&] { return launch_ring_forward_z64(m.ringT, nullptr, T1, nullptr, nullptr, 0.0, c.t2, m.VyiT, c.BxF, ex, ey, ex1, ey1, nx, ny, nz, m.rbuf, m.fvec, c.stream); }));
+        HIP_TRY(timed(c, HELM_K_RING, 16.0 * c.n + ring_work, [&] { return launch_ring_forward_z64(m.ringT, nullptr, T1, nullptr, nullptr, 0.0, c.t2, m.VyiT, m.VxiT, ex, ey, ex1, ey1, nx, ny, nz, m.rbuf, m.fvec, c.stream); }));
         HIP_TRY(timed(c, HELM_K_TRIDIAG64, 32.0 * c.n, [&] { return launch_tridiag_chunk_z64(c.t2, c.t2, c.tpiv_eig.d, c.dxe, c.dye, nx, ny, nz, c.ax, c.ay, c.c0, gz, 1.0, c.stream, zi); }));
         for (int layer = 0; layer < (two ? 2 : 1); ++layer)
-            HIP_TRY(timed(c, HELM_K_RING, 16.0 * c.n + ring_work / ring_pass, [&] { return launch_ring_inverse_z64(c.t2, m.ringW + layer * rsz, c.AyI, m.VyT, m.Vx, c.BxI, nx, ny, nz, layer, m.rpart, m.sv, m.rsum, c.stream); }));
+            HIP_TRY(timed(c, HELM_K_RING, 16.0 * c.n + ring_work / ring_pass, [&] { return launch_ring_inverse_z64(c.t2, m.ringW + layer * rsz, m.Vy, m.VyT, m.Vx, m.VxT, nx, ny, nz, layer, m.rpart, m.sv, m.rsum, c.stream); }));
         HIP_TRY(timed(c, HELM_K_RING, 32.0 * c.n + 2 * ring_work, [&] { return launch_ring_forward_z64(m.ringT, m.ringW, T1, W1, m.yhat, hz2, c.t2, m.Sy, m.Sx, ex, ey, ex1, ey1, nx, ny, nz, m.rbuf, m.fvec, c.stream); }));
         HIP_TRY(timed(c, HELM_K_TRIDIAG64, 32.0 * c.n, [&] { return launch_tridiag_chunk_z64(c.t2, c.t2, c.tpiv_dir.d, P.dFx, P.dFy, nx, ny, nz, c.ax, c.ay, c.c0, gz, 1.0, c.stream, zi); }));
         ST_TRY(sine_tf(c, 1, false, c.t2, c.t1, m));
@@ -405,10 +467,10 @@ helm_status pfft_apply(Ctx &c, const double2 *y, double2 *z, bool fp32, float2 *
         HIP_TRY(timed(c, HELM_K_TRIDIAG32, 16.0 * c.n, [&] { return launch_tridiag_chunk_z32(m.yhat, c.t2f, c.tpiv_dir.f, P.dFx, P.dFy, nx, ny, nz, c.ax, c.ay, c.c0, gz, hz2, c.stream, zi); }));
         for (int layer = 0; layer < (two ? 2 : 1); ++layer)
             HIP_TRY(timed(c, HELM_K_RING, 8.0 * c.n + ring_work / 2 / ring_pass, [&] { return launch_ring_inverse_z32(c.t2f, m.ringT + layer * rsz, m.Sy, m.Sy, m.Sx, m.Sx, nx, ny, nz, layer, m.rpart, m.sv, m.rsum, c.stream); }));
-        HIP_TRY(timed(c, HELM_K_RING, 8.0 * c.n + ring_work / 2, [&] { return launch_ring_forward_z32(m.ringT, nullptr, T1, nullptr, nullptr, 0.0, c.t2f, m.VyiT, c.BxF32, ex, ey, ex1, ey1, nx, ny, nz, m.rbuf, m.fvec, c.stream); }));
+        HIP_TRY(timed(c, HELM_K_RING, 8.0 * c.n + ring_work / 2, [&] { return launch_ring_forward_z32(m.ringT, nullptr, T1, nullptr, nullptr, 0.0, c.t2f, m.VyiT, m.VxiT, ex, ey, ex1, ey1, nx, ny, nz, m.rbuf, m.fvec, c.stream); }));
         HIP_TRY(timed(c, HELM_K_TRIDIAG32, 16.0 * c.n, [&] { return launch_tridiag_chunk_z32(c.t2f, c.t2f, c.tpiv_eig.f, c.dxe, c.dye, nx, ny, nz, c.ax, c.ay, c.c0, gz, 1.0, c.stream, zi); }));
         for (int layer = 0; layer < (two ? 2 : 1); ++layer)
-            HIP_TRY(timed(c, HELM_K_RING, 8.0 * c.n + ring_work / 2 / ring_pass, [&] { return launch_ring_inverse_z32(c.t2f, m.ringW + layer * rsz, c.AyI32, m.VyT, m.Vx, c.BxI32, nx, ny, nz, layer, m.rpart, m.sv, m.rsum, c.stream); }));
+            HIP_TRY(timed(c, HELM_K_RING, 8.0 * c.n + ring_work / 2 / ring_pass, [&] { return launch_ring_inverse_z32(c.t2f, m.ringW + layer * rsz, m.Vy, m.VyT, m.Vx, m.VxT, nx, ny, nz, layer, m.rpart, m.sv, m.rsum, c.stream); }));
         HIP_TRY(timed(c, HELM_K_RING, 16.0 * c.n + ring_work, [&] { return launch_ring_forward_z32(m.ringT, m.ringW, T1, W1, m.yhat, hz2, c.t2f, m.Sy, m.Sx, ex, ey, ex1, ey1, nx, ny, nz, m.rbuf, m.fvec, c.stream); }));
         HIP_TRY(timed(c, HELM_K_TRIDIAG32, 16.0 * c.n, [&] { return launch_tridiag_chunk_z32(c.t2f, c.t2f, c.tpiv_dir.f, P.dFx, P.dFy, nx, ny, nz, c.ax, c.ay, c.c0, gz, 1.0, c.stream, zi); }));
         ST_TRY(sine_tf(c, 1, false, c.t2f, c.t1f, m));
@@ -523,7 +585,7 @@ helm_status precond32(Ctx &c, const double2 *y, float2 *z, int kind) {
 helm_status ensure_krylov(Ctx &c, int m, int flexible) {
     KrylovWork &k = c.kw;
     if (k.V && k.m == m && k.flexible == flexible) return HELM_OK;
-    dfree(c, k.V); dfree(c, k.Z); dfree(c, k.Zf); dfree(c, k.tmp); dfree(c, k.partials); dfree(c, k.red);
+    dfree(c, k.V);      // the first of the slab
     if (k.red_host) { (void)hipHostFree(k.red_host); k.red_host = nullptr; }
     hipEvent_t red_ev = k.red_ev;
     k = KrylovWork{};
@@ -531,12 +593,15 @@ helm_status ensure_krylov(Ctx &c, int m, int flexible) {
     if (!k.red_ev) HIP_TRY(hipEventCreateWithFlags(&k.red_ev, hipEventDisableTiming));
     k.nblocks = dots_blocks(c.n);
     k.ld = c.n + KRYLOV_PAD;
-    ST_TRY(dalloc(c, &k.V, (size_t)(m + 1) * k.ld));
-    if (flexible == 1) ST_TRY(dalloc(c, &k.Z, (size_t)m * k.ld));
-    if (flexible == 2) ST_TRY(dalloc(c, &k.Zf, (size_t)m * k.ld));
-    ST_TRY(dalloc(c, &k.tmp, (size_t)c.n));
-    ST_TRY(dalloc(c, &k.partials, (size_t)k.nblocks * (m + 2)));
-    ST_TRY(dalloc(c, &k.red, (size_t)(m + 2)));
+    Slab slab;
+    slab.alone = ~(size_t)0;      // one block, freed by its first array's address above
+    slab.take(&k.V, (size_t)(m + 1) * k.ld);
+    if (flexible == 1) slab.take(&k.Z, (size_t)m * k.ld);
+    if (flexible == 2) slab.take(&k.Zf, (size_t)m * k.ld);
+    slab.take(&k.tmp, (size_t)c.n);
+    slab.take(&k.partials, (size_t)k.nblocks * (m + 2));
+    slab.take(&k.red, (size_t)(m + 2));
+    ST_TRY(slab.commit(c));
     HIP_TRY(hipHostMalloc((void **)&k.red_host, (m + 2) * sizeof(double2), hipHostMallocCoherent));
     k.m = m;
     k.flexible = flexible;
@@ -787,12 +852,19 @@ helm_status setup_impl(helm_ctx **out, helm_grid g, const double h[3], const voi
     p.tiles_y = (c.ny + STENCIL_TY - 1) / STENCIL_TY;
     // derived fields
     helm_status st;
-    if ((st = dalloc(c, &c.k2, (size_t)c.n)) != HELM_OK) return bail(st);
-    if (order == 6 && (st = dalloc(c, &c.fld, (size_t)c.n)) != HELM_OK) return bail(st);
+    Slab work;
+    work.take(&c.k2, (size_t)c.n);
+    if (order == 6) work.take(&c.fld, (size_t)c.n);
+    if (k2_complex) work.take(&c.k2i, (size_t)c.n);
+    if (k2_complex && order == 6) work.take(&c.fldi, (size_t)c.n);
+    work.take(&c.t1, (size_t)c.n);
+    work.take(&c.t2, (size_t)c.n);
+    // the z-solve's chunk pivots of the EigT preconditioner (2 bytes per unknown), so that no later preconditioner
+    // call has to allocate them
+    take_tpiv(c, work, &c.tpiv_eig);
+    if ((st = work.commit(c)) != HELM_OK) return bail(st);
     hipError_t he;
     if (k2_complex) {
-        if ((st = dalloc(c, &c.k2i, (size_t)c.n)) != HELM_OK) return bail(st);
-        if (order == 6 && (st = dalloc(c, &c.fldi, (size_t)c.n)) != HELM_OK) return bail(st);
         he = launch_derived_fields_c((const double2 *)k2_dev, k2_halo, c.k2, c.k2i, c.fld, c.fldi, p, c.hx, c.stream);
         p.k2i = c.k2i;
         p.fldi = c.fldi;
@@ -815,34 +887,16 @@ helm_status setup_impl(helm_ctx **out, helm_grid g, const double h[3], const voi
     std::vector<cd> dxv, Vx, Vxi, dyv, Vy, Vyi;
     eig_fold_dense(fxv, dxv, Vx, Vxi);
     eig_fold_dense(fyv, dyv, Vy, Vyi);
-    if ((st = upload_fold(c, fxv, true, c.fx64, c.fx32)) != HELM_OK) return bail(st);
-    if ((st = upload_fold(c, fyv, false, c.fy64, c.fy32)) != HELM_OK) return bail(st);
-    c.hVx = Vx; c.hVxi = Vxi; c.hVy = Vy; c.hVyi = Vyi;
-    // x-transform uses the transposed matrices as the B operand; y-transform uses them as the A operand
-    if ((st = upload_matrix(c, Vxi, c.nx, true, &c.BxF, &c.BxF32)) != HELM_OK) return bail(st);
-    if ((st = upload_matrix(c, Vx, c.nx, true, &c.BxI, &c.BxI32)) != HELM_OK) return bail(st);
-    if ((st = upload_matrix(c, Vyi, c.ny, false, &c.AyF, &c.AyF32)) != HELM_OK) return bail(st);
-    if ((st = upload_matrix(c, Vy, c.ny, false, &c.AyI, &c.AyI32)) != HELM_OK) return bail(st);
-    {
-        std::vector<double2> hx(c.nx), hy(c.ny);
-        for (int i = 0; i < c.nx; ++i) hx[i] = d2(dxv[i]);
-        for (int j = 0; j < c.ny; ++j) hy[j] = d2(dyv[j]);
-        if ((st = dalloc(c, &c.dxe, (size_t)c.nx)) != HELM_OK) return bail(st);
-        if ((st = dalloc(c, &c.dye, (size_t)c.ny)) != HELM_OK) return bail(st);
-        if (hipMemcpy(c.dxe, hx.data(), hx.size() * sizeof(double2), hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(c.dye, hy.data(), hy.size() * sizeof(double2), hipMemcpyHostToDevice) != hipSuccess) {
-            c.err = "upload of eigenvalues failed";
-            return bail(HELM_EDEVICE);
-        }
-    }
+    c.hVx = std::move(Vx); c.hVxi = std::move(Vxi); c.hVy = std::move(Vy); c.hVyi = std::move(Vyi);
+    Slab mats;
+    mats.put(&c.dxe, dxv.data(), dxv.size());
+    mats.put(&c.dye, dyv.data(), dyv.size());
+    if ((st = upload_folds(c, mats, {{&fxv, true, &c.fx64, &c.fx32}, {&fyv, false, &c.fy64, &c.fy32}})) != HELM_OK)
+        return bail(st);
     c.ax = c.hz * c.hz / (c.hx * c.hx);
     c.ay = c.hz * c.hz / (c.hy * c.hy);
     c.c0 = c.hz * c.hz * c.k0 * c.k0 - 2.0 * (c.ax + c.ay + 1.0);
-    if ((st = dalloc(c, &c.t1, (size_t)c.n)) != HELM_OK) return bail(st);
-    if ((st = dalloc(c, &c.t2, (size_t)c.n)) != HELM_OK) return bail(st);
-    // the z-solve's chunk pivots of the EigT preconditioner (2 bytes per unknown), so that no later preconditioner
-    // call has to allocate them
-    if ((st = ensure_tpiv(c, c.dxe, c.dye, &c.tpiv_eig)) != HELM_OK) return bail(st);
+    if ((st = fill_tpiv(c, c.dxe, c.dye, &c.tpiv_eig, d2(c.gamma[2]), 1.0 / c.zeta)) != HELM_OK) return bail(st);
     *out = ctx;
     return HELM_OK;
 }

@@ -37,6 +37,12 @@ using cd = std::complex<double>;
 
 namespace {
 
+// a b in four products and two sums: the operator's check of the result for NaN costs more than the product, and every
+// eigenpair is checked at the end (n = 64: 797 -> 703 us)
+inline cd mul(cd a, cd b) {
+    return cd(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+}
+
 // Givens rotation [[c, s], [-conj(s), c]] mapping (a, b) to (r, 0), c real.
 inline void givens(cd a, cd b, double &c, cd &s) {
     double aa = std::abs(a), bb = std::abs(b);
@@ -86,16 +92,16 @@ bool hessenberg_qr_eigenvalues(std::vector<cd> &H, int n, std::vector<cd> &ev) {
                 givens(at(k, k), at(k + 1, k), cs[k], sn[k]);
                 for (int j = k; j <= hi; ++j) {
                     cd x = at(k, j), y = at(k + 1, j);
-                    at(k, j) = cs[k] * x + sn[k] * y;
-                    at(k + 1, j) = -std::conj(sn[k]) * x + cs[k] * y;
+                    at(k, j) = cs[k] * x + mul(sn[k], y);
+                    at(k + 1, j) = mul(-std::conj(sn[k]), x) + cs[k] * y;
                 }
             }
             for (int k = lo; k < hi; ++k) {
                 int rmax = std::min(k + 2, hi);
                 for (int i = lo; i <= rmax; ++i) {
                     cd p = at(i, k), q = at(i, k + 1);
-                    at(i, k) = p * cs[k] + q * std::conj(sn[k]);
-                    at(i, k + 1) = -p * sn[k] + q * cs[k];
+                    at(i, k) = p * cs[k] + mul(q, std::conj(sn[k]));
+                    at(i, k + 1) = mul(-p, sn[k]) + q * cs[k];
                 }
             }
             for (int k = lo; k <= hi; ++k) at(k, k) += mu;
@@ -130,16 +136,16 @@ void tridiag_shifted_solve(const std::vector<cd> &lo, const std::vector<cd> &di,
             // the old row k had zero in column k+2 beyond cur2 (cur2 is column k+2)
             cd m = nxt0 / cur0;
             l[k] = m;
-            nxt0 = nxt1 - m * cur1;      // column k+1
-            nxt1 = nxt2 - m * cur2;      // column k+2
-            b[k + 1] -= m * b[k];
+            nxt0 = nxt1 - mul(m, cur1);  // column k+1
+            nxt1 = nxt2 - mul(m, cur2);  // column k+2
+            b[k + 1] -= mul(m, b[k]);
         } else {
             if (cur0 == cd(0.0)) cur0 = tiny;
             cd m = sub / cur0;
             l[k] = m;
-            nxt0 = nxt0 - m * cur1;
-            nxt1 = nxt1 - m * cur2;
-            b[k + 1] -= m * b[k];
+            nxt0 = nxt0 - mul(m, cur1);
+            nxt1 = nxt1 - mul(m, cur2);
+            b[k + 1] -= mul(m, b[k]);
         }
         u0[k] = cur0; u1[k] = cur1; u2[k] = cur2;
         cur0 = nxt0; cur1 = nxt1; cur2 = 0.0;
@@ -148,8 +154,8 @@ void tridiag_shifted_solve(const std::vector<cd> &lo, const std::vector<cd> &di,
     u0[n - 1] = cur0; u1[n - 1] = 0.0; u2[n - 1] = 0.0;
     for (int k = n - 1; k >= 0; --k) {
         cd s = b[k];
-        if (k + 1 < n) s -= u1[k] * b[k + 1];
-        if (k + 2 < n) s -= u2[k] * b[k + 2];
+        if (k + 1 < n) s -= mul(u1[k], b[k + 1]);
+        if (k + 2 < n) s -= mul(u2[k], b[k + 2]);
         cd d0 = u0[k];
         if (std::abs(d0) < tiny) d0 = tiny;
         b[k] = s / d0;
@@ -179,8 +185,8 @@ bool invert(std::vector<cd> &A, int n) {
             if (i == k) continue;
             cd m = A[(size_t)i * n + k] / piv;
             if (m == cd(0.0)) continue;
-            for (int j = k; j < n; ++j) A[(size_t)i * n + j] -= m * A[(size_t)k * n + j];
-            for (int j = 0; j < n; ++j) inv[(size_t)i * n + j] -= m * inv[(size_t)k * n + j];
+            for (int j = k; j < n; ++j) A[(size_t)i * n + j] -= mul(m, A[(size_t)k * n + j]);
+            for (int j = 0; j < n; ++j) inv[(size_t)i * n + j] -= mul(m, inv[(size_t)k * n + j]);
         }
         for (int j = k; j < n; ++j) A[(size_t)k * n + j] /= piv;
         for (int j = 0; j < n; ++j) inv[(size_t)k * n + j] /= piv;
@@ -209,9 +215,9 @@ bool eig_sym_tridiag(const std::vector<cd> &di, const std::vector<cd> &off, std:
 
     auto apply = [&](const std::vector<cd> &x, std::vector<cd> &y) {
         for (int i = 0; i < n; ++i) {
-            cd s = di[i] * x[i];
-            if (i > 0) s += lo[i - 1] * x[i - 1];
-            if (i + 1 < n) s += up[i] * x[i + 1];
+            cd s = mul(di[i], x[i]);
+            if (i > 0) s += mul(lo[i - 1], x[i - 1]);
+            if (i + 1 < n) s += mul(up[i], x[i + 1]);
             y[i] = s;
         }
     };
@@ -232,7 +238,7 @@ bool eig_sym_tridiag(const std::vector<cd> &di, const std::vector<cd> &off, std:
             if (it >= 1) {   // two-sided Rayleigh quotient (complex symmetric: left vector = x^T)
                 apply(x, y);
                 cd num = 0.0, den = 0.0;
-                for (int i = 0; i < n; ++i) { num += x[i] * y[i]; den += x[i] * x[i]; }
+                for (int i = 0; i < n; ++i) { num += mul(x[i], y[i]); den += mul(x[i], x[i]); }
                 if (std::abs(den) > 1e-8) lam = num / den;
             }
         }
@@ -244,7 +250,7 @@ bool eig_sym_tridiag(const std::vector<cd> &di, const std::vector<cd> &off, std:
     for (int k = 0; k < n; ++k) {
         for (int i = 0; i < n; ++i) x[i] = W[(size_t)i * n + k];
         apply(x, y);
-        for (int i = 0; i < n; ++i) res = std::max(res, std::abs(y[i] - d[k] * x[i]));
+        for (int i = 0; i < n; ++i) res = std::max(res, std::abs(y[i] - mul(d[k], x[i])));
     }
     if (!(res <= 1e-11 * anorm)) { err = "eig1d: eigenpair residual too large"; return false; }
     Winv = W;
@@ -253,7 +259,7 @@ bool eig_sym_tridiag(const std::vector<cd> &di, const std::vector<cd> &off, std:
     for (int i = 0; i < n; ++i) {
         for (int j = 0; j < n; ++j) {
             cd s = 0.0;
-            for (int k = 0; k < n; ++k) s += Winv[(size_t)i * n + k] * W[(size_t)k * n + j];
+            for (int k = 0; k < n; ++k) s += mul(Winv[(size_t)i * n + k], W[(size_t)k * n + j]);
             ortho = std::max(ortho, std::abs(s - (i == j ? cd(1.0) : cd(0.0))));
         }
     }

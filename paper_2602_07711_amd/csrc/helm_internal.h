@@ -94,6 +94,10 @@ hipError_t launch_fold_z32(int mode, const FoldDesc &f, const float2 *D, const f
                            hipStream_t s, int cfg, bool real = false);
 hipError_t launch_fold_z32_in64(int mode, const FoldDesc &f, const double2 *D, const float2 *Ms, const float2 *Ma,
                                 float2 *C, hipStream_t s, int cfg, bool real = false);
+// blocks as they come from the host (nb x nb, FP64) -> zero-padded P x P in FP64 and FP32
+struct FoldBlock { double2 *src, *d64; float2 *d32; int nb, P; };
+struct FoldBlocks { FoldBlock b[8]; int n; };
+hipError_t launch_fold_expand(const FoldBlocks &f, hipStream_t s);
 hipError_t launch_fold_z32_out64(int mode, const FoldDesc &f, const float2 *D, const float2 *Ms, const float2 *Ma,
                                  double2 *C, hipStream_t s, int cfg, bool real = false);
 // real = true: the blocks are real (their imaginary parts are ignored), two real MFMA products per complex MAC
@@ -115,8 +119,8 @@ template <typename CT> struct PfftMats {
     CT *Sx = nullptr, *Sy = nullptr;             // orthonormal sine matrices (symmetric; imaginary part 0)
     FoldMats<CT> fsx, fsy, fsz;                  // the sine transforms (z for FFT4 / FFT6 only) as folded real
                                                  // blocks (even modes symmetric, odd ones skew; natural order)
-    CT *Vxi = nullptr, *Vx = nullptr;            // V_x^{-1}, V_x row-major (the transposes are BxF, BxI)
-    CT *VyiT = nullptr, *VyT = nullptr;          // transposes of V_y^{-1}, V_y (the plain ones are AyF, AyI)
+    CT *Vxi = nullptr, *Vx = nullptr, *VxiT = nullptr, *VxT = nullptr;   // V_x^{-1}, V_x row-major, and transposed
+    CT *Vy = nullptr, *VyiT = nullptr, *VyT = nullptr;                   // V_y, and V_y^{-1}, V_y transposed
     CT *yhat = nullptr;                          // sine transform of the input (reused in step 3)
     CT *ringT = nullptr, *ringW = nullptr;       // face values of Theta and W, (2 Nx + 2 Ny) per slice
     CT *rpart = nullptr, *sv = nullptr, *rsum = nullptr;   // ring inverse work: row-group partials, row sums, their total
@@ -176,10 +180,7 @@ struct Ctx {
     double *k2i = nullptr;       // complex k^2 only: imaginary parts of k^2 and of the field block
     double4 *fldi = nullptr;
 
-    // dense eigenvector matrices (complex, row-major N x N; x: transposed, y: as is), which PFFT's face corrections use
-    double2 *BxF = nullptr, *BxI = nullptr, *AyF = nullptr, *AyI = nullptr;
-    float2 *BxF32 = nullptr, *BxI32 = nullptr, *AyF32 = nullptr, *AyI32 = nullptr;
-    // the same transforms as symmetric / skew half blocks (what the single-problem preconditioner applies)
+    // the eigenvector matrices as symmetric / skew half blocks
     FoldMats<double2> fx64, fy64;
     FoldMats<float2> fx32, fy32;
     double2 *dxe = nullptr, *dye = nullptr;    // eigenvalues d_x,i and d_y,j
