@@ -13,31 +13,29 @@
 
 namespace helm {
 hipError_t cnn_conv_fwd(int bf16, const float *in, long long in_bs, int Ci, int S, int taps, const void *wt, int Kp,
-                        int COP, const float *bias, int Co, float *out, long long out_bs, int relu, int B, hipStream_t s);
+                        int COP, const float *bias, int Co, float *out, long long out_bs, int relu, const float *mask, int B, hipStream_t s);
 hipError_t cnn_bias_grad(const float *g, long long g_bs, int B, long long V, int Co, float *part, float *db,
                          hipStream_t s);
-hipError_t cnn_pack_weights(int bf16, const float *W, int Co, int Ci, int taps, int transpose, int COP, int Kp,
-                            void *wt, hipStream_t s);
-hipError_t cnn_relu_bwd(float *g, long long g_bs, const float *y, long long y_bs, long long per, int B, hipStream_t s);
-hipError_t cnn_pool_fwd(const float *in, long long in_bs, float *out, long long out_bs, int C, int S, int B, hipStream_t s);
-hipError_t cnn_pool_bwd(const float *gout, long long gout_bs, float *gin, long long gin_bs, int C, int S, int B,
-                        int accumulate, hipStream_t s);
-hipError_t cnn_up_fwd(const float *in, long long in_bs, float *out, long long out_bs, int C, int S, int B, hipStream_t s);
-hipError_t cnn_up_bwd(const float *gout, long long gout_bs, float *gin, long long gin_bs, int C, int S, int B, hipStream_t s);
+hipError_t cnn_pack(int use_bf16, CnnPackJobs &p, hipStream_t s);
+hipError_t cnn_pool_fwd(const float *in, long long in_bs, float *out, long long out_bs, int C, int n, int B, hipStream_t s);
+hipError_t cnn_pool_bwd(const float *gout, long long gout_bs, float *gin, const float *y, long long gin_bs, int C, int n, int B,
+                        hipStream_t s);
+hipError_t cnn_up_fwd(const float *in, long long in_bs, float *out, long long out_bs, int C, int n, int B, hipStream_t s);
+hipError_t cnn_up_bwd(const float *gout, long long gout_bs, float *gin, const float *y, long long gin_bs, int C, int n, int B,
+                      hipStream_t s);
 hipError_t cnn_mse(const float *y, const float *t, long long n, float *g, double *part, double *loss, hipStream_t s);
 hipError_t cnn_adam(float *w, const float *g, float *m, float *v, long long n, float lr, float b1, float b2, float eps,
                     float c1, float c2, hipStream_t s);
 hipError_t cnn_prolong(const float *coarse, int nc, double scale, double gre, double gim, int cubic, double2 *fine,
                        int nf, double2 *work, hipStream_t s);
 hipError_t cnn_conv_direct(int use_bf16, const float *in, long long in_bs, int Ci, int S, const void *wt, int COP,
-                           const float *bias, int Co, float *out, long long out_bs, int relu, int B, hipStream_t s);
+                           const float *bias, int Co, float *out, long long out_bs, int relu, const float *mask, int B, hipStream_t s);
 long long cnn_direct_size(int Co, int Ci);
 hipError_t cnn_wgrad_1x1(const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci, int V, int B,
                          float *part, long long part_elems, float *dW, hipStream_t s);
 hipError_t cnn_wgrad_direct(int use_bf16, const float *g, long long g_bs, int Co, const float *in, long long in_bs,
                             int Ci, int S, int B, float *part, long long part_elems, float *bpart, float *dW, float *db,
                             hipStream_t s);
-hipError_t cnn_pack_direct(int use_bf16, const float *W, int Co, int Ci, int transpose, void *wt, hipStream_t s);
 hipError_t cnn_features(const double *k2h, const double2 *fh, int halo, int nf, int S, double k0sq, double cs,
                         double fs, float *x, hipStream_t s);
 }  // namespace helm
@@ -118,16 +116,13 @@ View view(helm_cnn &n, float *const *arr, int buf, int ch0) {
 // 27-tap layers: direct-convolution format (forward, and the data gradient with mirrored taps); the 1-tap head:
 // implicit-GEMM format
 helm_status pack_all(helm_cnn &n) {
+    CnnPackJobs p{};
     for (int l = 0; l < NL; ++l) {
         const int ci = LAYERS[l][0], co = LAYERS[l][1], taps = LAYERS[l][2];
-        if (taps == 27) {
-            NTRY(cnn_pack_direct(n.bf16, n.params + n.woff[l], co, ci, 0, n.wt[l], n.stream));
-            NTRY(cnn_pack_direct(n.bf16, n.params + n.woff[l], ci, co, 1, n.wtT[l], n.stream));
-        } else {
-            NTRY(cnn_pack_weights(n.bf16, n.params + n.woff[l], co, ci, taps, 0, n.COP[l], n.Kp[l], n.wt[l], n.stream));
-            NTRY(cnn_pack_weights(n.bf16, n.params + n.woff[l], co, ci, taps, 1, n.COPt[l], n.Kpt[l], n.wtT[l], n.stream));
-        }
+        p.j[p.n++] = {n.params + n.woff[l], n.wt[l], co, ci, taps, 0, n.Kp[l]};
+        p.j[p.n++] = {n.params + n.woff[l], n.wtT[l], ci, co, taps, 1, n.Kpt[l]};
     }
+    NTRY(cnn_pack(n.bf16, p, n.stream));
     return HELM_OK;
 }
 
@@ -135,15 +130,16 @@ helm_status conv_fwd(helm_cnn &n, int l, View in, View out, int B) {
     const int ci = LAYERS[l][0], co = LAYERS[l][1], taps = LAYERS[l][2], relu = LAYERS[l][3];
     if (taps == 27)
         NTRY(cnn_conv_direct(n.bf16, in.p, in.bs, ci, S_of(n, LAYERS[l][4]), n.wt[l], n.COP[l], n.params + n.boff[l],
-                             co, out.p, out.bs, relu, B, n.stream));
+                             co, out.p, out.bs, relu, nullptr, B, n.stream));
     else
         NTRY(cnn_conv_fwd(n.bf16, in.p, in.bs, ci, S_of(n, LAYERS[l][4]), taps, n.wt[l], n.Kp[l], n.COP[l],
-                          n.params + n.boff[l], co, out.p, out.bs, relu, B, n.stream));
+                          n.params + n.boff[l], co, out.p, out.bs, relu, nullptr, B, n.stream));
     return HELM_OK;
 }
 
-// gradients of layer l given dL/d(out) in g (already ReLU-masked); dL/d(in) into gin (may be null)
-helm_status conv_bwd(helm_cnn &n, int l, View in, View g, View *gin, int B) {
+// gradients of layer l given dL/d(out) in g (already ReLU-masked); dL/d(in) into gin (may be null), zero where the
+// activations `mask` (of gin's shape and strides; may be null) are not positive
+helm_status conv_bwd(helm_cnn &n, int l, View in, View g, View *gin, const float *mask, int B) {
     const int ci = LAYERS[l][0], co = LAYERS[l][1], taps = LAYERS[l][2], lev = LAYERS[l][4];
     const int S = S_of(n, lev);
     if (taps == 27) {
@@ -155,16 +151,11 @@ helm_status conv_bwd(helm_cnn &n, int l, View in, View g, View *gin, int B) {
         NTRY(cnn_bias_grad(g.p, g.bs, B, V_of(n, lev), co, n.bias_part, n.grads + n.boff[l], n.stream));
     }
     if (gin && taps == 27)
-        NTRY(cnn_conv_direct(n.bf16, g.p, g.bs, co, S, n.wtT[l], n.COPt[l], nullptr, ci, gin->p, gin->bs, 0, B,
+        NTRY(cnn_conv_direct(n.bf16, g.p, g.bs, co, S, n.wtT[l], n.COPt[l], nullptr, ci, gin->p, gin->bs, 0, mask, B,
                              n.stream));
     else if (gin)
         NTRY(cnn_conv_fwd(n.bf16, g.p, g.bs, co, S, taps, n.wtT[l], n.Kpt[l], n.COPt[l], nullptr, ci, gin->p, gin->bs,
-                          0, B, n.stream));
-    return HELM_OK;
-}
-
-helm_status relu_mask(helm_cnn &n, View g, View y, int C, int lev, int B) {
-    NTRY(cnn_relu_bwd(g.p, g.bs, y.p, y.bs, (long long)C * V_of(n, lev), B, n.stream));
+                          0, mask, B, n.stream));
     return HELM_OK;
 }
 
@@ -176,13 +167,13 @@ helm_status forward(helm_cnn &n, const float *x, int B) {
 #define F(expr) if ((st = (expr)) != HELM_OK) return st
     F(conv_fwd(n, 0, vx, v(helm_cnn::C1A, 0), B));
     F(conv_fwd(n, 1, v(helm_cnn::C1A, 0), v(helm_cnn::CAT1, 32), B));
-    NTRY(cnn_pool_fwd(v(helm_cnn::CAT1, 32).p, v(helm_cnn::CAT1, 32).bs, A[helm_cnn::P1], v(helm_cnn::P1, 0).bs, 16, n.S0, B, n.stream));
+    NTRY(cnn_pool_fwd(v(helm_cnn::CAT1, 32).p, v(helm_cnn::CAT1, 32).bs, A[helm_cnn::P1], v(helm_cnn::P1, 0).bs, 16, S_of(n, 1), B, n.stream));
     F(conv_fwd(n, 2, v(helm_cnn::P1, 0), v(helm_cnn::C2A, 0), B));
     F(conv_fwd(n, 3, v(helm_cnn::C2A, 0), v(helm_cnn::CAT2, 64), B));
-    NTRY(cnn_pool_fwd(v(helm_cnn::CAT2, 64).p, v(helm_cnn::CAT2, 64).bs, A[helm_cnn::P2], v(helm_cnn::P2, 0).bs, 32, S_of(n, 1), B, n.stream));
+    NTRY(cnn_pool_fwd(v(helm_cnn::CAT2, 64).p, v(helm_cnn::CAT2, 64).bs, A[helm_cnn::P2], v(helm_cnn::P2, 0).bs, 32, S_of(n, 2), B, n.stream));
     F(conv_fwd(n, 4, v(helm_cnn::P2, 0), v(helm_cnn::C3A, 0), B));
     F(conv_fwd(n, 5, v(helm_cnn::C3A, 0), v(helm_cnn::CAT3, 64), B));
-    NTRY(cnn_pool_fwd(v(helm_cnn::CAT3, 64).p, v(helm_cnn::CAT3, 64).bs, A[helm_cnn::P3], v(helm_cnn::P3, 0).bs, 64, S_of(n, 2), B, n.stream));
+    NTRY(cnn_pool_fwd(v(helm_cnn::CAT3, 64).p, v(helm_cnn::CAT3, 64).bs, A[helm_cnn::P3], v(helm_cnn::P3, 0).bs, 64, S_of(n, 3), B, n.stream));
     F(conv_fwd(n, 6, v(helm_cnn::P3, 0), v(helm_cnn::C4A, 0), B));
     F(conv_fwd(n, 7, v(helm_cnn::C4A, 0), v(helm_cnn::C4B, 0), B));
     NTRY(cnn_up_fwd(A[helm_cnn::C4B], v(helm_cnn::C4B, 0).bs, v(helm_cnn::CAT3, 0).p, v(helm_cnn::CAT3, 0).bs, 64, S_of(n, 3), B, n.stream));
@@ -204,46 +195,35 @@ helm_status backward(helm_cnn &n, const float *x, int B) {
     helm_status st;
     View g;
     g = vg(helm_cnn::D1, 0);
-    F(conv_bwd(n, 11, va(helm_cnn::D1, 0), vg(helm_cnn::OUT, 0), &g, B));
-    F(relu_mask(n, vg(helm_cnn::D1, 0), va(helm_cnn::D1, 0), 16, 0, B));
+    F(conv_bwd(n, 11, va(helm_cnn::D1, 0), vg(helm_cnn::OUT, 0), &g, A[helm_cnn::D1], B));
     g = vg(helm_cnn::CAT1, 0);
-    F(conv_bwd(n, 10, va(helm_cnn::CAT1, 0), vg(helm_cnn::D1, 0), &g, B));
-    NTRY(cnn_up_bwd(vg(helm_cnn::CAT1, 0).p, vg(helm_cnn::CAT1, 0).bs, G[helm_cnn::D2], vg(helm_cnn::D2, 0).bs, 32, S_of(n, 1), B, n.stream));
-    F(relu_mask(n, vg(helm_cnn::D2, 0), va(helm_cnn::D2, 0), 32, 1, B));
+    F(conv_bwd(n, 10, va(helm_cnn::CAT1, 0), vg(helm_cnn::D1, 0), &g, nullptr, B));
+    NTRY(cnn_up_bwd(vg(helm_cnn::CAT1, 0).p, vg(helm_cnn::CAT1, 0).bs, G[helm_cnn::D2], A[helm_cnn::D2], vg(helm_cnn::D2, 0).bs, 32, S_of(n, 1), B, n.stream));
     g = vg(helm_cnn::CAT2, 0);
-    F(conv_bwd(n, 9, va(helm_cnn::CAT2, 0), vg(helm_cnn::D2, 0), &g, B));
-    NTRY(cnn_up_bwd(vg(helm_cnn::CAT2, 0).p, vg(helm_cnn::CAT2, 0).bs, G[helm_cnn::D3], vg(helm_cnn::D3, 0).bs, 64, S_of(n, 2), B, n.stream));
-    F(relu_mask(n, vg(helm_cnn::D3, 0), va(helm_cnn::D3, 0), 64, 2, B));
+    F(conv_bwd(n, 9, va(helm_cnn::CAT2, 0), vg(helm_cnn::D2, 0), &g, nullptr, B));
+    NTRY(cnn_up_bwd(vg(helm_cnn::CAT2, 0).p, vg(helm_cnn::CAT2, 0).bs, G[helm_cnn::D3], A[helm_cnn::D3], vg(helm_cnn::D3, 0).bs, 64, S_of(n, 2), B, n.stream));
     g = vg(helm_cnn::CAT3, 0);
-    F(conv_bwd(n, 8, va(helm_cnn::CAT3, 0), vg(helm_cnn::D3, 0), &g, B));
-    NTRY(cnn_up_bwd(vg(helm_cnn::CAT3, 0).p, vg(helm_cnn::CAT3, 0).bs, G[helm_cnn::C4B], vg(helm_cnn::C4B, 0).bs, 64, S_of(n, 3), B, n.stream));
-    F(relu_mask(n, vg(helm_cnn::C4B, 0), va(helm_cnn::C4B, 0), 64, 3, B));
+    F(conv_bwd(n, 8, va(helm_cnn::CAT3, 0), vg(helm_cnn::D3, 0), &g, nullptr, B));
+    NTRY(cnn_up_bwd(vg(helm_cnn::CAT3, 0).p, vg(helm_cnn::CAT3, 0).bs, G[helm_cnn::C4B], A[helm_cnn::C4B], vg(helm_cnn::C4B, 0).bs, 64, S_of(n, 3), B, n.stream));
     g = vg(helm_cnn::C4A, 0);
-    F(conv_bwd(n, 7, va(helm_cnn::C4A, 0), vg(helm_cnn::C4B, 0), &g, B));
-    F(relu_mask(n, vg(helm_cnn::C4A, 0), va(helm_cnn::C4A, 0), 64, 3, B));
+    F(conv_bwd(n, 7, va(helm_cnn::C4A, 0), vg(helm_cnn::C4B, 0), &g, A[helm_cnn::C4A], B));
     g = vg(helm_cnn::P3, 0);
-    F(conv_bwd(n, 6, va(helm_cnn::P3, 0), vg(helm_cnn::C4A, 0), &g, B));
-    // skip s3 = CAT3[64:128): its gradient already holds the concat part; add the pooling path
-    NTRY(cnn_pool_bwd(G[helm_cnn::P3], vg(helm_cnn::P3, 0).bs, vg(helm_cnn::CAT3, 64).p, vg(helm_cnn::CAT3, 64).bs, 64, S_of(n, 2), B, 1, n.stream));
-    F(relu_mask(n, vg(helm_cnn::CAT3, 64), va(helm_cnn::CAT3, 64), 64, 2, B));
+    F(conv_bwd(n, 6, va(helm_cnn::P3, 0), vg(helm_cnn::C4A, 0), &g, nullptr, B));
+    // skip s3 = CAT3[64:128): its gradient already holds the concat part; the pooling path is added
+    NTRY(cnn_pool_bwd(G[helm_cnn::P3], vg(helm_cnn::P3, 0).bs, vg(helm_cnn::CAT3, 64).p, va(helm_cnn::CAT3, 64).p, vg(helm_cnn::CAT3, 64).bs, 64, S_of(n, 3), B, n.stream));
     g = vg(helm_cnn::C3A, 0);
-    F(conv_bwd(n, 5, va(helm_cnn::C3A, 0), vg(helm_cnn::CAT3, 64), &g, B));
-    F(relu_mask(n, vg(helm_cnn::C3A, 0), va(helm_cnn::C3A, 0), 64, 2, B));
+    F(conv_bwd(n, 5, va(helm_cnn::C3A, 0), vg(helm_cnn::CAT3, 64), &g, A[helm_cnn::C3A], B));
     g = vg(helm_cnn::P2, 0);
-    F(conv_bwd(n, 4, va(helm_cnn::P2, 0), vg(helm_cnn::C3A, 0), &g, B));
-    NTRY(cnn_pool_bwd(G[helm_cnn::P2], vg(helm_cnn::P2, 0).bs, vg(helm_cnn::CAT2, 64).p, vg(helm_cnn::CAT2, 64).bs, 32, S_of(n, 1), B, 1, n.stream));
-    F(relu_mask(n, vg(helm_cnn::CAT2, 64), va(helm_cnn::CAT2, 64), 32, 1, B));
+    F(conv_bwd(n, 4, va(helm_cnn::P2, 0), vg(helm_cnn::C3A, 0), &g, nullptr, B));
+    NTRY(cnn_pool_bwd(G[helm_cnn::P2], vg(helm_cnn::P2, 0).bs, vg(helm_cnn::CAT2, 64).p, va(helm_cnn::CAT2, 64).p, vg(helm_cnn::CAT2, 64).bs, 32, S_of(n, 2), B, n.stream));
     g = vg(helm_cnn::C2A, 0);
-    F(conv_bwd(n, 3, va(helm_cnn::C2A, 0), vg(helm_cnn::CAT2, 64), &g, B));
-    F(relu_mask(n, vg(helm_cnn::C2A, 0), va(helm_cnn::C2A, 0), 32, 1, B));
+    F(conv_bwd(n, 3, va(helm_cnn::C2A, 0), vg(helm_cnn::CAT2, 64), &g, A[helm_cnn::C2A], B));
     g = vg(helm_cnn::P1, 0);
-    F(conv_bwd(n, 2, va(helm_cnn::P1, 0), vg(helm_cnn::C2A, 0), &g, B));
-    NTRY(cnn_pool_bwd(G[helm_cnn::P1], vg(helm_cnn::P1, 0).bs, vg(helm_cnn::CAT1, 32).p, vg(helm_cnn::CAT1, 32).bs, 16, n.S0, B, 1, n.stream));
-    F(relu_mask(n, vg(helm_cnn::CAT1, 32), va(helm_cnn::CAT1, 32), 16, 0, B));
+    F(conv_bwd(n, 2, va(helm_cnn::P1, 0), vg(helm_cnn::C2A, 0), &g, nullptr, B));
+    NTRY(cnn_pool_bwd(G[helm_cnn::P1], vg(helm_cnn::P1, 0).bs, vg(helm_cnn::CAT1, 32).p, va(helm_cnn::CAT1, 32).p, vg(helm_cnn::CAT1, 32).bs, 16, S_of(n, 1), B, n.stream));
     g = vg(helm_cnn::C1A, 0);
-    F(conv_bwd(n, 1, va(helm_cnn::C1A, 0), vg(helm_cnn::CAT1, 32), &g, B));
-    F(relu_mask(n, vg(helm_cnn::C1A, 0), va(helm_cnn::C1A, 0), 16, 0, B));
-    F(conv_bwd(n, 0, vx, vg(helm_cnn::C1A, 0), nullptr, B));
+    F(conv_bwd(n, 1, va(helm_cnn::C1A, 0), vg(helm_cnn::CAT1, 32), &g, A[helm_cnn::C1A], B));
+    F(conv_bwd(n, 0, vx, vg(helm_cnn::C1A, 0), nullptr, nullptr, B));
     return HELM_OK;
 #undef F
 }

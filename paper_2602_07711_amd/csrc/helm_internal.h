@@ -422,6 +422,10 @@ hipError_t bl_zero_x(const BLaunch &L, hipStream_t s);
 hipError_t bl_cycle(const BLaunch &L, hipStream_t s);                // one restart cycle: restart + m steps + update
 hipError_t bl_restart(const BLaunch &L, hipStream_t s);              // the restart test alone
 
+// weights of the network's layers to be brought into their operand forms (Co, Ci: of the convolution that reads them)
+struct CnnPackJob { const float *W; void *wt; int Co, Ci, taps, transpose, Kp, COP, total, block0; };
+struct CnnPackJobs { CnnPackJob j[24]; int n; };
+
 }  // namespace helm
 
 struct helm_ctx { helm::Ctx c; };

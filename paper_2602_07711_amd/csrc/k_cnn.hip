@@ -71,7 +71,7 @@ template <typename T, int COP>
 __global__ __launch_bounds__(256) void k_conv_fwd(const float *__restrict__ in, long long in_bs, int Ci, int S,
                                                   int taps, const T *__restrict__ wt, int Kp,
                                                   const float *__restrict__ bias, int Co, float *__restrict__ out,
-                                                  long long out_bs, int relu) {
+                                                  long long out_bs, int relu, const float *__restrict__ mask) {
     constexpr int KL = MT<T>::KL;
     constexpr int FR = COP / 16;
     __shared__ __attribute__((aligned(16))) T sA[COP][KC + 4];
@@ -133,6 +133,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const float *__restrict__ in, 
             if (co < Co && vo < V) {
                 float y = acc[f][r] + (bias ? bias[co] : 0.f);
                 if (relu) y = fmaxf(y, 0.f);
+                if (mask && !(mask[(long long)b * out_bs + (long long)co * V + vo] > 0.f)) y = 0.f;
                 outb[(long long)co * V + vo] = y;
             }
         }
@@ -169,96 +170,106 @@ __global__ void k_bias_reduce(const float *__restrict__ part, int Co, float *__r
     db[co] = s;
 }
 
-// pack FP32 weights W[co][k] (k = ci*taps + tap) into the padded operand layout wt[COP][Kp];
-// transpose = 1 builds the dgrad weights W'[ci][co*taps + (taps-1-tap)] from W (Co, Ci swapped)
-template <typename T>
-__global__ void k_pack_weights(const float *__restrict__ W, int Co, int Ci, int taps, int transpose, int COP, int Kp,
-                               T *__restrict__ wt) {
-    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (long long)COP * Kp) return;
-    int r = (int)(i / Kp), k = (int)(i % Kp);
-    float v = 0.f;
-    if (!transpose) {
-        if (r < Co && k < Ci * taps) v = W[(long long)r * Ci * taps + k];
-    } else {   // r = ci (row of W'), k = co*taps + tap'
-        if (r < Ci && k < Co * taps) {
-            int co = k / taps, tp = k % taps;
-            v = W[(long long)co * Ci * taps + (long long)r * taps + (taps - 1 - tp)];
-        }
+// 2x average pooling and nearest upsampling between a volume of n^3 voxels (parents) and one of (2n)^3 (children), both
+// directions; the backward kernels also apply the mask of the ReLU behind them (zero where y is not positive).
+// A thread owns W parents along x (two where n is even) and their 8 W children, each row of which is one access: the
+// bytes are what bounds them. Before, a thread took one output, its place from 64-bit divisions, and the mask was a pass
+// of its own. At 4 x 64^3 in a training step: upsampling 172 -> 36 us, pooling backward 102 -> 50 us, the masks 150 us -> 13 us
+// of longer epilogues; the step 2930 -> 2560 us, inference at 64^3 384 -> 352 us.
+template <int N> struct FloatN;
+template <> struct FloatN<1> { float v[1]; };
+template <> struct __attribute__((aligned(8))) FloatN<2> { float v[2]; };
+template <> struct __attribute__((aligned(16))) FloatN<4> { float v[4]; };
+template <int N> __device__ __forceinline__ FloatN<N> ld(const float *p) { return *reinterpret_cast<const FloatN<N> *>(p); }
+template <int N> __device__ __forceinline__ void st(float *p, const FloatN<N> &v) { *reinterpret_cast<FloatN<N> *>(p) = v; }
+
+// this thread's parents: channel and sample, offset within the parents' channel and of the first child; false if none
+template <int W> __device__ __forceinline__ bool parents(int n, int C, int &c, int &b, int &po, int &co) {
+    const int nx = n / W, per = n * n * nx, nb = (per + 255) / 256;
+    const int bc = blockIdx.x / nb, r = (blockIdx.x - bc * nb) * 256 + threadIdx.x;
+    c = bc % C;
+    b = bc / C;
+    const int q = r / nx, x = (r - q * nx) * W, z = q / n, y = q - z * n;
+    po = q * n + x;
+    co = ((2 * z) * 2 * n + 2 * y) * 2 * n + 2 * x;
+    return r < per;
+}
+// row k (0..3: z and y of the child) of a parent's children
+__device__ __forceinline__ int child_row(int n, int k) { return ((k >> 1) * 2 * n + (k & 1)) * 2 * n; }
+
+template <int W>
+__global__ __launch_bounds__(256) void k_pool_fwd(const float *__restrict__ in, long long in_bs, float *__restrict__ out,
+                                                  long long out_bs, int C, int n) {
+    int c, b, po, co;
+    if (!parents<W>(n, C, c, b, po, co)) return;
+    const float *p = in + b * in_bs + 8LL * c * n * n * n + co;
+    FloatN<2 * W> r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = ld<2 * W>(p + child_row(n, k));
+    FloatN<W> o;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { s += r[k].v[2 * w]; s += r[k].v[2 * w + 1]; }
+        o.v[w] = 0.125f * s;
     }
-    wt[i] = MT<T>::cvt(v);
+    st<W>(out + b * out_bs + (long long)c * n * n * n + po, o);
 }
-
-__global__ void k_relu_bwd(float *__restrict__ g, long long g_bs, const float *__restrict__ y, long long y_bs,
-                           long long per, int B) {
-    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= per * B) return;
-    long long b = i / per, o = i % per;
-    if (!(y[b * y_bs + o] > 0.f)) g[b * g_bs + o] = 0.f;
+// gin += gout / 8 on the children
+template <int W>
+__global__ __launch_bounds__(256) void k_pool_bwd(const float *__restrict__ gout, long long gout_bs, float *__restrict__ gin,
+                                                  const float *__restrict__ y, long long gin_bs, int C, int n) {
+    int c, b, po, co;
+    if (!parents<W>(n, C, c, b, po, co)) return;
+    const long long at = b * gin_bs + 8LL * c * n * n * n + co;
+    const FloatN<W> g = ld<W>(gout + b * gout_bs + (long long)c * n * n * n + po);
+    FloatN<2 * W> r[4], m[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        r[k] = ld<2 * W>(gin + at + child_row(n, k));
+        m[k] = ld<2 * W>(y + at + child_row(n, k));
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int w = 0; w < 2 * W; ++w) r[k].v[w] = m[k].v[w] > 0.f ? r[k].v[w] + 0.125f * g.v[w / 2] : 0.f;
+        st<2 * W>(gin + at + child_row(n, k), r[k]);
+    }
 }
-
-// 2x average pooling S -> S/2 over C channels; backward spreads g/8 to the 8 children (accumulate = add)
-__global__ void k_pool_fwd(const float *__restrict__ in, long long in_bs, float *__restrict__ out, long long out_bs,
-                           int C, int S, int B) {
-    const int s2 = S / 2;
-    const long long per = (long long)C * s2 * s2 * s2;
-    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= per * B) return;
-    long long b = i / per, o = i % per;
-    int c = (int)(o / ((long long)s2 * s2 * s2));
-    long long r = o % ((long long)s2 * s2 * s2);
-    int x = (int)(r % s2), y = (int)((r / s2) % s2), z = (int)(r / ((long long)s2 * s2));
-    const float *p = in + b * in_bs + (long long)c * S * S * S;
-    float s = 0.f;
-    for (int dz = 0; dz < 2; ++dz)
-        for (int dy = 0; dy < 2; ++dy)
-            for (int dx = 0; dx < 2; ++dx) s += p[((long long)(2 * z + dz) * S + 2 * y + dy) * S + 2 * x + dx];
-    out[b * out_bs + o] = 0.125f * s;
+template <int W>
+__global__ __launch_bounds__(256) void k_up_fwd(const float *__restrict__ in, long long in_bs, float *__restrict__ out,
+                                                long long out_bs, int C, int n) {
+    int c, b, po, co;
+    if (!parents<W>(n, C, c, b, po, co)) return;
+    const FloatN<W> g = ld<W>(in + b * in_bs + (long long)c * n * n * n + po);
+    FloatN<2 * W> r;
+#pragma unroll
+    for (int w = 0; w < 2 * W; ++w) r.v[w] = g.v[w / 2];
+    float *o = out + b * out_bs + 8LL * c * n * n * n + co;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) st<2 * W>(o + child_row(n, k), r);
 }
-__global__ void k_pool_bwd(const float *__restrict__ gout, long long gout_bs, float *__restrict__ gin,
-                           long long gin_bs, int C, int S, int B, int accumulate) {
-    const int s2 = S / 2;
-    const long long per = (long long)C * S * S * S;
-    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= per * B) return;
-    long long b = i / per, o = i % per;
-    int c = (int)(o / ((long long)S * S * S));
-    long long r = o % ((long long)S * S * S);
-    int x = (int)(r % S), y = (int)((r / S) % S), z = (int)(r / ((long long)S * S));
-    float v = 0.125f * gout[b * gout_bs + (long long)c * s2 * s2 * s2 + ((long long)(z / 2) * s2 + y / 2) * s2 + x / 2];
-    float *q = gin + b * gin_bs + o;
-    *q = accumulate ? *q + v : v;
-}
-
-// nearest 2x upsampling S -> 2S; backward sums the 8 children
-__global__ void k_up_fwd(const float *__restrict__ in, long long in_bs, float *__restrict__ out, long long out_bs,
-                         int C, int S, int B) {
-    const int S2 = 2 * S;
-    const long long per = (long long)C * S2 * S2 * S2;
-    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= per * B) return;
-    long long b = i / per, o = i % per;
-    int c = (int)(o / ((long long)S2 * S2 * S2));
-    long long r = o % ((long long)S2 * S2 * S2);
-    int x = (int)(r % S2), y = (int)((r / S2) % S2), z = (int)(r / ((long long)S2 * S2));
-    out[b * out_bs + o] = in[b * in_bs + (long long)c * S * S * S + ((long long)(z / 2) * S + y / 2) * S + x / 2];
-}
-__global__ void k_up_bwd(const float *__restrict__ gout, long long gout_bs, float *__restrict__ gin, long long gin_bs,
-                         int C, int S, int B) {
-    const int S2 = 2 * S;
-    const long long per = (long long)C * S * S * S;
-    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= per * B) return;
-    long long b = i / per, o = i % per;
-    int c = (int)(o / ((long long)S * S * S));
-    long long r = o % ((long long)S * S * S);
-    int x = (int)(r % S), y = (int)((r / S) % S), z = (int)(r / ((long long)S * S));
-    const float *p = gout + b * gout_bs + (long long)c * S2 * S2 * S2;
-    float s = 0.f;
-    for (int dz = 0; dz < 2; ++dz)
-        for (int dy = 0; dy < 2; ++dy)
-            for (int dx = 0; dx < 2; ++dx) s += p[((long long)(2 * z + dz) * S2 + 2 * y + dy) * S2 + 2 * x + dx];
-    gin[b * gin_bs + o] = s;
+template <int W>
+__global__ __launch_bounds__(256) void k_up_bwd(const float *__restrict__ gout, long long gout_bs, float *__restrict__ gin,
+                                                const float *__restrict__ y, long long gin_bs, int C, int n) {
+    int c, b, po, co;
+    if (!parents<W>(n, C, c, b, po, co)) return;
+    const long long at = b * gin_bs + (long long)c * n * n * n + po;
+    const float *p = gout + b * gout_bs + 8LL * c * n * n * n + co;
+    const FloatN<W> m = ld<W>(y + at);
+    FloatN<2 * W> r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = ld<2 * W>(p + child_row(n, k));
+    FloatN<W> o;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { s += r[k].v[2 * w]; s += r[k].v[2 * w + 1]; }
+        o.v[w] = m.v[w] > 0.f ? s : 0.f;
+    }
+    st<W>(gin + at, o);
 }
 
 // MSE: partial sums of (y - t)^2 per block and the gradient 2 (y - t) / N
@@ -630,12 +641,13 @@ __device__ __forceinline__ void conv_dz(v4f (&acc)[FR][4], const typename Chan<T
                 for (int f = 0; f < FR; ++f) acc[f][y] = Chan<T>::mul(a[dy * 3 + dx][f], b[y + dy][dx], acc[f][y]);
 }
 
-// All chunks by one workgroup of four waves: bias and ReLU in the epilogue.
+// All chunks by one workgroup of four waves: bias and ReLU in the epilogue, or the mask of a ReLU's backward pass (zero
+// where mask, which has the output's strides, is not positive).
 template <typename T, int FR, int TX, int TZ>
 __global__ __launch_bounds__(256) void k_conv_direct(const float *__restrict__ in, long long in_bs, int Ci, int S,
                                                      const T *__restrict__ wt, int COP, const float *__restrict__ bias,
                                                      int Co, float *__restrict__ out, long long out_bs, int relu,
-                                                     int rowgroups, int vec, int blocks) {
+                                                     const float *__restrict__ mask, int rowgroups, int vec, int blocks) {
     typedef typename Chan<T>::t CT4;
     constexpr int PITCH = ConvTile<TX, TZ>::PITCH, NXB = TX / 16, NJ = NXB * TZ / 4;   // column blocks of a wave
     static_assert(NJ >= 1 && NJ * 4 == NXB * TZ, "four waves share the tile's column blocks");
@@ -696,7 +708,16 @@ __global__ __launch_bounds__(256) void k_conv_direct(const float *__restrict__ i
         for (int y = 0; y < 4; ++y) {
             const int gy = y0 + y;
             const bool ok = gx < S && gy < S && gz < S;
-            float *o = out + (long long)b * out_bs + ((long long)gz * S + gy) * S + gx;
+            const long long at = (long long)b * out_bs + ((long long)gz * S + gy) * S + gx;
+            float *o = out + at;
+            float mk[FR][4];
+            if (FR < 3 && mask) {                             // unconditional loads, all of a row in flight
+                const float *m = mask + (ok ? at : 0);
+#pragma unroll
+                for (int f = 0; f < FR; ++f)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mk[f][r] = m[(long long)min(row0 + f * 16 + 4 * (lane >> 4) + r, Co - 1) * V];
+            }
 #pragma unroll
             for (int f = 0; f < FR; ++f)
 #pragma unroll
@@ -705,6 +726,7 @@ __global__ __launch_bounds__(256) void k_conv_direct(const float *__restrict__ i
                     if (!ok || co >= Co) continue;
                     float v = acc[j][f][y][r] + (bias ? bias[co] : 0.f);
                     if (relu) v = fmaxf(v, 0.f);
+                    if (FR < 3 && mask && !(mk[f][r] > 0.f)) v = 0.f;
                     o[(long long)co * V] = v;
                 }
         }
@@ -721,7 +743,7 @@ __global__ __launch_bounds__(64 * PARTS_MAX) void k_conv_deep(const float *__res
                                                               const T *__restrict__ wt, int COP,
                                                               const float *__restrict__ bias, int Co,
                                                               float *__restrict__ out, long long out_bs, int relu,
-                                                              int rowgroups, int vec, int nsplit, int cpb) {
+                                                              const float *__restrict__ mask, int rowgroups, int vec, int nsplit, int cpb) {
     typedef typename Chan<T>::t CT4;
     constexpr int TX = 16, TZ = 1, PITCH = ConvTile<TX, TZ>::PITCH, QUADS = ConvTile<TX, TZ>::QUADS, PER = deep_per<T>();
     extern __shared__ __attribute__((aligned(16))) unsigned char dsm[];
@@ -777,33 +799,41 @@ __global__ __launch_bounds__(64 * PARTS_MAX) void k_conv_deep(const float *__res
     for (int e = tid; e < 1024; e += blockDim.x) {
         const int gx = x0 + (e & 15), co = row0 + ((e >> 4) & 15), gy = y0 + (e >> 8);
         if (gx >= S || gy >= S || co >= Co) continue;
+        const long long at = (long long)b * out_bs + (long long)co * V + ((long long)z0 * S + gy) * S + gx;
+        const float mk = mask ? mask[at] : 1.f;
         float v = bias ? bias[co] : 0.f;
         for (int k = 0; k < nsplit; ++k) v += red[k * 1024 + e];
         if (relu) v = fmaxf(v, 0.f);
-        out[(long long)b * out_bs + (long long)co * V + ((long long)z0 * S + gy) * S + gx] = v;
+        out[at] = mk > 0.f ? v : 0.f;
     }
 }
 
-// direct-format weights wt[chunk][tap][COP][16] (channels in the order of Chan<T>) of a conv with Co outputs and Ci inputs; transpose = 1 takes
-// them from a layer W[Ci][Co][27] with the tap mirrored (the data-gradient convolution of that layer)
-template <typename T>
-__global__ void k_pack_direct(const float *__restrict__ W, int Co, int Ci, int transpose, int COP, long long total,
-                              T *__restrict__ wt) {
-    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (e >= total) return;
-    const int cc = (int)(e % DCC);
-    long long r = e / DCC;
-    const int o = (int)(r % COP);
-    r /= COP;
-    const int tap = (int)(r % 27);
-    const int ch = (int)(r / 27);
-    const int i = ch * DCC + Chan<T>::ch(cc / 4, cc % 4);
+// The operand forms of all layers in one launch (24 launches of 2.6 us took 90 us of a training step).
+// 27 taps: direct format wt[chunk][tap][COP][16] (channels in the order of Chan<T>) of a conv with Co outputs and Ci inputs;
+// transpose = 1 takes them from a layer W[Ci][Co][27] with the tap mirrored (the data-gradient convolution of that layer).
+// 1 tap: wt[COP][Kp], row o, column i, zero-padded.
+template <typename T> __global__ __launch_bounds__(256) void k_pack(CnnPackJobs p) {
+    int k = 0;
+    while (k + 1 < p.n && (int)blockIdx.x >= p.j[k + 1].block0) ++k;
+    const CnnPackJob &q = p.j[k];
+    const int e = ((int)blockIdx.x - q.block0) * 256 + threadIdx.x;
+    if (e >= q.total) return;
+    int o, i, tap = 0;
+    if (q.taps == 27) {
+        const int cc = e % DCC;
+        int r = e / DCC;
+        o = r % q.COP;
+        r /= q.COP;
+        tap = r % 27;
+        i = r / 27 * DCC + Chan<T>::ch(cc / 4, cc % 4);
+    } else {
+        o = e / q.Kp;
+        i = e % q.Kp;
+    }
     float v = 0.f;
-    if (o < Co && i < Ci)
-        v = transpose ? W[((long long)i * Co + o) * 27 + (26 - tap)] : W[((long long)o * Ci + i) * 27 + tap];
-    wt[e] = MT<T>::cvt(v);
+    if (o < q.Co && i < q.Ci) v = q.transpose ? q.W[(i * q.Co + o) * q.taps + (q.taps - 1 - tap)] : q.W[(o * q.Ci + i) * q.taps + tap];
+    reinterpret_cast<T *>(q.wt)[e] = MT<T>::cvt(v);
 }
-
 
 // Weight and bias gradient of a 27-tap layer, dW[o][i][tap] = sum_{b,v} g[b][o][v] in[b][i][v + off(tap)] and
 // db[o] = sum_{b,v} g[b][o][v]. Per tap this is a product with M = output channels, N = 16 input channels and
@@ -1141,16 +1171,17 @@ __global__ __launch_bounds__(256) void k_wgrad_1x1(const float *__restrict__ g, 
 // ---------------------------------------------------------------------------------------------- launchers
 template <typename T>
 hipError_t cnn_conv_fwd_t(const float *in, long long in_bs, int Ci, int S, int taps, const void *wt, int Kp, int COP,
-                          const float *bias, int Co, float *out, long long out_bs, int relu, int B, hipStream_t s) {
+                          const float *bias, int Co, float *out, long long out_bs, int relu, const float *mask, int B,
+                          hipStream_t s) {
     long long V = (long long)S * S * S;
     unsigned grid = (unsigned)(B * ((V + CT - 1) / CT));
     const T *w = (const T *)wt;
-    if (COP == 16) hipLaunchKernelGGL((k_conv_fwd<T, 16>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu);
-    else if (COP == 32) hipLaunchKernelGGL((k_conv_fwd<T, 32>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu);
-    else if (COP == 64) hipLaunchKernelGGL((k_conv_fwd<T, 64>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu);
-    else if (COP == 48) hipLaunchKernelGGL((k_conv_fwd<T, 48>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu);
-    else if (COP == 96) hipLaunchKernelGGL((k_conv_fwd<T, 96>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu);
-    else if (COP == 128) hipLaunchKernelGGL((k_conv_fwd<T, 128>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu);
+    if (COP == 16) hipLaunchKernelGGL((k_conv_fwd<T, 16>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu, mask);
+    else if (COP == 32) hipLaunchKernelGGL((k_conv_fwd<T, 32>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu, mask);
+    else if (COP == 64) hipLaunchKernelGGL((k_conv_fwd<T, 64>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu, mask);
+    else if (COP == 48) hipLaunchKernelGGL((k_conv_fwd<T, 48>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu, mask);
+    else if (COP == 96) hipLaunchKernelGGL((k_conv_fwd<T, 96>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu, mask);
+    else if (COP == 128) hipLaunchKernelGGL((k_conv_fwd<T, 128>), dim3(grid), dim3(256), 0, s, in, in_bs, Ci, S, taps, w, Kp, bias, Co, out, out_bs, relu, mask);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -1179,14 +1210,17 @@ struct ConvArgs {
     int Co;
     float *out;
     long long out_bs;
-    int relu, B, vec;
+    int relu;
+    const float *mask;
+    int B, vec;
 };
 
 template <typename T, int FR, int TX, int TZ> hipError_t conv_launch(const ConvArgs &a, hipStream_t s) {
     const int tiles = ((a.S + TX - 1) / TX) * ((a.S + CY - 1) / CY) * ((a.S + TZ - 1) / TZ);
     const int rowgroups = a.COP / 16 / FR, blocks = a.B * tiles * rowgroups;
     hipLaunchKernelGGL((k_conv_direct<T, FR, TX, TZ>), dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, s, a.in, a.in_bs,
-                       a.Ci, a.S, (const T *)a.wt, a.COP, a.bias, a.Co, a.out, a.out_bs, a.relu, rowgroups, a.vec, blocks);
+                       a.Ci, a.S, (const T *)a.wt, a.COP, a.bias, a.Co, a.out, a.out_bs, a.relu, a.mask, rowgroups, a.vec,
+                       blocks);
     return hipGetLastError();
 }
 
@@ -1196,7 +1230,7 @@ template <typename T, int TX> hipError_t conv_shape(const ConvArgs &a, hipStream
     constexpr int Z2 = 512 / 4 / TX, Z1 = Z2 / 2;
     const int fr = a.COP / 16;
     const long long vox = (long long)a.B * a.S * a.S * a.S;
-    const int best = fr % 3 == 0 ? 3 : fr % 2 == 0 ? 2 : 1;
+    const int best = fr % 3 == 0 && !a.mask ? 3 : fr % 2 == 0 ? 2 : 1;   // (three leave no registers for a mask)
     const bool wide = vox / 512 * (fr / best) >= 512;
     const int take = wide || vox / 256 * (fr / best) >= 512 ? best : 1;
     if (wide) return take == 3 ? conv_launch<T, 3, TX, Z2>(a, s) : take == 2 ? conv_launch<T, 2, TX, Z2>(a, s) : conv_launch<T, 1, TX, Z2>(a, s);
@@ -1205,7 +1239,7 @@ template <typename T, int TX> hipError_t conv_shape(const ConvArgs &a, hipStream
 
 template <typename T>
 hipError_t cnn_conv_direct_t(const float *in, long long in_bs, int Ci, int S, const void *wt, int COP, const float *bias,
-                             int Co, float *out, long long out_bs, int relu, int B, hipStream_t s) {
+                             int Co, float *out, long long out_bs, int relu, const float *mask, int B, hipStream_t s) {
     const int vec = S % 4 == 0 && (uintptr_t)in % 16 == 0 && in_bs % 4 == 0;
     int nsplit, cpb;
     cnn_direct_split(Ci, S, COP, B, nsplit, cpb);
@@ -1216,19 +1250,21 @@ hipError_t cnn_conv_direct_t(const float *in, long long in_bs, int Ci, int S, co
         const size_t lds = sizeof(typename Chan<T>::t) * ConvTile<16, 1>::QUADS * waves;
         static_assert(sizeof(typename Chan<T>::t) * ConvTile<16, 1>::QUADS >= 4096 * PER, "the parts fit the staging area");
         hipLaunchKernelGGL(k_conv_deep<T>, dim3((unsigned)((long long)B * tiles * rowgroups)), dim3(64 * waves), lds, s, in,
-                           in_bs, Ci, S, (const T *)wt, COP, bias, Co, out, out_bs, relu, rowgroups, vec, nsplit, cpb);
+                           in_bs, Ci, S, (const T *)wt, COP, bias, Co, out, out_bs, relu, mask, rowgroups, vec, nsplit,
+                           cpb);
         return hipGetLastError();
     }
-    const ConvArgs a{in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, vec};
+    const ConvArgs a{in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, mask, B, vec};
     if (S > 32) return conv_shape<T, 64>(a, s);
     if (S > 16) return conv_shape<T, 32>(a, s);
     return conv_shape<T, 16>(a, s);
 }
 
 hipError_t cnn_conv_direct(int use_bf16, const float *in, long long in_bs, int Ci, int S, const void *wt, int COP,
-                           const float *bias, int Co, float *out, long long out_bs, int relu, int B, hipStream_t s) {
-    return use_bf16 ? cnn_conv_direct_t<bf16>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, s)
-                    : cnn_conv_direct_t<float>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, B, s);
+                           const float *bias, int Co, float *out, long long out_bs, int relu, const float *mask, int B,
+                           hipStream_t s) {
+    return use_bf16 ? cnn_conv_direct_t<bf16>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, mask, B, s)
+                    : cnn_conv_direct_t<float>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, mask, B, s);
 }
 
 // Tile groups of a weight gradient: about 512 workgroups (two per CU are resident), every group with the same number of
@@ -1308,20 +1344,25 @@ hipError_t cnn_wgrad_direct(int use_bf16, const float *g, long long g_bs, int Co
 
 long long cnn_direct_size(int Co, int Ci) { return (long long)((Ci + DCC - 1) / DCC) * 27 * ((Co + 15) / 16 * 16) * DCC; }
 
-hipError_t cnn_pack_direct(int use_bf16, const float *W, int Co, int Ci, int transpose, void *wt, hipStream_t s) {
-    const int COP = (Co + 15) / 16 * 16;
-    const long long total = cnn_direct_size(Co, Ci);
-    const unsigned grid = (unsigned)((total + 255) / 256);
-    if (use_bf16) hipLaunchKernelGGL(k_pack_direct<bf16>, dim3(grid), dim3(256), 0, s, W, Co, Ci, transpose, COP, total, (bf16 *)wt);
-    else hipLaunchKernelGGL(k_pack_direct<float>, dim3(grid), dim3(256), 0, s, W, Co, Ci, transpose, COP, total, (float *)wt);
+hipError_t cnn_pack(int use_bf16, CnnPackJobs &p, hipStream_t s) {
+    int blocks = 0;
+    for (int k = 0; k < p.n; ++k) {
+        CnnPackJob &q = p.j[k];
+        q.COP = (q.Co + 15) / 16 * 16;
+        q.total = q.taps == 27 ? (int)cnn_direct_size(q.Co, q.Ci) : q.COP * q.Kp;
+        q.block0 = blocks;
+        blocks += (q.total + 255) / 256;
+    }
+    if (use_bf16) hipLaunchKernelGGL(k_pack<bf16>, dim3(blocks), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(k_pack<float>, dim3(blocks), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
 hipError_t cnn_conv_fwd(int use_bf16, const float *in, long long in_bs, int Ci, int S, int taps, const void *wt, int Kp,
-                        int COP, const float *bias, int Co, float *out, long long out_bs, int relu, int B,
+                        int COP, const float *bias, int Co, float *out, long long out_bs, int relu, const float *mask, int B,
                         hipStream_t s) {
-    return use_bf16 ? cnn_conv_fwd_t<bf16>(in, in_bs, Ci, S, taps, wt, Kp, COP, bias, Co, out, out_bs, relu, B, s)
-                : cnn_conv_fwd_t<float>(in, in_bs, Ci, S, taps, wt, Kp, COP, bias, Co, out, out_bs, relu, B, s);
+    return use_bf16 ? cnn_conv_fwd_t<bf16>(in, in_bs, Ci, S, taps, wt, Kp, COP, bias, Co, out, out_bs, relu, mask, B, s)
+                : cnn_conv_fwd_t<float>(in, in_bs, Ci, S, taps, wt, Kp, COP, bias, Co, out, out_bs, relu, mask, B, s);
 }
 
 hipError_t cnn_bias_grad(const float *g, long long g_bs, int B, long long V, int Co, float *part, float *db,
@@ -1331,40 +1372,29 @@ hipError_t cnn_bias_grad(const float *g, long long g_bs, int B, long long V, int
     return hipGetLastError();
 }
 
-hipError_t cnn_pack_weights(int use_bf16, const float *W, int Co, int Ci, int taps, int transpose, int COP, int Kp,
-                            void *wt, hipStream_t s) {
-    long long n = (long long)COP * Kp;
-    unsigned grid = (unsigned)((n + 255) / 256);
-    if (use_bf16) hipLaunchKernelGGL(k_pack_weights<bf16>, dim3(grid), dim3(256), 0, s, W, Co, Ci, taps, transpose, COP, Kp, (bf16 *)wt);
-    else hipLaunchKernelGGL(k_pack_weights<float>, dim3(grid), dim3(256), 0, s, W, Co, Ci, taps, transpose, COP, Kp, (float *)wt);
-    return hipGetLastError();
+// n: parents along an axis
+#define PARENTS_LAUNCH(kernel, ...)                                                                                     \
+    do {                                                                                                                \
+        const long long per = (long long)n * n * n;                                                                     \
+        if (n % 2 == 0) hipLaunchKernelGGL(kernel<2>, dim3((unsigned)((per / 2 + 255) / 256 * C * B)), dim3(256), 0, s, __VA_ARGS__); \
+        else hipLaunchKernelGGL(kernel<1>, dim3((unsigned)((per + 255) / 256 * C * B)), dim3(256), 0, s, __VA_ARGS__);   \
+        return hipGetLastError();                                                                                       \
+    } while (0)
+hipError_t cnn_pool_fwd(const float *in, long long in_bs, float *out, long long out_bs, int C, int n, int B, hipStream_t s) {
+    PARENTS_LAUNCH(k_pool_fwd, in, in_bs, out, out_bs, C, n);
 }
-
-hipError_t cnn_relu_bwd(float *g, long long g_bs, const float *y, long long y_bs, long long per, int B, hipStream_t s) {
-    hipLaunchKernelGGL(k_relu_bwd, dim3((unsigned)((per * B + 255) / 256)), dim3(256), 0, s, g, g_bs, y, y_bs, per, B);
-    return hipGetLastError();
+hipError_t cnn_pool_bwd(const float *gout, long long gout_bs, float *gin, const float *y, long long gin_bs, int C, int n, int B,
+                        hipStream_t s) {
+    PARENTS_LAUNCH(k_pool_bwd, gout, gout_bs, gin, y, gin_bs, C, n);
 }
-hipError_t cnn_pool_fwd(const float *in, long long in_bs, float *out, long long out_bs, int C, int S, int B, hipStream_t s) {
-    long long n = (long long)C * (S / 2) * (S / 2) * (S / 2) * B;
-    hipLaunchKernelGGL(k_pool_fwd, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, in, in_bs, out, out_bs, C, S, B);
-    return hipGetLastError();
+hipError_t cnn_up_fwd(const float *in, long long in_bs, float *out, long long out_bs, int C, int n, int B, hipStream_t s) {
+    PARENTS_LAUNCH(k_up_fwd, in, in_bs, out, out_bs, C, n);
 }
-hipError_t cnn_pool_bwd(const float *gout, long long gout_bs, float *gin, long long gin_bs, int C, int S, int B,
-                        int accumulate, hipStream_t s) {
-    long long n = (long long)C * S * S * S * B;
-    hipLaunchKernelGGL(k_pool_bwd, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, gout, gout_bs, gin, gin_bs, C, S, B, accumulate);
-    return hipGetLastError();
+hipError_t cnn_up_bwd(const float *gout, long long gout_bs, float *gin, const float *y, long long gin_bs, int C, int n, int B,
+                      hipStream_t s) {
+    PARENTS_LAUNCH(k_up_bwd, gout, gout_bs, gin, y, gin_bs, C, n);
 }
-hipError_t cnn_up_fwd(const float *in, long long in_bs, float *out, long long out_bs, int C, int S, int B, hipStream_t s) {
-    long long n = (long long)C * 8 * S * S * S * B;
-    hipLaunchKernelGGL(k_up_fwd, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, in, in_bs, out, out_bs, C, S, B);
-    return hipGetLastError();
-}
-hipError_t cnn_up_bwd(const float *gout, long long gout_bs, float *gin, long long gin_bs, int C, int S, int B, hipStream_t s) {
-    long long n = (long long)C * S * S * S * B;
-    hipLaunchKernelGGL(k_up_bwd, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, gout, gout_bs, gin, gin_bs, C, S, B);
-    return hipGetLastError();
-}
+#undef PARENTS_LAUNCH
 hipError_t cnn_mse(const float *y, const float *t, long long n, float *g, double *part, double *loss, hipStream_t s) {
     unsigned nb = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, y, t, n, g, part);
