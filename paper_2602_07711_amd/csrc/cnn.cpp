@@ -12,8 +12,8 @@
 #include "helm_internal.h"
 
 namespace helm {
-hipError_t cnn_conv_fwd(int bf16, const float *in, long long in_bs, int Ci, int S, int taps, const void *wt, int Kp,
-                        int COP, const float *bias, int Co, float *out, long long out_bs, int relu, const float *mask, int B, hipStream_t s);
+hipError_t cnn_head(int use_bf16, const float *in, long long in_bs, int Ci, int V, const void *wt, int Kp, const float *bias,
+                    int Co, float *out, long long out_bs, const float *mask, int B, hipStream_t s);
 hipError_t cnn_bias_grad(const float *g, long long g_bs, int B, long long V, int Co, float *part, float *db,
                          hipStream_t s);
 hipError_t cnn_pack(int use_bf16, CnnPackJobs &p, hipStream_t s);
@@ -132,8 +132,8 @@ helm_status conv_fwd(helm_cnn &n, int l, View in, View out, int B) {
         NTRY(cnn_conv_direct(n.bf16, in.p, in.bs, ci, S_of(n, LAYERS[l][4]), n.wt[l], n.COP[l], n.params + n.boff[l],
                              co, out.p, out.bs, relu, nullptr, B, n.stream));
     else
-        NTRY(cnn_conv_fwd(n.bf16, in.p, in.bs, ci, S_of(n, LAYERS[l][4]), taps, n.wt[l], n.Kp[l], n.COP[l],
-                          n.params + n.boff[l], co, out.p, out.bs, relu, nullptr, B, n.stream));
+        NTRY(cnn_head(n.bf16, in.p, in.bs, ci, (int)V_of(n, LAYERS[l][4]), n.wt[l], n.Kp[l], n.params + n.boff[l], co, out.p,
+                      out.bs, nullptr, B, n.stream));
     return HELM_OK;
 }
 
@@ -154,8 +154,8 @@ helm_status conv_bwd(helm_cnn &n, int l, View in, View g, View *gin, const float
         NTRY(cnn_conv_direct(n.bf16, g.p, g.bs, co, S, n.wtT[l], n.COPt[l], nullptr, ci, gin->p, gin->bs, 0, mask, B,
                              n.stream));
     else if (gin)
-        NTRY(cnn_conv_fwd(n.bf16, g.p, g.bs, co, S, taps, n.wtT[l], n.Kpt[l], n.COPt[l], nullptr, ci, gin->p, gin->bs,
-                          0, mask, B, n.stream));
+        NTRY(cnn_head(n.bf16, g.p, g.bs, co, (int)V_of(n, lev), n.wtT[l], n.Kpt[l], nullptr, ci, gin->p, gin->bs, mask, B,
+                      n.stream));
     return HELM_OK;
 }
 
