@@ -148,6 +148,28 @@ __device__ double2 reduce_part(const double2 *part, int nblk, int nout, int t) {
     return make_double2(sr[0], si[0]);
 }
 
+// the same for all outputs t < nout of a step at once, into shared out[]: a wave takes every (waves)-th output, its lanes
+// the blocks, eight loads in flight, no barrier between outputs
+__device__ __forceinline__ void reduce_all(const double2 *__restrict__ part, int nblk, int nout, double2 *out) {
+    const int lane = threadIdx.x & 63;
+    for (int t = threadIdx.x >> 6; t < nout; t += blockDim.x >> 6) {
+        double re = 0.0, im = 0.0;
+        for (int b0 = lane; b0 < nblk; b0 += 8 * 64) {
+            double2 v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = part[(long long)min(b0 + k * 64, nblk - 1) * nout + t];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                re += b0 + k * 64 < nblk ? v[k].x : 0.0;
+                im += b0 + k * 64 < nblk ? v[k].y : 0.0;
+            }
+        }
+        re = wave_sum(re);
+        im = wave_sum(im);
+        if (lane == 0) out[t] = make_double2(re, im);
+    }
+}
+
 __device__ __forceinline__ double2 cmulb(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
@@ -202,120 +224,133 @@ __global__ __launch_bounds__(256) void k_b_restart(const BProb *__restrict__ P, 
     st[p] = s;
 }
 
+// What a step's block shares: the inner products, the earlier rotations, and what to write to coef: nothing (0), the inner
+// products (1) or those over `scale` (2)
+constexpr int ARN_THREADS = 1024;
+struct StepShared {
+    double2 hv[130], h2[130], sn[130];
+    double cs[130];
+    double scale;
+    int write;
+};
+
 // Column j of H from the orthogonalisation coefficients hv[0..j] and eta (shifted Arnoldi: -h + e_j, eta), the
-// previous rotations, the new rotation, g, the convergence test, and the coefficients of the update
-// v_{j+1} = -(y - V h)/eta. One thread.
-__device__ void arnoldi_column(BState &s, BArrays a, int p, int m, const BParams *__restrict__ prm, int j,
-                               const double2 *hv, double eta) {
+// previous rotations, the new rotation, g, the convergence test, and (for the caller to write) the coefficients of the
+// update v_{j+1} = -(y - V h)/eta. One thread; it reads shared memory only (with H and the rotations read from global
+// memory, a step of 128^3 problems took 22 us, now 7 us).
+__device__ void arnoldi_column(BState &s, const StepShared &sh, BArrays a, int p, int m, const BParams *__restrict__ prm,
+                               int j, double eta) {
     double2 *H = a.H + (long long)p * (m + 1) * m;
     double *cs = a.cs + (long long)p * m;
     double2 *sn = a.sn + (long long)p * m;
     double2 *g = a.g + (long long)p * (m + 1);
-    double2 *coef = a.coef + (long long)p * (m + 1);
-    for (int i = 0; i <= j; ++i) H[(long long)i * m + j] = make_double2(-hv[i].x, -hv[i].y);
-    H[(long long)j * m + j].x += 1.0;
+    const double2 gj = g[j];
+    auto entry = [&](int i) { return make_double2(-sh.hv[i].x + (i == j ? 1.0 : 0.0), -sh.hv[i].y); };
+    double2 av = entry(0);                                     // the entry that the next rotation turns
     for (int i = 0; i < j; ++i) {
-        double2 x0 = H[(long long)i * m + j], x1 = H[(long long)(i + 1) * m + j];
-        double2 t0 = cmulb(sn[i], x1);
-        H[(long long)i * m + j] = make_double2(cs[i] * x0.x + t0.x, cs[i] * x0.y + t0.y);
-        double2 t1 = cmulb(cconj(sn[i]), x0);
-        H[(long long)(i + 1) * m + j] = make_double2(-t1.x + cs[i] * x1.x, -t1.y + cs[i] * x1.y);
+        const double2 x0 = av, x1 = entry(i + 1);
+        const double2 t0 = cmulb(sh.sn[i], x1);
+        H[(long long)i * m + j] = make_double2(sh.cs[i] * x0.x + t0.x, sh.cs[i] * x0.y + t0.y);
+        const double2 t1 = cmulb(cconj(sh.sn[i]), x0);
+        av = make_double2(-t1.x + sh.cs[i] * x1.x, -t1.y + sh.cs[i] * x1.y);
     }
-    {
-        double2 av = H[(long long)j * m + j];
-        double aa = cabs2(av);
-        if (eta == 0.0) { cs[j] = 1.0; sn[j] = make_double2(0.0, 0.0); }
-        else if (aa == 0.0) { cs[j] = 0.0; sn[j] = make_double2(1.0, 0.0); H[(long long)j * m + j] = make_double2(eta, 0.0); }
-        else {
-            double tt = hypot(aa, eta);
-            double2 ph = make_double2(av.x / aa, av.y / aa);
-            cs[j] = aa / tt;
-            sn[j] = make_double2(ph.x * eta / tt, ph.y * eta / tt);
-            H[(long long)j * m + j] = make_double2(ph.x * tt, ph.y * tt);
-        }
-        double2 gj = g[j];
-        double2 t1 = cmulb(cconj(sn[j]), gj);
-        g[j + 1] = make_double2(-t1.x, -t1.y);
-        g[j] = make_double2(cs[j] * gj.x, cs[j] * gj.y);
+    const double aa = cabs2(av);
+    double c = 1.0;
+    double2 sj = make_double2(0.0, 0.0), hjj = av;
+    if (eta == 0.0) {}
+    else if (aa == 0.0) { c = 0.0; sj = make_double2(1.0, 0.0); hjj = make_double2(eta, 0.0); }
+    else {
+        const double tt = hypot(aa, eta);
+        const double2 ph = make_double2(av.x / aa, av.y / aa);
+        c = aa / tt;
+        sj = make_double2(ph.x * eta / tt, ph.y * eta / tt);
+        hjj = make_double2(ph.x * tt, ph.y * tt);
     }
+    cs[j] = c;
+    sn[j] = sj;
+    H[(long long)j * m + j] = hjj;
+    const double2 t1 = cmulb(cconj(sj), gj), gn = make_double2(-t1.x, -t1.y);
+    g[j + 1] = gn;
+    g[j] = make_double2(c * gj.x, c * gj.y);
     s.its += 1;
     s.k = j + 1;
-    const double res = cabs2(g[j + 1]);
+    const double res = cabs2(gn);
     s.relres_est = res / s.bnorm;
-    if (eta == 0.0 || res <= prm->rtol * s.bnorm || s.its >= prm->maxit || j + 1 == m || !isfinite(res)) {
-        s.active = 0;
-    } else {
-        for (int i = 0; i <= j; ++i) coef[i] = make_double2(hv[i].x / eta, hv[i].y / eta);
-        s.alpha = make_double2(-1.0 / eta, 0.0);
-    }
+    if (eta == 0.0 || res <= prm->rtol * s.bnorm || s.its >= prm->maxit || j + 1 == m || !isfinite(res)) s.active = 0;
+    else s.alpha = make_double2(-1.0 / eta, 0.0);
 }
 
 // one block per problem: reduce V^H y and ||y||^2 and finish the step (arnoldi_column). With severe cancellation
 // (||y - V h||^2 = ||y||^2 - sum |h_i|^2 <= reorth ||y||^2, reorth = cgs_reorth()) that norm is not accurate enough: the step takes a
 // second Gram-Schmidt pass instead. The update then leaves u = -(y - V h) unscaled (coefficients h, alpha = -1), and
 // k_b_arnoldi2 finishes the step from the inner products of u.
-__global__ __launch_bounds__(256) void k_b_arnoldi(const BProb *__restrict__ P, BState *__restrict__ st, BArrays a,
-                                                   const BParams *__restrict__ prm, int j) {
-    __shared__ double2 hv[130];
-    const int p = blockIdx.x;
+__global__ __launch_bounds__(ARN_THREADS) void k_b_arnoldi(const BProb *__restrict__ P, BState *__restrict__ st, BArrays a,
+                                                           const BParams *__restrict__ prm, int j) {
+    __shared__ StepShared sh;
+    const int p = blockIdx.x, tid = threadIdx.x;
     if (!st[p].active) return;
     const BProb &q = P[p];
     const int m = prm->m;
     const int nv = j + 1;
-    for (int t = 0; t <= nv; ++t) {
-        double2 r = reduce_part(q.part, q.nblk_dots, nv + 1, t);
-        if (threadIdx.x == 0) hv[t] = r;
+    double2 *coef = a.coef + (long long)p * (m + 1);
+    if (tid < j) { sh.cs[tid] = a.cs[(long long)p * m + tid]; sh.sn[tid] = a.sn[(long long)p * m + tid]; }
+    reduce_all(q.part, q.nblk_dots, nv + 1, sh.hv);
+    __syncthreads();
+    if (tid == 0) {
+        BState s = st[p];
+        double hh = 0.0;
+        for (int i = 0; i <= j; ++i) hh += sh.hv[i].x * sh.hv[i].x + sh.hv[i].y * sh.hv[i].y;
+        const double ww = sh.hv[nv].x;
+        const double eta2 = ww - hh;
+        s.reo = 0;
+        if (!(eta2 > prm->reorth * ww) && isfinite(eta2)) {
+            s.cancel += 1;
+            s.reo = 1;
+            sh.write = 1;
+            s.alpha = make_double2(-1.0, 0.0);
+        } else {
+            sh.scale = eta2 > 0.0 ? sqrt(eta2) : 0.0;
+            arnoldi_column(s, sh, a, p, m, prm, j, sh.scale);
+            sh.write = s.active ? 2 : 0;
+        }
+        st[p] = s;
     }
-    if (threadIdx.x != 0) return;
-    BState s = st[p];
-    double hh = 0.0;
-    for (int i = 0; i <= j; ++i) hh += hv[i].x * hv[i].x + hv[i].y * hv[i].y;
-    const double ww = hv[nv].x;
-    const double eta2 = ww - hh;
-    s.reo = 0;
-    if (!(eta2 > prm->reorth * ww) && isfinite(eta2)) {
-        s.cancel += 1;
-        s.reo = 1;
-        double2 *coef = a.coef + (long long)p * (m + 1);
-        for (int i = 0; i <= j; ++i) coef[i] = hv[i];
-        s.alpha = make_double2(-1.0, 0.0);
-    } else {
-        arnoldi_column(s, a, p, m, prm, j, hv, eta2 > 0.0 ? sqrt(eta2) : 0.0);
-    }
-    st[p] = s;
+    __syncthreads();
+    if (tid > j) return;
+    if (sh.write == 1) coef[tid] = sh.hv[tid];
+    else if (sh.write == 2) coef[tid] = make_double2(sh.hv[tid].x / sh.scale, sh.hv[tid].y / sh.scale);
 }
 
 // the second pass of a cancelled step: h2 = V^H u and ||u||^2 (u = -(y - V h) in V_{j+1}); then
 // v_{j+1} = (u - V h2)/eta' = -(y - V (h - h2))/eta' with eta'^2 = ||u||^2 - sum |h2_i|^2
-__global__ __launch_bounds__(256) void k_b_arnoldi2(const BProb *__restrict__ P, BState *__restrict__ st, BArrays a,
-                                                    const BParams *__restrict__ prm, int j) {
-    __shared__ double2 h2[130];
-    __shared__ double2 hv[130];
-    const int p = blockIdx.x;
+__global__ __launch_bounds__(ARN_THREADS) void k_b_arnoldi2(const BProb *__restrict__ P, BState *__restrict__ st, BArrays a,
+                                                            const BParams *__restrict__ prm, int j) {
+    __shared__ StepShared sh;
+    const int p = blockIdx.x, tid = threadIdx.x;
     if (!st[p].active || !st[p].reo) return;
     const BProb &q = P[p];
     const int m = prm->m;
     const int nv = j + 1;
-    for (int t = 0; t <= nv; ++t) {
-        double2 r = reduce_part(q.part, q.nblk_dots, nv + 1, t);
-        if (threadIdx.x == 0) h2[t] = r;
-    }
-    if (threadIdx.x != 0) return;
-    BState s = st[p];
     double2 *coef = a.coef + (long long)p * (m + 1);
-    double hh = 0.0;
-    for (int i = 0; i <= j; ++i) {
-        hv[i] = make_double2(coef[i].x - h2[i].x, coef[i].y - h2[i].y);
-        hh += h2[i].x * h2[i].x + h2[i].y * h2[i].y;
+    if (tid < j) { sh.cs[tid] = a.cs[(long long)p * m + tid]; sh.sn[tid] = a.sn[(long long)p * m + tid]; }
+    reduce_all(q.part, q.nblk_dots, nv + 1, sh.h2);
+    __syncthreads();
+    if (tid <= j) sh.hv[tid] = make_double2(coef[tid].x - sh.h2[tid].x, coef[tid].y - sh.h2[tid].y);
+    __syncthreads();
+    if (tid == 0) {
+        BState s = st[p];
+        double hh = 0.0;
+        for (int i = 0; i <= j; ++i) hh += sh.h2[i].x * sh.h2[i].x + sh.h2[i].y * sh.h2[i].y;
+        const double e2 = sh.h2[nv].x - hh;
+        sh.scale = e2 > 0.0 ? sqrt(e2) : 0.0;
+        arnoldi_column(s, sh, a, p, m, prm, j, sh.scale);
+        sh.write = s.active ? 2 : 0;
+        if (s.active) s.alpha = make_double2(1.0 / sh.scale, 0.0);
+        st[p] = s;
     }
-    const double e2 = h2[nv].x - hh;
-    const double eta = e2 > 0.0 ? sqrt(e2) : 0.0;
-    arnoldi_column(s, a, p, m, prm, j, hv, eta);
-    if (s.active) {                  // the correction of u (k_b_lincomb kind 3)
-        for (int i = 0; i <= j; ++i) coef[i] = make_double2(-h2[i].x / eta, -h2[i].y / eta);
-        s.alpha = make_double2(1.0 / eta, 0.0);
-    }
-    st[p] = s;
+    __syncthreads();
+    // the correction of u (k_b_lincomb kind 3)
+    if (tid <= j && sh.write == 2) coef[tid] = make_double2(-sh.h2[tid].x / sh.scale, -sh.h2[tid].y / sh.scale);
 }
 
 // one thread per problem: y = R^{-1} g (k x k, upper triangular) into coef, for problems that iterated
@@ -504,11 +539,11 @@ hipError_t bl_cycle(const BLaunch &L, hipStream_t s) {
         if (e != hipSuccess) return e;
         if ((e = matvec_step(L, s, 1, j)) != hipSuccess) return e;
         hipLaunchKernelGGL(k_b_dots, dim3(L.tot_dot), dim3(256), 0, s, L.P, L.st, L.off.dot, L.np, 2, j);
-        hipLaunchKernelGGL(k_b_arnoldi, dim3(L.np), dim3(256), 0, s, L.P, L.st, L.a, L.prm, j);
+        hipLaunchKernelGGL(k_b_arnoldi, dim3(L.np), dim3(ARN_THREADS), 0, s, L.P, L.st, L.a, L.prm, j);
         if ((e = lincomb_step(L, s, 1, j)) != hipSuccess) return e;
         // second Gram-Schmidt pass of the steps that cancelled (every block of the other problems returns at once)
         hipLaunchKernelGGL(k_b_dots, dim3(L.tot_dot), dim3(256), 0, s, L.P, L.st, L.off.dot, L.np, 3, j);
-        hipLaunchKernelGGL(k_b_arnoldi2, dim3(L.np), dim3(256), 0, s, L.P, L.st, L.a, L.prm, j);
+        hipLaunchKernelGGL(k_b_arnoldi2, dim3(L.np), dim3(ARN_THREADS), 0, s, L.P, L.st, L.a, L.prm, j);
         if ((e = lincomb_step(L, s, 3, j)) != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_b_trisolve, dim3((L.np + 63) / 64), dim3(64), 0, s, L.st, L.a, L.prm, L.np);

@@ -31,3 +31,27 @@ def test_inner_products_and_update(shape):
     true = np.linalg.norm(r) / np.linalg.norm(F)
     assert abs(true - info["relres_est"]) <= 1e-11
     h.helm_destroy(ctx)
+
+
+@pytest.mark.parametrize("reorth", [None, "0.9"], ids=["one_pass", "two_passes"])
+def test_batch_steps_match_single_solves(reorth, monkeypatch):
+    """Batched steps whose inner products come from more blocks than a wave reads in one round (537) and are more in
+    number than the reducing block's waves (16), next to a problem of one block; the same with a second Gram-Schmidt pass
+    at nearly every step. Both solves stop at 1e-10, so their solutions agree to that times the operator's condition."""
+    if reorth:
+        monkeypatch.setenv("HELM_CGS_REORTH", reorth)
+    h = H()
+    ctxs, Fs = [], []
+    for shape, seed in (((130, 130, 130), 1), ((9, 11, 10), 2)):
+        h3 = _h3(shape, 6)
+        k0 = 0.5 / max(h3)
+        ctxs.append(h.helm_setup(dev(medium(shape, h3, k0, seed)), h3, 6, "abc", k0))
+        Fs.append(dev(cvec(int(np.prod(shape)), seed)))
+    xs, infos = h.helm_batch_solve(h.helm_batch_create(ctxs, m=40, prec_fp32=False), Fs, rtol=1e-10)
+    assert infos[0]["iters"] > 16
+    for ctx, F, x, info in zip(ctxs, Fs, xs, infos):
+        x1, single = h.helm_gmres_solve(ctx, F, m=40, rtol=1e-10, flexible=True)
+        assert info["converged"] and abs(info["iters"] - single["iters"]) <= 1
+        assert (info["cancellations"] > 0) == bool(reorth)
+        a, b = host(x), host(x1)
+        assert np.linalg.norm(a - b) <= 1e-8 * np.linalg.norm(b)
