@@ -54,20 +54,23 @@ void dfree(Ctx &c, void *p) {
 // at 255^3 the z-solve was 6 % slower with its vectors and pivot table in one allocation.
 struct Slab {
     size_t alone = 16u << 20;
-    struct Slot { void **p; size_t bytes, off; };
+    struct Slot { void **p; size_t bytes, off; const void *src; };
     std::vector<Slot> up, work;
     std::vector<char> host;
     static size_t aligned(size_t off, size_t bytes) {
         const size_t a = bytes >= (1u << 20) ? 2u << 20 : 256;
         return (off + a - 1) / a * a;
     }
-    template <typename T> void put(T **p, const void *data, size_t count) {
+    // the contents' place on the host, to be written before the next call
+    template <typename T> T *put(T **p, size_t count) {
         const size_t bytes = count * sizeof(T), off = aligned(host.size(), bytes);
-        up.push_back({(void **)p, bytes, off});
+        up.push_back({(void **)p, bytes, off, nullptr});
         host.resize(off + bytes);
-        std::memcpy(host.data() + off, data, bytes);
+        return reinterpret_cast<T *>(host.data() + off);
     }
-    template <typename T> void take(T **p, size_t count) { work.push_back({(void **)p, count * sizeof(T), 0}); }
+    template <typename T> void put(T **p, const void *data, size_t count) { std::memcpy(put(p, count), data, count * sizeof(T)); }
+    // src (may be null): contents that stay where they are until commit copies them, one copy each
+    template <typename T> void take(T **p, size_t count, const void *src = nullptr) { work.push_back({(void **)p, count * sizeof(T), 0, src}); }
     helm_status commit(Ctx &c);
 };
 
@@ -91,6 +94,7 @@ helm_status Slab::commit(Ctx &c) {
     for (const Slot &s : work) {
         char *q = base + s.off;
         if (s.bytes >= alone) ST_TRY(dalloc(c, &q, s.bytes));
+        if (s.src) HIP_TRY(hipMemcpy(q, s.src, s.bytes, hipMemcpyHostToDevice));
         *s.p = q;
     }
     return HELM_OK;
@@ -252,14 +256,13 @@ std::vector<cd> sine_matrix(int n) {
 }
 
 template <typename CT> void put_matrix(Slab &slab, const std::vector<cd> &M, int n, bool transpose, CT **d) {
-    std::vector<CT> hbuf((size_t)n * n);
+    CT *h = slab.put(d, (size_t)n * n);
     for (int r = 0; r < n; ++r)
         for (int k = 0; k < n; ++k) {
             cd v = transpose ? M[(size_t)k * n + r] : M[(size_t)r * n + k];
-            hbuf[(size_t)r * n + k].x = (decltype(hbuf[0].x))v.real();
-            hbuf[(size_t)r * n + k].y = (decltype(hbuf[0].x))v.imag();
+            h[(size_t)r * n + k].x = (decltype(h[0].x))v.real();
+            h[(size_t)r * n + k].y = (decltype(h[0].x))v.imag();
         }
-    slab.put(d, hbuf.data(), hbuf.size());
 }
 
 // The orthonormal sine matrix S (S[j][k] = sqrt(2/(N+1)) sin(pi (j+1)(k+1)/(N+1))) as folded real blocks: S is its
@@ -267,8 +270,7 @@ template <typename CT> void put_matrix(Slab &slab, const std::vector<cd> &M, int
 // S = Q diag(Vs, Va) in that mode order, Vs[i][k'] = sqrt(2) S[i][2k'] and Va[i][k'] = sqrt(2) S[i][2k'+1] (the middle
 // row of an odd axis unscaled), and the inverse blocks the same with S's rows. The modes stay in natural order
 // (FoldDesc moff = 1, mstep = 2).
-EigFold sine_fold(int n) {
-    const std::vector<cd> S = sine_matrix(n);
+EigFold sine_fold(int n, const std::vector<cd> &S) {
     EigFold f;
     f.n = n;
     f.ms = n - n / 2;
@@ -337,8 +339,8 @@ helm_status sine_tf(Ctx &c, int axis, bool fwd, const TD *in, TC *out, const Pff
     return HELM_OK;
 }
 
-template <typename CT> helm_status build_sine_mats(Ctx &c, PfftMats<CT> &m) {
-    std::vector<cd> Sx = sine_matrix(c.nx), Sy = sine_matrix(c.ny);
+template <typename CT>
+helm_status build_sine_mats(Ctx &c, PfftMats<CT> &m, const std::vector<cd> &Sx, const std::vector<cd> &Sy) {
     Slab slab;
     put_matrix(slab, Sx, c.nx, false, &m.Sx);
     put_matrix(slab, Sy, c.ny, false, &m.Sy);
@@ -346,14 +348,19 @@ template <typename CT> helm_status build_sine_mats(Ctx &c, PfftMats<CT> &m) {
 }
 
 template <typename CT> helm_status build_ring_mats(Ctx &c, PfftMats<CT> &m) {
+    // the four matrices as they are; their transposes and FP32 forms are made on the device
     Slab slab;
-    put_matrix(slab, c.hVxi, c.nx, false, &m.Vxi);
-    put_matrix(slab, c.hVx, c.nx, false, &m.Vx);
-    put_matrix(slab, c.hVxi, c.nx, true, &m.VxiT);
-    put_matrix(slab, c.hVx, c.nx, true, &m.VxT);
-    put_matrix(slab, c.hVyi, c.ny, true, &m.VyiT);
-    put_matrix(slab, c.hVy, c.ny, false, &m.Vy);
-    put_matrix(slab, c.hVy, c.ny, true, &m.VyT);
+    const size_t xx = (size_t)c.nx * c.nx, yy = (size_t)c.ny * c.ny;
+    double2 *src[4];
+    slab.take(&src[0], xx, c.hVxi.data());
+    slab.take(&src[1], xx, c.hVx.data());
+    slab.take(&src[2], yy, c.hVyi.data());
+    slab.take(&src[3], yy, c.hVy.data());
+    if (sizeof(CT) == sizeof(float2)) { slab.take(&m.Vxi, xx); slab.take(&m.Vx, xx); slab.take(&m.Vy, yy); }
+    slab.take(&m.VxiT, xx);
+    slab.take(&m.VxT, xx);
+    slab.take(&m.VyiT, yy);
+    slab.take(&m.VyT, yy);
     slab.take(&m.yhat, (size_t)c.n);
     size_t ring = (size_t)c.nz * (2 * c.nx + 2 * c.ny);
     const size_t layers = c.zeta != 1.0 ? 2 : 1;     // the collocated closure reads a second layer per face
@@ -364,7 +371,14 @@ template <typename CT> helm_status build_ring_mats(Ctx &c, PfftMats<CT> &m) {
     slab.take(&m.rsum, (size_t)c.nz * 2 * c.nx);
     slab.take(&m.rbuf, ring);
     slab.take(&m.fvec, ring);
-    return slab.commit(c);
+    ST_TRY(slab.commit(c));
+    if (sizeof(CT) == sizeof(double2)) { m.Vxi = (CT *)src[0]; m.Vx = (CT *)src[1]; m.Vy = (CT *)src[3]; }
+    HIP_TRY(launch_dense_forms(src[0], m.Vxi, m.VxiT, c.nx, c.stream));
+    HIP_TRY(launch_dense_forms(src[1], m.Vx, m.VxT, c.nx, c.stream));
+    HIP_TRY(launch_dense_forms(src[2], (CT *)nullptr, m.VyiT, c.ny, c.stream));
+    HIP_TRY(launch_dense_forms(src[3], m.Vy, m.VyT, c.ny, c.stream));
+    prof_gap(c);
+    return HELM_OK;
 }
 
 // Sine matrices and Dirichlet eigenvalues (shared by PFFT and FFT2); `ring` adds PFFT's face-correction data.
@@ -385,15 +399,20 @@ helm_status ensure_sine(Ctx &c, bool fp32, bool ring) {
         ST_TRY(slab.commit(c));
     }
     PfftPlan &P = *c.pfft;
-    if (!P.m64.Sx) ST_TRY(build_sine_mats(c, P.m64));
+    std::vector<cd> Sx, Sy;          // the sines are most of a first use's host work (1.2 ms for 255 of them squared)
+    if (!P.m64.Sx || !P.m64.fsx.fs || (fp32 && !P.m32.Sx)) {
+        Sx = sine_matrix(c.nx);
+        Sy = c.ny == c.nx ? Sx : sine_matrix(c.ny);
+    }
+    if (!P.m64.Sx) ST_TRY(build_sine_mats(c, P.m64, Sx, Sy));
     if (!P.m64.fsx.fs) {
-        const EigFold fx = sine_fold(c.nx), fy = sine_fold(c.ny);
+        const EigFold fx = sine_fold(c.nx, Sx), fy = sine_fold(c.ny, Sy);
         Slab slab;
         ST_TRY(upload_folds(c, slab, {{&fx, true, &P.m64.fsx, &P.m32.fsx}, {&fy, false, &P.m64.fsy, &P.m32.fsy}}));
     }
     if (ring && !P.m64.ringT) ST_TRY(build_ring_mats(c, P.m64));
     if (fp32) {
-        if (!P.m32.Sx) ST_TRY(build_sine_mats(c, P.m32));
+        if (!P.m32.Sx) ST_TRY(build_sine_mats(c, P.m32, Sx, Sy));
         if (ring && !P.m32.ringT) ST_TRY(build_ring_mats(c, P.m32));
     }
     return HELM_OK;
@@ -418,7 +437,7 @@ helm_status ensure_fftk(Ctx &c, bool fp32) {
         }
     }
     if (!P.m64.fsz.fs) {
-        const EigFold fz = sine_fold(c.nz);
+        const EigFold fz = sine_fold(c.nz, sine_matrix(c.nz));
         Slab slab;
         ST_TRY(upload_folds(c, slab, {{&fz, false, &P.m64.fsz, &P.m32.fsz}}));
     }

@@ -98,6 +98,9 @@ hipError_t launch_fold_z32_in64(int mode, const FoldDesc &f, const double2 *D, c
 struct FoldBlock { double2 *src, *d64; float2 *d32; int nb, P; };
 struct FoldBlocks { FoldBlock b[8]; int n; };
 hipError_t launch_fold_expand(const FoldBlocks &f, hipStream_t s);
+// an n x n matrix in its transposed and (FP32, unless null) plain form
+hipError_t launch_dense_forms(const double2 *src, double2 *plain, double2 *transposed, int n, hipStream_t s);
+hipError_t launch_dense_forms(const double2 *src, float2 *plain, float2 *transposed, int n, hipStream_t s);
 hipError_t launch_fold_z32_out64(int mode, const FoldDesc &f, const float2 *D, const float2 *Ms, const float2 *Ma,
                                  double2 *C, hipStream_t s, int cfg, bool real = false);
 // real = true: the blocks are real (their imaginary parts are ignored), two real MFMA products per complex MAC

@@ -152,6 +152,26 @@ __global__ __launch_bounds__(256) void k_fold_expand(FoldBlocks f) {
         q.d32[t] = make_float2((float)v.x, (float)v.y);
     }
 }
+// (once per context: 2 MB at 255; the host's transposing loops took 0.25 ms each)
+template <typename CT>
+__global__ __launch_bounds__(256) void k_dense_forms(const double2 *__restrict__ src, CT *__restrict__ plain, CT *__restrict__ transposed, int n) {
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < n * n; t += gridDim.x * 256) {
+        const int r = t / n, k = t - r * n;
+        CT v;
+        v.x = (decltype(v.x))src[t].x;
+        v.y = (decltype(v.y))src[t].y;
+        if (plain) plain[t] = v;
+        transposed[(long long)k * n + r] = v;
+    }
+}
+hipError_t launch_dense_forms(const double2 *src, double2 *, double2 *transposed, int n, hipStream_t s) {
+    hipLaunchKernelGGL(k_dense_forms<double2>, dim3((n * n + 255) / 256), dim3(256), 0, s, src, (double2 *)nullptr, transposed, n);
+    return hipGetLastError();
+}
+hipError_t launch_dense_forms(const double2 *src, float2 *plain, float2 *transposed, int n, hipStream_t s) {
+    hipLaunchKernelGGL(k_dense_forms<float2>, dim3((n * n + 255) / 256), dim3(256), 0, s, src, plain, transposed, n);
+    return hipGetLastError();
+}
 hipError_t launch_fold_expand(const FoldBlocks &f, hipStream_t s) {
     hipLaunchKernelGGL(k_fold_expand, dim3(64, f.n), dim3(256), 0, s, f);
     return hipGetLastError();
