@@ -87,16 +87,28 @@ helm_status Slab::commit(Ctx &c) {
         s.off = aligned(end, s.bytes);
         end = s.off + s.bytes;
     }
+    // all or nothing: a caller takes a set pointer for the whole set
+    const size_t before = c.allocs.size();
+    std::vector<char *> at(work.size());
     char *base = nullptr;
-    if (end) ST_TRY(dalloc(c, &base, end));
-    if (!host.empty()) HIP_TRY(hipMemcpy(base, host.data(), host.size(), hipMemcpyHostToDevice));
-    for (const Slot &s : up) *s.p = base + s.off;
-    for (const Slot &s : work) {
-        char *q = base + s.off;
-        if (s.bytes >= alone) ST_TRY(dalloc(c, &q, s.bytes));
-        if (s.src) HIP_TRY(hipMemcpy(q, s.src, s.bytes, hipMemcpyHostToDevice));
-        *s.p = q;
+    auto fill = [&]() -> helm_status {
+        if (end) ST_TRY(dalloc(c, &base, end));
+        if (!host.empty()) HIP_TRY(hipMemcpy(base, host.data(), host.size(), hipMemcpyHostToDevice));
+        for (size_t i = 0; i < work.size(); ++i) {
+            const Slot &s = work[i];
+            if (s.bytes >= alone) ST_TRY(dalloc(c, &at[i], s.bytes));
+            else at[i] = base + s.off;
+            if (s.src) HIP_TRY(hipMemcpy(at[i], s.src, s.bytes, hipMemcpyHostToDevice));
+        }
+        return HELM_OK;
+    };
+    const helm_status st = fill();
+    if (st != HELM_OK) {
+        while (c.allocs.size() > before) dfree(c, c.allocs.back());
+        return st;
     }
+    for (const Slot &s : up) *s.p = base + s.off;
+    for (size_t i = 0; i < work.size(); ++i) *work[i].p = at[i];
     return HELM_OK;
 }
 
