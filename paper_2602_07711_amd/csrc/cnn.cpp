@@ -289,8 +289,8 @@ helm_status helm_cnn_create(helm_cnn **out, int size, int max_batch, int bf16, u
     long long pe = 0;
     for (int l = 0; l < NL; ++l) pe = std::max(pe, 129LL * pad16(LAYERS[l][1]) * pad64(LAYERS[l][0] * LAYERS[l][2]));
     n->part_elems = pe;
-    // bias partials: one value per output channel (at most 64) and tile group (at most 512)
-    if (nalloc(*n, &n->part, pe) || nalloc(*n, &n->bias_part, 64 * 512)) return fail(HELM_ENOMEM, "partials");
+    // bias partials: 64 slices of the voxels for each of at most 64 output channels
+    if (nalloc(*n, &n->part, pe) || nalloc(*n, &n->bias_part, 64 * 64)) return fail(HELM_ENOMEM, "partials");
     long long mp = ((long long)2 * V_of(*n, 0) * max_batch + 255) / 256;
     if (nalloc(*n, &n->mse_part, mp) || nalloc(*n, &n->loss_dev, 1)) return fail(HELM_ENOMEM, "loss");
     // He-uniform initial weights (fan-in), zero biases, from a 64-bit LCG seeded by `seed`

@@ -114,16 +114,16 @@ __global__ __launch_bounds__(256) void k_head(const float *__restrict__ in, long
     }
 }
 
-// s + p[i0] + p[i0 + step] + ... (below n) in that order, eight loads in flight
-template <typename T> __device__ __forceinline__ T sum_strided(const T *__restrict__ p, long long i0, long long n, long long step) {
+// s + p[i0] + p[i0 + step] + ... (below n) in that order, K loads in flight
+template <int K = 8, typename T> __device__ __forceinline__ T sum_strided(const T *__restrict__ p, long long i0, long long n, long long step) {
     T s = 0;
     long long i = i0;
-    for (; i + 7 * step < n; i += 8 * step) {
-        T v[8];
+    for (; i + (K - 1) * step < n; i += K * step) {
+        T v[K];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = p[i + k * step];
+        for (int k = 0; k < K; ++k) v[k] = p[i + k * step];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) s += v[k];
+        for (int k = 0; k < K; ++k) s += v[k];
     }
     for (; i < n; i += step) s += p[i];
     return s;
@@ -828,278 +828,194 @@ template <typename T> __global__ __launch_bounds__(256) void k_pack(CnnPackJobs 
     reinterpret_cast<T *>(q.wt)[e] = MT<T>::cvt(v);
 }
 
-// Weight and bias gradient of a 27-tap layer, dW[o][i][tap] = sum_{b,v} g[b][o][v] in[b][i][v + off(tap)] and
-// db[o] = sum_{b,v} g[b][o][v]. Per tap this is a product with M = output channels, N = 16 input channels and
-// K = voxels. A workgroup (input-channel chunk ch, tile group tg) loops over consecutive TX x 4 x TZ tiles of all samples
-// and stages g and the input tile with its halo channel-first in LDS, so that a lane's four consecutive voxels are one
-// 8-byte read. A wave owns one block of 16 output rows and all 27 taps (4 / FR waves share the K rows of such a
-// block): the operands of the three taps of one (dz, dy) come from one 16-byte window of the input row, shifted in
-// registers, and the windows of six rows serve four output rows: 22 LDS reads for 108 products.
-// Bound: bringing g and the input to the CUs. The tiles take whole rows (TX = 64, 32 or 16 by the volume's width): with
-// rows of 16 voxels every 128-byte line was fetched for a part of it, and the 48 -> 16 layer at 4 x 64^3 read 1.7 GB
-// for its 268 MB.
-// At 4 x 64^3 in BF16 (the launch that sums the parts included): 48 -> 16 channels 232 us (before: one 8 x 8 x 4 tile at
-// a time with every load waiting for its own result, 4-byte loads and a scalar reduction, 720 us), 16 -> 16 at 84 us
-// (175 us), 96 -> 32 at 32^3 101 us (250 us), all layers of a training step 0.70 ms (1.95 ms).
-// Partial sums per tile group, part[tg][ch][tap][COP][16] and bpart[tg][o], are added in order by k_wgrad_sum.
-constexpr int WY = 4, WHY = WY + 2;                           // tile height, rows with halo
-template <typename T, int TX> struct WgTile {
-    static constexpr int TZ = (MT<T>::KL == 4 && TX == 64 ? 128 : 64) / TX, HZ = TZ + 2;   // 256 voxels, 512 in the widest
-    static constexpr int ROW = TX + 4;                        // stored row: halo at 1 and TX + 2, interior from 2
-    static constexpr int XCH = HZ * WHY * ROW + 8;            // channel strides: 4 mod 8 banks, so that the 16 channels
-    static constexpr int GCH = TX * WY * TZ + 8;              // of a quarter wave's reads share no bank
+// Weight gradient of a 27-tap layer, dW[o][i][tap] = sum_{b,v} g[b][o][v] in[b][i][v + off(tap)]. Per tap this is a
+// product with M = output channels, N = 16 input channels and K = voxels. A workgroup (input-channel chunk ch, tile group
+// tg) takes the 8 x 8 x 4 tiles tg, tg + G, ... of all samples and stages g and the input tile with its halo channel-first
+// in LDS; a wave owns one block of 16 output rows and the nine taps of one dz, and its operands of the three dx of a dy
+// come from one window of the input row: 22 LDS reads for 36 products.
+// Every sum is made in the order that a training run has always had: a group's products tile by tile, two rows of eight
+// voxels at a time (BF16: one product of 16; FP32: four products of four, half a row each), the groups j, j + 4, ... in
+// four chains, and these one after another. Adam divides by the gradient's own size, so that an order which changes
+// values near zero in their last bit changes the next step's gradients by 1e-3: the order is part of the result
+// (tests/golden/cnn_training.npz).
+// Bound: bringing g and the input to the CUs, and the latency of a tile's loads, which the other workgroups of a CU hide
+// (five of them with 16 output channels, two with 64): neighbouring tiles run on one XCD, so that a 128-byte line comes
+// from its L2 for all of its four tiles. At 4 x 64^3 in BF16, bias and final sum included: 48 -> 16 channels 220 us
+// (whole-row tiles, with the sums in an order of their own, 232 us; four waves sharing the 27 taps of one tile, its
+// neighbours on other XCDs, 720 us), 16 -> 16 at 92 us, 96 -> 32 at 32^3 97 us, all layers of a training step 0.69 ms.
+constexpr int GX = 8, GY = 8, GZ = 4;                         // a tile
+constexpr int GHY = GY + 2, GROWS = GHY * (GZ + 2), GROW = GX + 4;   // stored rows: halo at 1 and GX + 2, interior from 2
+template <typename T> struct WgTile {
+    // channel strides of 4 mod 8 (BF16) or 4 mod 16 (FP32) words: the 16 channels of a read share no bank
+    static constexpr int PAD = sizeof(T) == 2 ? 8 : 4;
+    static constexpr int XCH = GROWS * GROW + PAD, GCH = GX * GY * GZ + PAD;
 };
 
-// A lane's window of an input row, from two elements before its four voxels of the output row to two after, and the
-// products of one K step of 16 voxels (a: the lane's four values of g) for the three taps dx on it
-template <typename T> struct WgWin;
-template <> struct WgWin<bf16> {
-    uint2 lo, hi;
-    typedef uint2 av;
-    __device__ __forceinline__ void load(const bf16 *p) {
-        lo = *reinterpret_cast<const uint2 *>(p);
-        hi = *reinterpret_cast<const uint2 *>(p + 4);
-    }
-    __device__ __forceinline__ static av load_a(const bf16 *p) { return *reinterpret_cast<const uint2 *>(p); }
-    __device__ __forceinline__ void mul(const av &a, v4f *acc) const {
-        const unsigned m01 = __builtin_amdgcn_alignbit(lo.y, lo.x, 16), m12 = __builtin_amdgcn_alignbit(hi.x, lo.y, 16);
-        const unsigned m23 = __builtin_amdgcn_alignbit(hi.y, hi.x, 16);
-        const uint2 b[3] = {make_uint2(m01, m12), make_uint2(lo.y, hi.x), make_uint2(m12, m23)};
-        v4s a4, b4;
-        __builtin_memcpy(&a4, &a, 8);
+// The nine taps of a dz over one plane of a tile: w the lane's channel of the input plane, a its output channel's row of g
+template <typename T> struct WgPlane;
+template <> struct WgPlane<bf16> {
+    // four K steps of two rows; lane group k holds the four voxels 4 (k % 2) .. of row k / 2
+    __device__ __forceinline__ static void run(const bf16 *w, const bf16 *a, int k, v4f *acc) {
+        w += (k >> 1) * GROW + 4 * (k & 1);
+        a += (k >> 1) * GX + 4 * (k & 1);
+        uint2 lo[GHY - 1], hi[GHY - 1];                       // from two elements before the four voxels to two after
+        v4s av[4];
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx) {
-            __builtin_memcpy(&b4, &b[dx], 8);
-            acc[dx] = MT<bf16>::mma(a4, b4, acc[dx]);
+        for (int y = 0; y < GHY - 1; ++y) {
+            lo[y] = *reinterpret_cast<const uint2 *>(w + y * GROW);
+            hi[y] = *reinterpret_cast<const uint2 *>(w + y * GROW + 4);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) __builtin_memcpy(&av[s], a + 2 * s * GX, 8);
+#pragma unroll
+        for (int y = 0; y < GHY - 1; ++y) {
+            const unsigned m01 = __builtin_amdgcn_alignbit(lo[y].y, lo[y].x, 16);
+            const unsigned m12 = __builtin_amdgcn_alignbit(hi[y].x, lo[y].y, 16);
+            const unsigned m23 = __builtin_amdgcn_alignbit(hi[y].y, hi[y].x, 16);
+            const uint2 b[3] = {make_uint2(m01, m12), make_uint2(lo[y].y, hi[y].x), make_uint2(m12, m23)};
+            // row y is row 2 s + dy of step s; every tap meets the steps in their order
+#pragma unroll
+            for (int dy = 2; dy >= 0; --dy) {
+                if ((y - dy) % 2 || y < dy || y - dy > 6) continue;
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) {
+                    v4s b4;
+                    __builtin_memcpy(&b4, &b[dx], 8);
+                    acc[dy * 3 + dx] = MT<bf16>::mma(av[(y - dy) / 2], b4, acc[dy * 3 + dx]);
+                }
+            }
         }
     }
 };
-template <> struct WgWin<float> {
-    float w[6];
-    typedef float4 av;
-    __device__ __forceinline__ void load(const float *p) {
-        const float2 a = *reinterpret_cast<const float2 *>(p + 2), b = *reinterpret_cast<const float2 *>(p + 4);
-        w[0] = p[1]; w[1] = a.x; w[2] = a.y; w[3] = b.x; w[4] = b.y; w[5] = p[6];
-    }
-    __device__ __forceinline__ static av load_a(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-    __device__ __forceinline__ void mul(const av &a, v4f *acc) const {
-        const float as[4] = {a.x, a.y, a.z, a.w};
+template <> struct WgPlane<float> {
+    // sixteen K steps of half a row; lane group k holds voxel k of the half
+    __device__ __forceinline__ static void run(const float *w, const float *a, int k, v4f *acc) {
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx)
+        for (int y = 0; y < GHY; ++y) {
+            float b[2][3];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[dx] = MT<float>::mma(as[j], w[j + dx], acc[dx]);
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) b[h][dx] = w[y * GROW + 1 + 4 * h + k + dx];
+#pragma unroll
+            for (int dy = 2; dy >= 0; --dy) {
+                if (y < dy || y - dy >= GY) continue;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float av = a[(y - dy) * GX + 4 * h + k];
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx) acc[dy * 3 + dx] = MT<float>::mma(av, b[h][dx], acc[dy * 3 + dx]);
+                }
+            }
+        }
     }
 };
 
-template <typename T, int FR, int TX, bool V4>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && (FR == 1 || (FR == 2 && TX < 64)) ? 2 : 1))) void k_wgrad_direct(
-    const float *__restrict__ g, long long g_bs, int Co, const float *__restrict__ in, long long in_bs, int Ci, int S,
-    int B, int G, float *__restrict__ part, float *__restrict__ bpart) {
-    typedef WgTile<T, TX> W;
-    constexpr int TZ = W::TZ, HZ = W::HZ, ROW = W::ROW, XCH = W::XCH, GCH = W::GCH, NQ = TX / 4;
-    constexpr int COP = FR * 16, KS = 4 / FR;                 // K parts per row block
-    constexpr int ST = (DCC * XCH + COP * GCH) * (int)sizeof(T);
-    constexpr int RB = FR * (KS - 1) * 9 * 4 * 64 * 4;        // values passed on per reduction round
-    __shared__ __attribute__((aligned(16))) unsigned char sm[ST > RB ? ST : RB];
-    T *sX = reinterpret_cast<T *>(sm), *sG = sX + DCC * XCH;
+template <typename T, int FR, bool V4>
+__global__ __launch_bounds__(192 * FR) void k_wgrad_direct(const float *__restrict__ g, long long g_bs, int Co,
+                                                           const float *__restrict__ in, long long in_bs, int Ci, int S,
+                                                           int B, int G, float *__restrict__ part) {
+    constexpr int COP = FR * 16, NT = 192 * FR, XCH = WgTile<T>::XCH, GCH = WgTile<T>::GCH;
+    __shared__ __attribute__((aligned(16))) T sm[DCC * XCH + COP * GCH];
+    T *sX = sm, *sG = sm + DCC * XCH;
     const int nch = (Ci + DCC - 1) / DCC;
     const int per = (nch * G + 7) / 8;
     const int lin = (blockIdx.x % 8) * per + blockIdx.x / 8;  // neighbouring tile groups on one XCD
     if (lin >= nch * G) return;
     const int ch = lin % nch, tg = lin / nch;                 // the chunks of a tile group share its g
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int rg = wave % FR, ks = wave / FR;
-    const int ntx = (S + TX - 1) / TX, nty = (S + WY - 1) / WY, ntz = (S + TZ - 1) / TZ;
+    const int dz = wave % 3, rg = wave / 3;
+    const int ntx = (S + GX - 1) / GX, nty = (S + GY - 1) / GY, ntz = (S + GZ - 1) / GZ;
     const int tiles = ntx * nty * ntz;
     const int V = S * S * S;
-    const int nc = Ci - ch * DCC < DCC ? Ci - ch * DCC : DCC;
-    v4f acc[27];
+    const int nc = min(Ci - ch * DCC, DCC);
+    v4f acc[9];
 #pragma unroll
-    for (int q = 0; q < 27; ++q) acc[q] = v4f{0, 0, 0, 0};
-    // this thread's quads of the tile of g: GQ quads of one channel are spread over a whole number of threads, so that
-    // its channels are fixed and their sums (the bias gradient) stay in registers
-    constexpr int GQ = NQ * WY * TZ, GP = 256 / GQ > 0 ? 256 / GQ : 1, GN = COP / GP;   // channels at a time, passes
-    float bs[GN];
-#pragma unroll
-    for (int q = 0; q < GN; ++q) bs[q] = 0.f;
-    static_assert(GQ * GP == 256 && GN * GP == COP, "256 threads take whole channels of g");
-    const int gq = tid % GQ, go = tid / GQ;
-    const int gx = (gq % NQ) * 4, gy = (gq / NQ) % WY, gz = gq / (NQ * WY);
-    // of the input tile: per channel XI interior quads, then two halo ends per row, whose value is the last or first of
-    // the quad beside the tile
-    constexpr int XI = HZ * WHY * NQ, XU = XI + 2 * HZ * WHY, XP = (XU + 255) / 256;
-    const int k4 = 4 * (lane >> 4);
-    const T *arow = sG + (rg * 16 + (lane & 15)) * GCH + k4;
-    const T *wrow = sX + (lane & 15) * XCH + k4;
-    const int total = B * tiles, each = (total + G - 1) / G;
-    const int t1 = (tg + 1) * each < total ? (tg + 1) * each : total;
-    for (int tt = tg * each; tt < t1; ++tt) {
+    for (int q = 0; q < 9; ++q) acc[q] = v4f{0, 0, 0, 0};
+    // staged in units of four channels, half a row and its halo end; channels from a unit's end on stay zero
+    const int units = (nc + 3) / 4 * 2 * GROWS;
+    for (int e = (nc + 3) / 4 * 4 * XCH + tid; e < DCC * XCH; e += NT) st_one(sX + e, 0.f);
+    for (int tt = tg; tt < B * tiles; tt += G) {
         const int b = tt / tiles, t = tt % tiles;
-        const int x0 = (t % ntx) * TX, y0 = ((t / ntx) % nty) * WY, z0 = (t / (ntx * nty)) * TZ;
+        const int x0 = (t % ntx) * GX, y0 = ((t / ntx) % nty) * GY, z0 = (t / (ntx * nty)) * GZ;
         const float *ib = in + ((long long)b * in_bs + (long long)ch * DCC * V);
         const float *gb = g + (long long)b * g_bs;
+        constexpr int GU = COP * GX * GY * GZ / 4, GP = (GU + NT - 1) / NT;   // quads of g; the last ones more than once
+        float4 gv[GP];
+#pragma unroll
+        for (int p = 0; p < GP; ++p) {
+            const int u = min(tid + NT * p, GU - 1), o = u >> 6, q = u & 63;
+            const int z = z0 + (q >> 4), y = y0 + ((q >> 1) & 7);
+            const bool rin = z < S && y < S && o < Co;
+            gv[p] = row4<V4>(gb + (rin ? (long long)o * V + ((long long)z * S + y) * S : 0), x0 + 4 * (q & 1), S, rin);
+        }
         __syncthreads();
-#pragma unroll 1
-        for (int p = 0; p < XP; ++p) {
-            const int u = tid + 256 * p;
-            const bool quad = u < XI, used = u < XU;
-            const int r = !used ? 0 : quad ? u / NQ : (u - XI) >> 1, xp = quad ? u % NQ : (u & 1);
-            const int z = z0 + r / WHY - 1, y = y0 + r % WHY - 1, x = x0 + (quad ? 4 * xp : (xp ? TX : -4));
-            const bool rin = used && (unsigned)z < (unsigned)S && (unsigned)y < (unsigned)S;
+        for (int u0 = 0; u0 < units; u0 += NT) {
+            const int u = min(u0 + tid, units - 1), c0 = u / (2 * GROWS) * 4, r = u % (2 * GROWS) >> 1, e = u & 1;
+            const int z = z0 + r / GHY - 1, y = y0 + r % GHY - 1;
+            const bool rin = (unsigned)z < (unsigned)S && (unsigned)y < (unsigned)S;
             const float *row = ib + (rin ? ((long long)z * S + y) * S : 0);
-            float4 v[DCC];
+            float4 v[4];
+            float h[4];
 #pragma unroll
-            for (int c = 0; c < DCC; ++c) v[c] = row4<V4>(row + (long long)(c < nc ? c : 0) * V, x, S, rin && c < nc);
-            T *d = sX + r * ROW + (quad ? 2 + 4 * xp : 1 + (TX + 1) * xp);
-            if (quad) {
+            for (int j = 0; j < 4; ++j) {
+                const bool cin = c0 + j < nc;
+                const float *rc = row + (long long)(cin ? c0 + j : 0) * V;
+                v[j] = row4<V4>(rc, x0 + 4 * e, S, rin && cin);
+                h[j] = row1(rc, e ? x0 + GX : x0 - 1, S, rin && cin);
+            }
+            T *d = sX + c0 * XCH + r * GROW;
 #pragma unroll
-                for (int c = 0; c < DCC; ++c) {
-                    st_two(d + c * XCH, v[c].x, v[c].y);
-                    st_two(d + c * XCH + 2, v[c].z, v[c].w);
-                }
-            } else if (used) {
-#pragma unroll
-                for (int c = 0; c < DCC; ++c) st_one(d + c * XCH, xp ? v[c].x : v[c].w);
+            for (int j = 0; j < 4; ++j) {
+                st_two(d + j * XCH + 2 + 4 * e, v[j].x, v[j].y);
+                st_two(d + j * XCH + 4 + 4 * e, v[j].z, v[j].w);
+                st_one(d + j * XCH + (e ? GX + 2 : 1), h[j]);
             }
         }
-        {
-            const int z = z0 + gz, y = y0 + gy;
-            const bool rin = z < S && y < S;
-            const float *row = gb + (rin ? ((long long)z * S + y) * S : 0);
-            T *d = sG + go * GCH + gq * 4;
-            constexpr int GB = GN < 16 ? GN : 16;             // loads in flight
 #pragma unroll
-            for (int q0 = 0; q0 < GN; q0 += GB) {
-                float4 v[GB];
-#pragma unroll
-                for (int q = 0; q < GB; ++q) {
-                    const int o = go + GP * (q0 + q);
-                    v[q] = row4<V4>(row + (long long)(o < Co ? o : 0) * V, x0 + gx, S, rin && o < Co);
-                }
-#pragma unroll
-                for (int q = 0; q < GB; ++q) {
-                    bs[q0 + q] += (v[q].x + v[q].y) + (v[q].z + v[q].w);
-                    st_two(d + GP * (q0 + q) * GCH, v[q].x, v[q].y);
-                    st_two(d + GP * (q0 + q) * GCH + 2, v[q].z, v[q].w);
-                }
-            }
+        for (int p = 0; p < GP; ++p) {
+            const int u = min(tid + NT * p, GU - 1);
+            T *d = sG + (u >> 6) * GCH + (u & 63) * 4;
+            st_two(d, gv[p].x, gv[p].y);
+            st_two(d + 2, gv[p].z, gv[p].w);
         }
         __syncthreads();
-        // segments of four rows and 16 columns of one plane; the six windows of the next (segment, dz) are read while
-        // the 36 products of this one run
-        constexpr int NS = TZ * (TX / 16);
-        typename WgWin<T>::av av[4];
-        WgWin<T> win[2][6];
-        auto rows = [&](int sg) { return (sg / (TX / 16)) * WHY * ROW + (sg % (TX / 16)) * 16; };
+        const T *w = sX + (lane & 15) * XCH + dz * GHY * GROW, *a = sG + (rg * 16 + (lane & 15)) * GCH;
 #pragma unroll
-        for (int y = 0; y < 6; ++y) win[0][y].load(wrow + rows(ks) + y * ROW);
-#pragma unroll 1
-        for (int sg = ks; sg < NS; sg += KS) {
-            const T *a = arow + (sg / (TX / 16)) * WY * TX + (sg % (TX / 16)) * 16;
-#pragma unroll
-            for (int y = 0; y < 4; ++y) av[y] = WgWin<T>::load_a(a + y * TX);
-            const T *w = wrow + rows(sg), *wn = wrow + rows(sg + KS < NS ? sg + KS : sg);
-#pragma unroll
-            for (int dz = 0; dz < 3; ++dz) {
-                const T *nx = dz < 2 ? w + (dz + 1) * WHY * ROW : wn;
-#pragma unroll
-                for (int y = 0; y < 6; ++y) win[(dz + 1) & 1][y].load(nx + y * ROW);
-#pragma unroll
-                for (int y = 0; y < 4; ++y)
-#pragma unroll
-                    for (int dy = 0; dy < 3; ++dy) win[dz & 1][y + dy].mul(av[y], acc + (dz * 3 + dy) * 3);
-            }
-#pragma unroll
-            for (int y = 0; y < 6; ++y) win[0][y] = win[1][y];
-        }
+        for (int z = 0; z < GZ; ++z) WgPlane<T>::run(w + z * GHY * GROW, a + z * GX * GY, lane >> 4, acc);
     }
-    // add the K parts of a row block in order (nine taps a round), then write it
-    if constexpr (KS > 1) {
-        float *red = reinterpret_cast<float *>(sm);
+    // part[tg][ch][tap][row block][i][16 outputs], of the chunk's existing input channels (nci: of every chunk)
+    const int nci = min(Ci, DCC), i = lane & 15;
+    if (i >= nc) return;
 #pragma unroll
-        for (int rnd = 0; rnd < 3; ++rnd) {
-            __syncthreads();
-            // KS - 1 slots per row block: FR (KS - 1) <= 3
-            if (ks > 0) {
-#pragma unroll
-                for (int q = 0; q < 9; ++q)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) red[((rg * (KS - 1) + ks - 1) * 36 + q * 4 + r) * 64 + lane] = acc[rnd * 9 + q][r];
-            }
-            __syncthreads();
-            if (ks == 0) {
-#pragma unroll
-                for (int k = 0; k < KS - 1; ++k)
-#pragma unroll
-                    for (int q = 0; q < 9; ++q)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[rnd * 9 + q][r] += red[((rg * (KS - 1) + k) * 36 + q * 4 + r) * 64 + lane];
-            }
-        }
-    }
-    if (ks == 0) {
-        float *pp = part + ((long long)tg * nch + ch) * 27 * COP * DCC + (rg * 16 + k4) * DCC + (lane & 15);
-#pragma unroll
-        for (int q = 0; q < 27; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) pp[(q * COP + r) * DCC] = acc[q][r];
-    }
-    if (ch == 0) {                                            // the bias: every channel's sums over its GQ threads
-        float *red = reinterpret_cast<float *>(sm);
-#pragma unroll
-        for (int q = 0; q < GN; ++q) {
-            float v = bs[q];
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if constexpr (GQ == 64) {
-                if (lane == 0) bpart[(long long)tg * COP + go + GP * q] = v;
-            } else {
-                __syncthreads();
-                if (lane == 0) red[wave] = v;
-                __syncthreads();
-                if (tid < GP) {
-                    float s = red[tid * (GQ / 64)];
-                    for (int k = 1; k < GQ / 64; ++k) s += red[tid * (GQ / 64) + k];
-                    bpart[(long long)tg * COP + tid + GP * q] = s;
-                }
-            }
-        }
+    for (int q = 0; q < 9; ++q) {
+        float *p = part + (((((long long)tg * nch + ch) * 27 + dz * 9 + q) * FR + rg) * nci + i) * 16 + 4 * (lane >> 4);
+        *reinterpret_cast<float4 *>(p) = make_float4(acc[q][0], acc[q][1], acc[q][2], acc[q][3]);
     }
 }
 
-// dW and db from the tile groups' partial sums: a block takes 16 consecutive partial values e (64 B rows), thread
-// (e, j) adds the groups j, j + 16, ..., and the 16 sums are added in order. The last blocks take the bias.
-__global__ __launch_bounds__(256) void k_wgrad_sum(const float *__restrict__ part, const float *__restrict__ bpart,
-                                                   int G, int Co, int COP, int Ci, float *__restrict__ dW,
-                                                   float *__restrict__ db) {
-    __shared__ float sm[16][17];
-    const int el = threadIdx.x & 15, j = threadIdx.x >> 4;
-    const int nch = (Ci + DCC - 1) / DCC;
-    const int nb = nch * 27 * COP;                            // blocks of weights, one (chunk, tap, o) each
-    const bool bias = (int)blockIdx.x >= nb;
-    const long long n = bias ? COP : (long long)nb * DCC;
-    const float *src = bias ? bpart + ((int)blockIdx.x - nb) * 16 + el : part + (long long)blockIdx.x * 16 + el;
-    float s = 0.f;
-    int q = j;
-    for (; q + 48 < G; q += 64) {
-        const float a = src[q * n], b = src[(q + 16) * n], c = src[(q + 32) * n], d = src[(q + 48) * n];
-        s += a;
-        s += b;
-        s += c;
-        s += d;
-    }
-    for (; q < G; q += 16) s += src[q * n];
-    sm[j][el] = s;
-    __syncthreads();
-    if (j) return;
-    s = sm[0][el];
-    for (int k = 1; k < 16; ++k) s += sm[k][el];
-    if (bias) {
-        const int o = ((int)blockIdx.x - nb) * 16 + el;
-        if (o < Co) db[o] = s;
+// dW from the tile groups' partial sums: thread (e, j) adds the groups j, j + 4, ... of value e, and the four sums are added
+// in the order j = 0..3. The last block adds the slices of the bias (k_bias_part).
+__global__ __launch_bounds__(256) void k_wgrad_sum(const float *__restrict__ part, const float *__restrict__ bpart, int G,
+                                                   int n, int Co, int FR, int Ci, float *__restrict__ dW, float *__restrict__ db) {
+    __shared__ float sm[4][64];
+    const int el = threadIdx.x & 63, j = threadIdx.x >> 6;
+    if (blockIdx.x == gridDim.x - 1) {
+        if ((int)threadIdx.x < Co) db[threadIdx.x] = sum_strided(bpart + threadIdx.x * BG_SLICES, 0, BG_SLICES, 1);
         return;
     }
-    const int o = blockIdx.x % COP, tap = (blockIdx.x / COP) % 27, i = blockIdx.x / (COP * 27) * DCC + el;
-    if (o < Co && i < Ci) dW[((long long)o * Ci + i) * 27 + tap] = s;
+    const int e = blockIdx.x * 64 + el;
+    sm[j][el] = e < n ? sum_strided<16>(part + e, (long long)j * n, (long long)G * n, 4LL * n) : 0.f;
+    __syncthreads();
+    if (j || e >= n) return;
+    const int nci = min(Ci, DCC);
+    int r = e / 16, o = e % 16;
+    const int i = r % nci;
+    r /= nci;
+    o += r % FR * 16;
+    r /= FR;
+    const int tap = r % 27, c = r / 27 * DCC + i;
+    if (o < Co && c < Ci) dW[((long long)o * Ci + c) * 27 + tap] = ((sm[0][el] + sm[1][el]) + sm[2][el]) + sm[3][el];
 }
 
 // dW[e] = sum_q part[q][e], q = 0..G-1: a block takes 64 consecutive e; thread (e, j) adds q = j, j + 4, ...
@@ -1246,46 +1162,27 @@ hipError_t cnn_conv_direct(int use_bf16, const float *in, long long in_bs, int C
                     : cnn_conv_direct_t<float>(in, in_bs, Ci, S, wt, COP, bias, Co, out, out_bs, relu, mask, B, s);
 }
 
-// Tile groups of a weight gradient: about 512 workgroups (two per CU are resident), every group with the same number of
-// consecutive tiles up to one. A group writes partial sums as large as the layer's weights, which the last kernel reads
-// again: so at least two tiles per group where there are enough, and half as many groups for few tiles and many chunks
-// (128 -> 64 channels at 16^3: 56 MB of partial sums with 512 workgroups).
-int cnn_wgrad_groups(int Ci, int B, int tiles_of_one) {
-    const int tiles = B * tiles_of_one;
-    const int nch = (Ci + DCC - 1) / DCC;
-    const int want = std::max(1, (nch <= 2 || tiles >= 512 ? 512 : 256) / nch);
-    const int each = std::max(tiles >= 512 ? 2 : 1, (tiles + want - 1) / want);
-    return (tiles + each - 1) / each;
-}
-
-template <typename T, int FR, int TX>
+// Tile groups: 1024 workgroups in all, or one tile each. The number fixes the order of the sums.
+template <typename T, int FR>
 hipError_t wgrad_launch(hipStream_t s, const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci,
                         int S, int B, float *part, long long part_elems, float *bpart, float *dW, float *db) {
-    constexpr int COP = FR * 16, TZ = WgTile<T, TX>::TZ;
     const int nch = (Ci + DCC - 1) / DCC;
-    const int tiles = ((S + TX - 1) / TX) * ((S + WY - 1) / WY) * ((S + TZ - 1) / TZ);
-    const long long per = (long long)nch * 27 * COP * DCC;
-    const int G = (int)std::min<long long>(cnn_wgrad_groups(Ci, B, tiles), part_elems / per);
-    if (G < 1) return hipErrorInvalidValue;
+    if (nch > 1 && Ci % DCC) return hipErrorInvalidValue;     // every chunk has the same number of input channels
+    const int tiles = ((S + GX - 1) / GX) * ((S + GY - 1) / GY) * ((S + GZ - 1) / GZ);
+    const long long n = (long long)27 * FR * 16 * Ci;
+    const int G = (int)std::min<long long>((long long)B * tiles, (1024 + nch - 1) / nch);
+    if (G * n > part_elems) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_bias_part, dim3(Co * BG_SLICES), dim3(256), 0, s, g, g_bs, B, S * S * S, bpart);
     const unsigned grid = (unsigned)((nch * G + 7) / 8 * 8);
     // 16-byte loads need every row 16-byte aligned
     if (S % 4 == 0 && ((uintptr_t)g | (uintptr_t)in) % 16 == 0 && (g_bs | in_bs) % 4 == 0)
-        hipLaunchKernelGGL((k_wgrad_direct<T, FR, TX, true>), dim3(grid), dim3(256), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, G, part, bpart);
+        hipLaunchKernelGGL((k_wgrad_direct<T, FR, true>), dim3(grid), dim3(192 * FR), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, G, part);
     else
-        hipLaunchKernelGGL((k_wgrad_direct<T, FR, TX, false>), dim3(grid), dim3(256), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, G, part, bpart);
+        hipLaunchKernelGGL((k_wgrad_direct<T, FR, false>), dim3(grid), dim3(192 * FR), 0, s, g, g_bs, Co, in, in_bs, Ci, S, B, G, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)(nch * 27 * COP + COP / 16)), dim3(256), 0, s, part, bpart, G, Co, COP,
-                       Ci, dW, db);
+    hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)((n + 63) / 64 + 1)), dim3(256), 0, s, part, bpart, G, (int)n, Co, FR, Ci, dW, db);
     return hipGetLastError();
-}
-
-template <typename T, int FR>
-hipError_t wgrad_width(hipStream_t s, const float *g, long long g_bs, int Co, const float *in, long long in_bs, int Ci,
-                       int S, int B, float *part, long long part_elems, float *bpart, float *dW, float *db) {
-    if (S > 32) return wgrad_launch<T, FR, 64>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
-    if (S > 16) return wgrad_launch<T, FR, 32>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
-    return wgrad_launch<T, FR, 16>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
 }
 
 template <typename T>
@@ -1293,9 +1190,9 @@ hipError_t cnn_wgrad_direct_t(const float *g, long long g_bs, int Co, const floa
                               int B, float *part, long long part_elems, float *bpart, float *dW, float *db,
                               hipStream_t s) {
     switch ((Co + 15) / 16) {
-    case 1: return wgrad_width<T, 1>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
-    case 2: return wgrad_width<T, 2>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
-    case 4: return wgrad_width<T, 4>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+    case 1: return wgrad_launch<T, 1>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+    case 2: return wgrad_launch<T, 2>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
+    case 4: return wgrad_launch<T, 4>(s, g, g_bs, Co, in, in_bs, Ci, S, B, part, part_elems, bpart, dW, db);
     default: return hipErrorInvalidValue;
     }
 }
