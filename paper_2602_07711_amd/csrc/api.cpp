@@ -152,8 +152,6 @@ helm_status upload_folds(Ctx &c, Slab &slab, std::initializer_list<FoldJob> jobs
     for (int q = 0; q < fb.n; ++q) { fb.b[q].d64 = *out[q].first; fb.b[q].d32 = *out[q].second; }
     HIP_TRY(launch_fold_expand(fb, c.stream));
     prof_gap(c);
-    // a batch applies the blocks on a stream of its own
-    HIP_TRY(hipStreamSynchronize(c.stream));
     return HELM_OK;
 }
 
@@ -928,6 +926,9 @@ helm_status setup_impl(helm_ctx **out, helm_grid g, const double h[3], const voi
     c.ay = c.hz * c.hz / (c.hy * c.hy);
     c.c0 = c.hz * c.hz * c.k0 * c.k0 - 2.0 * (c.ax + c.ay + 1.0);
     if ((st = fill_tpiv(c, c.dxe, c.dye, &c.tpiv_eig, d2(c.gamma[2]), 1.0 / c.zeta)) != HELM_OK) return bail(st);
+    // a batch reads the blocks and the pivots on a stream of its own, which waits for the first context's stream only
+    const hipError_t we = hipStreamSynchronize(c.stream);
+    if (we != hipSuccess) { c.err = std::string("set-up: ") + hipGetErrorString(we); return bail(HELM_EDEVICE); }
     *out = ctx;
     return HELM_OK;
 }
