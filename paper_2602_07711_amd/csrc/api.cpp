@@ -47,7 +47,9 @@ void dfree(Ctx &c, void *p) {
     (void)hipFree(p);
 }
 
-// Several arrays in one allocation, those with contents (put) first and uploaded by one copy. The pointers are set by commit.
+// Several arrays in one allocation, those with contents (put) first and uploaded by one copy. The pointers are set by commit,
+// and stay set only if its `fill`, which launches the kernels that write the others, succeeds: a set pointer stands for a
+// filled set.
 // hipMalloc of more than 1 MiB takes 30 to 240 us, hipFree of 8 MiB and more 225 us, and a copy from pageable memory 12 to
 // 60 us: a 64^3 context with one allocation and one copy per array spent 2 ms on them. Arrays of 1 MiB and more begin at
 // 2 MiB, as if allocated alone, and those of `alone` bytes and more are: their 260 us are little beside the work on them, and
@@ -71,7 +73,8 @@ struct Slab {
     template <typename T> void put(T **p, const void *data, size_t count) { std::memcpy(put(p, count), data, count * sizeof(T)); }
     // src (may be null): contents that stay where they are until commit copies them, one copy each
     template <typename T> void take(T **p, size_t count, const void *src = nullptr) { work.push_back({(void **)p, count * sizeof(T), 0, src}); }
-    helm_status commit(Ctx &c);
+    template <typename Fill> helm_status commit(Ctx &c, Fill fill);
+    helm_status commit(Ctx &c) { return commit(c, [] { return HELM_OK; }); }
 };
 
 #define ST_TRY(expr)                              \
@@ -80,18 +83,17 @@ struct Slab {
         if (_s != HELM_OK) return _s;             \
     } while (0)
 
-helm_status Slab::commit(Ctx &c) {
+template <typename Fill> helm_status Slab::commit(Ctx &c, Fill fill) {
     size_t end = host.size();
     for (Slot &s : work) {
         if (s.bytes >= alone) continue;
         s.off = aligned(end, s.bytes);
         end = s.off + s.bytes;
     }
-    // all or nothing: a caller takes a set pointer for the whole set
     const size_t before = c.allocs.size();
     std::vector<char *> at(work.size());
     char *base = nullptr;
-    auto fill = [&]() -> helm_status {
+    auto place = [&]() -> helm_status {
         if (end) ST_TRY(dalloc(c, &base, end));
         if (!host.empty()) HIP_TRY(hipMemcpy(base, host.data(), host.size(), hipMemcpyHostToDevice));
         for (size_t i = 0; i < work.size(); ++i) {
@@ -100,16 +102,17 @@ helm_status Slab::commit(Ctx &c) {
             else at[i] = base + s.off;
             if (s.src) HIP_TRY(hipMemcpy(at[i], s.src, s.bytes, hipMemcpyHostToDevice));
         }
-        return HELM_OK;
+        for (const Slot &s : up) *s.p = base + s.off;
+        for (size_t i = 0; i < work.size(); ++i) *work[i].p = at[i];
+        return fill();
     };
-    const helm_status st = fill();
+    const helm_status st = place();
     if (st != HELM_OK) {
+        for (const Slot &s : up) *s.p = nullptr;
+        for (const Slot &s : work) *s.p = nullptr;
         while (c.allocs.size() > before) dfree(c, c.allocs.back());
-        return st;
     }
-    for (const Slot &s : up) *s.p = base + s.off;
-    for (size_t i = 0; i < work.size(); ++i) *work[i].p = at[i];
-    return HELM_OK;
+    return st;
 }
 
 inline double2 d2(cd v) { return make_double2(v.real(), v.imag()); }
@@ -148,11 +151,12 @@ helm_status upload_folds(Ctx &c, Slab &slab, std::initializer_list<FoldJob> jobs
         block(j.f->ms, j.f->Vsi, j.f->Vs, true, &j.m64->fs, &j.m32->fs, &j.m64->is, &j.m32->is);
         block(j.f->ma, j.f->Vai, j.f->Va, false, &j.m64->fa, &j.m32->fa, &j.m64->ia, &j.m32->ia);
     }
-    ST_TRY(slab.commit(c));
-    for (int q = 0; q < fb.n; ++q) { fb.b[q].d64 = *out[q].first; fb.b[q].d32 = *out[q].second; }
-    HIP_TRY(launch_fold_expand(fb, c.stream));
-    prof_gap(c);
-    return HELM_OK;
+    return slab.commit(c, [&]() -> helm_status {
+        for (int q = 0; q < fb.n; ++q) { fb.b[q].d64 = *out[q].first; fb.b[q].d32 = *out[q].second; }
+        HIP_TRY(launch_fold_expand(fb, c.stream));
+        prof_gap(c);
+        return HELM_OK;
+    });
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -202,8 +206,7 @@ helm_status ensure_tpiv(Ctx &c, const double2 *dx, const double2 *dy, TriPiv *pi
     if (piv->d) return HELM_OK;
     Slab slab;
     take_tpiv(c, slab, piv);
-    ST_TRY(slab.commit(c));
-    return fill_tpiv(c, dx, dy, piv, gz, zi);
+    return slab.commit(c, [&] { return fill_tpiv(c, dx, dy, piv, gz, zi); });
 }
 // the operator's own closure (gamma_z and, for the collocated closure, zeta)
 helm_status ensure_tpiv(Ctx &c, const double2 *dx, const double2 *dy, TriPiv *piv) {
@@ -361,11 +364,11 @@ template <typename CT> helm_status build_ring_mats(Ctx &c, PfftMats<CT> &m) {
     // the four matrices as they are; their transposes and FP32 forms are made on the device
     Slab slab;
     const size_t xx = (size_t)c.nx * c.nx, yy = (size_t)c.ny * c.ny;
-    double2 *src[4];
-    slab.take(&src[0], xx, c.hVxi.data());
-    slab.take(&src[1], xx, c.hVx.data());
-    slab.take(&src[2], yy, c.hVyi.data());
-    slab.take(&src[3], yy, c.hVy.data());
+    double2 *Vxi, *Vx, *Vyi, *Vy;
+    slab.take(&Vxi, xx, c.hVxi.data());
+    slab.take(&Vx, xx, c.hVx.data());
+    slab.take(&Vyi, yy, c.hVyi.data());
+    slab.take(&Vy, yy, c.hVy.data());
     if (sizeof(CT) == sizeof(float2)) { slab.take(&m.Vxi, xx); slab.take(&m.Vx, xx); slab.take(&m.Vy, yy); }
     slab.take(&m.VxiT, xx);
     slab.take(&m.VxT, xx);
@@ -381,14 +384,15 @@ template <typename CT> helm_status build_ring_mats(Ctx &c, PfftMats<CT> &m) {
     slab.take(&m.rsum, (size_t)c.nz * 2 * c.nx);
     slab.take(&m.rbuf, ring);
     slab.take(&m.fvec, ring);
-    ST_TRY(slab.commit(c));
-    if (sizeof(CT) == sizeof(double2)) { m.Vxi = (CT *)src[0]; m.Vx = (CT *)src[1]; m.Vy = (CT *)src[3]; }
-    HIP_TRY(launch_dense_forms(src[0], m.Vxi, m.VxiT, c.nx, c.stream));
-    HIP_TRY(launch_dense_forms(src[1], m.Vx, m.VxT, c.nx, c.stream));
-    HIP_TRY(launch_dense_forms(src[2], (CT *)nullptr, m.VyiT, c.ny, c.stream));
-    HIP_TRY(launch_dense_forms(src[3], m.Vy, m.VyT, c.ny, c.stream));
-    prof_gap(c);
-    return HELM_OK;
+    return slab.commit(c, [&]() -> helm_status {
+        if (sizeof(CT) == sizeof(double2)) { m.Vxi = (CT *)Vxi; m.Vx = (CT *)Vx; m.Vy = (CT *)Vy; }
+        HIP_TRY(launch_dense_forms(Vxi, m.Vxi, m.VxiT, c.nx, c.stream));
+        HIP_TRY(launch_dense_forms(Vx, m.Vx, m.VxT, c.nx, c.stream));
+        HIP_TRY(launch_dense_forms(Vyi, (CT *)nullptr, m.VyiT, c.ny, c.stream));
+        HIP_TRY(launch_dense_forms(Vy, m.Vy, m.VyT, c.ny, c.stream));
+        prof_gap(c);
+        return HELM_OK;
+    });
 }
 
 // Sine matrices and Dirichlet eigenvalues (shared by PFFT and FFT2); `ring` adds PFFT's face-correction data.
@@ -397,8 +401,8 @@ helm_status ensure_sine(Ctx &c, bool fp32, bool ring) {
         c.err = "the PFFT preconditioner supports N_x, N_y <= " + std::to_string(ring_max_n());
         return HELM_EUNSUPPORTED;
     }
-    if (!c.pfft) {
-        c.pfft = new PfftPlan();
+    if (!c.pfft) c.pfft = new PfftPlan();
+    if (!c.pfft->dFx) {
         std::vector<double2> fx(c.nx), fy(c.ny);
         const double pi = 3.14159265358979323846;
         for (int i = 0; i < c.nx; ++i) fx[i] = make_double2(2.0 * std::cos(pi * (i + 1) / (c.nx + 1)), 0.0);
@@ -439,12 +443,12 @@ helm_status ensure_fftk(Ctx &c, bool fp32) {
         const int ns[3] = {c.nx, c.ny, c.nz};
         const double hs[3] = {c.hx, c.hy, c.hz};
         double **dst[3] = {&P.tx, &P.ty, &P.tz};
+        Slab slab;
         for (int a = 0; a < 3; ++a) {
-            std::vector<double> t(ns[a]);
+            double *t = slab.put(dst[a], (size_t)ns[a]);
             for (int i = 0; i < ns[a]; ++i) t[i] = (2.0 * std::cos(pi * (i + 1) / (ns[a] + 1)) - 2.0) / (hs[a] * hs[a]);
-            ST_TRY(dalloc(c, dst[a], (size_t)ns[a]));
-            HIP_TRY(hipMemcpy(*dst[a], t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice));
         }
+        ST_TRY(slab.commit(c));
     }
     if (!P.m64.fsz.fs) {
         const EigFold fz = sine_fold(c.nz, sine_matrix(c.nz));

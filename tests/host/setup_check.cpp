@@ -162,11 +162,48 @@ void check_setup_waits() {
     helm_destroy(c);
 }
 
+// every device call of a set-up or a first use fails once: the call reports it, and the next one does what was not done
+void check_faults() {
+    helm_ctx *c = nullptr;
+    fail_at = 0, calls = 0;
+    if (setup(&c) != HELM_OK) complain("set-up failed");
+    const long of_setup = calls;
+    helm_destroy(c);
+    for (long k = 1; k <= of_setup; ++k) {
+        at = "set-up, call " + std::to_string(k);
+        calls = 0, fail_at = k;
+        if (setup(&c) == HELM_OK || c) complain("not reported");
+        if (!live.empty()) complain("memory not given back");
+    }
+    for (int bc : {HELM_BC_ABC2, HELM_BC_ABC3})
+        for (int kind : {HELM_PREC_EIGT, HELM_PREC_PFFT, HELM_PREC_FFT2, HELM_PREC_FFT4})
+            for (int fp32 = 0; fp32 < 2; ++fp32)
+                for (long k = 1, of_use = 1; k <= of_use; ++k) {
+                    at = "closure " + std::to_string(bc) + ", kind " + std::to_string(kind) + ", fp32 " + std::to_string(fp32) + ", call " + std::to_string(k);
+                    fail_at = 0;
+                    if (setup(&c, bc) != HELM_OK) complain("set-up failed");
+                    calls = 0;
+                    if (k == 1) {                              // how many calls the first use makes
+                        if (helm_precond_apply(c, vec_y, vec_z, kind, fp32) != HELM_OK) complain("first use failed");
+                        of_use = calls;
+                        helm_destroy(c);
+                        setup(&c, bc);
+                        calls = 0;
+                    }
+                    fail_at = k;
+                    if (helm_precond_apply(c, vec_y, vec_z, kind, fp32) == HELM_OK) complain("not reported");
+                    fail_at = 0;
+                    if (helm_precond_apply(c, vec_y, vec_z, kind, fp32) != HELM_OK) complain("next use failed");
+                    helm_destroy(c);
+                }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "waits") check_setup_waits();
+    else if (what == "faults") check_faults();
     else return 2;
     if (!live.empty()) { at = "end"; complain("memory not given back"); }
     std::printf(bad ? "%d faults\n" : "ok\n", bad);

@@ -33,3 +33,7 @@ def program(tmp_path_factory):
 
 def test_setup_leaves_no_queued_work(program):
     program("waits")
+
+
+def test_a_failed_call_leaves_nothing_half_made(program):
+    program("faults")
