@@ -360,16 +360,17 @@ helm_status build_sine_mats(Ctx &c, PfftMats<CT> &m, const std::vector<cd> &Sx, 
     return slab.commit(c);
 }
 
-template <typename CT> helm_status build_ring_mats(Ctx &c, PfftMats<CT> &m) {
-    // the four matrices as they are; their transposes and FP32 forms are made on the device
+// The four matrices go up as they are, once; their transposes and FP32 forms are made on the device, the latter from the
+// FP64 plan, which is made first.
+template <typename CT> helm_status build_ring_mats(Ctx &c, PfftMats<CT> &m, const PfftMats<double2> &m64) {
+    constexpr bool f32 = sizeof(CT) == sizeof(float2);
     Slab slab;
     const size_t xx = (size_t)c.nx * c.nx, yy = (size_t)c.ny * c.ny;
-    double2 *Vxi, *Vx, *Vyi, *Vy;
-    slab.take(&Vxi, xx, c.hVxi.data());
-    slab.take(&Vx, xx, c.hVx.data());
-    slab.take(&Vyi, yy, c.hVyi.data());
-    slab.take(&Vy, yy, c.hVy.data());
-    if (sizeof(CT) == sizeof(float2)) { slab.take(&m.Vxi, xx); slab.take(&m.Vx, xx); slab.take(&m.Vy, yy); }
+    double2 *Vyi = nullptr;
+    slab.take(&m.Vxi, xx, f32 ? nullptr : c.hVxi.data());
+    slab.take(&m.Vx, xx, f32 ? nullptr : c.hVx.data());
+    slab.take(&m.Vy, yy, f32 ? nullptr : c.hVy.data());
+    if (!f32) slab.take(&Vyi, yy, c.hVyi.data());
     slab.take(&m.VxiT, xx);
     slab.take(&m.VxT, xx);
     slab.take(&m.VyiT, yy);
@@ -385,11 +386,11 @@ template <typename CT> helm_status build_ring_mats(Ctx &c, PfftMats<CT> &m) {
     slab.take(&m.rbuf, ring);
     slab.take(&m.fvec, ring);
     return slab.commit(c, [&]() -> helm_status {
-        if (sizeof(CT) == sizeof(double2)) { m.Vxi = (CT *)Vxi; m.Vx = (CT *)Vx; m.Vy = (CT *)Vy; }
-        HIP_TRY(launch_dense_forms(Vxi, m.Vxi, m.VxiT, c.nx, c.stream));
-        HIP_TRY(launch_dense_forms(Vx, m.Vx, m.VxT, c.nx, c.stream));
-        HIP_TRY(launch_dense_forms(Vyi, (CT *)nullptr, m.VyiT, c.ny, c.stream));
-        HIP_TRY(launch_dense_forms(Vy, m.Vy, m.VyT, c.ny, c.stream));
+        HIP_TRY(launch_dense_forms(m64.Vxi, f32 ? m.Vxi : nullptr, m.VxiT, c.nx, c.stream));
+        HIP_TRY(launch_dense_forms(m64.Vx, f32 ? m.Vx : nullptr, m.VxT, c.nx, c.stream));
+        HIP_TRY(launch_dense_forms(m64.Vy, f32 ? m.Vy : nullptr, m.VyT, c.ny, c.stream));
+        if (f32) HIP_TRY(launch_dense_forms(m64.VyiT, m.VyiT, (CT *)nullptr, c.ny, c.stream));
+        else HIP_TRY(launch_dense_forms(Vyi, (CT *)nullptr, m.VyiT, c.ny, c.stream));
         prof_gap(c);
         return HELM_OK;
     });
@@ -424,10 +425,10 @@ helm_status ensure_sine(Ctx &c, bool fp32, bool ring) {
         Slab slab;
         ST_TRY(upload_folds(c, slab, {{&fx, true, &P.m64.fsx, &P.m32.fsx}, {&fy, false, &P.m64.fsy, &P.m32.fsy}}));
     }
-    if (ring && !P.m64.ringT) ST_TRY(build_ring_mats(c, P.m64));
+    if (ring && !P.m64.ringT) ST_TRY(build_ring_mats(c, P.m64, P.m64));
     if (fp32) {
         if (!P.m32.Sx) ST_TRY(build_sine_mats(c, P.m32, Sx, Sy));
-        if (ring && !P.m32.ringT) ST_TRY(build_ring_mats(c, P.m32));
+        if (ring && !P.m32.ringT) ST_TRY(build_ring_mats(c, P.m32, P.m64));
     }
     return HELM_OK;
 }

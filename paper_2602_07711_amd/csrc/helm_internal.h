@@ -98,7 +98,7 @@ hipError_t launch_fold_z32_in64(int mode, const FoldDesc &f, const double2 *D, c
 struct FoldBlock { double2 *src, *d64; float2 *d32; int nb, P; };
 struct FoldBlocks { FoldBlock b[8]; int n; };
 hipError_t launch_fold_expand(const FoldBlocks &f, hipStream_t s);
-// an n x n matrix in its transposed and (FP32, unless null) plain form
+// an n x n matrix in its plain and its transposed form (either may be null)
 hipError_t launch_dense_forms(const double2 *src, double2 *plain, double2 *transposed, int n, hipStream_t s);
 hipError_t launch_dense_forms(const double2 *src, float2 *plain, float2 *transposed, int n, hipStream_t s);
 hipError_t launch_fold_z32_out64(int mode, const FoldDesc &f, const float2 *D, const float2 *Ms, const float2 *Ma,

@@ -161,11 +161,11 @@ __global__ __launch_bounds__(256) void k_dense_forms(const double2 *__restrict__
         v.x = (decltype(v.x))src[t].x;
         v.y = (decltype(v.y))src[t].y;
         if (plain) plain[t] = v;
-        transposed[(long long)k * n + r] = v;
+        if (transposed) transposed[(long long)k * n + r] = v;
     }
 }
-hipError_t launch_dense_forms(const double2 *src, double2 *, double2 *transposed, int n, hipStream_t s) {
-    hipLaunchKernelGGL(k_dense_forms<double2>, dim3((n * n + 255) / 256), dim3(256), 0, s, src, (double2 *)nullptr, transposed, n);
+hipError_t launch_dense_forms(const double2 *src, double2 *plain, double2 *transposed, int n, hipStream_t s) {
+    hipLaunchKernelGGL(k_dense_forms<double2>, dim3((n * n + 255) / 256), dim3(256), 0, s, src, plain, transposed, n);
     return hipGetLastError();
 }
 hipError_t launch_dense_forms(const double2 *src, float2 *plain, float2 *transposed, int n, hipStream_t s) {

@@ -198,12 +198,25 @@ void check_faults() {
                 }
 }
 
+// the FP32 form of the face corrections is made from the FP64 one on the device: only the sine matrices go up again
+void check_uploads() {
+    at = "first FP32 use of PFFT";
+    helm_ctx *c = nullptr;
+    if (setup(&c) != HELM_OK) complain("set-up failed");
+    if (helm_precond_apply(c, vec_y, vec_z, HELM_PREC_PFFT, 0) != HELM_OK) complain("failed");
+    copied = 0;
+    if (helm_precond_apply(c, vec_y, vec_z, HELM_PREC_PFFT, 1) != HELM_OK) complain("failed");
+    if (copied > sizeof(float2) * (NX * NX + NY * NY) + 256) complain("uploads the eigenvector matrices once more");
+    helm_destroy(c);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "waits") check_setup_waits();
     else if (what == "faults") check_faults();
+    else if (what == "uploads") check_uploads();
     else return 2;
     if (!live.empty()) { at = "end"; complain("memory not given back"); }
     std::printf(bad ? "%d faults\n" : "ok\n", bad);

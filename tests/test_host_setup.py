@@ -37,3 +37,7 @@ def test_setup_leaves_no_queued_work(program):
 
 def test_a_failed_call_leaves_nothing_half_made(program):
     program("faults")
+
+
+def test_matrices_are_uploaded_once(program):
+    program("uploads")
