@@ -137,14 +137,15 @@ helm_status upload_folds(Ctx &c, Slab &slab, std::initializer_list<FoldJob> jobs
                     fw[j.xaxis ? (size_t)i * nb + k : (size_t)k * nb + i] = Vi[(size_t)k * nb + i] * (mid ? 0.5 : r);
                     iv[j.xaxis ? (size_t)k * nb + i : (size_t)i * nb + k] = V[(size_t)i * nb + k] * (mid ? 1.0 : r);
                 }
-            const size_t P = fold_pad(nb);
+            const int sum = fold_pad_sum(nb), outs = fold_pad_out(nb);
             for (int inv = 0; inv < 2; ++inv) {
                 FoldBlock &q = fb.b[fb.n++];
                 q.nb = nb;
-                q.P = (int)P;
+                q.rows = j.xaxis ? sum : outs;
+                q.ld = j.xaxis ? outs : sum;
                 slab.put(&q.src, (inv ? iv : fw).data(), (size_t)nb * nb);
-                slab.take(inv ? i64 : f64, P * P);
-                slab.take(inv ? i32 : f32, P * P);
+                slab.take(inv ? i64 : f64, (size_t)sum * outs);
+                slab.take(inv ? i32 : f32, (size_t)sum * outs);
                 out.push_back({inv ? i64 : f64, inv ? i32 : f32});
             }
         };

@@ -269,8 +269,9 @@ __device__ __forceinline__ void gemm_tile(const TA *__restrict__ A, const TB *__
 // Bound by the matrix cores where they are many (FP64 MFMAs busy 70% of the time at 200^3), by latency where few.
 // One transform, before and after: FP64 200^3 x 168 -> 163 us, y 203 -> 163, y inverse 215 -> 161; 256^3 x 317 -> 304;
 // 32^3 5.2 -> 3.8, inverse 9.1 -> 6.3; FP32 256^3 x 159 -> 152, y inverse 136 -> 130, 64^3 inverse 10.3 -> 7.3.
-// The block matrices are zero-padded to whole tiles (fold_pad), which makes their loads unconditional and lets the
-// data's run past the end of the half: they are clamped to the line's own values, which then meet zeros.
+// The block matrices are zero-padded (fold_pad_sum, fold_pad_out), which makes their loads unconditional and lets the
+// data's run past the end of the half: they are clamped to the line's own values, which then meet zeros. A tile of 128
+// modes may reach past the padding of its block: there it reads the last padded mode, for results that are not stored.
 
 template <int MODE, int BM, int BN> __host__ __device__ inline long long fold_tiles(const FoldDesc &f) {
     return fold_tile_count(MODE, f, BM, BN);
@@ -386,7 +387,8 @@ __device__ __forceinline__ void fold_tile(const TD *__restrict__ D, const TM *__
         // transforms) is then not shared between them and held in registers across the first
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        const int K = skew ? ma : ms, P = fold_pad(K), off = skew ? f.moff : 0, mst = f.mstep;
+        const int K = skew ? ma : ms, outs = fold_pad_out(K), P = X ? outs : fold_pad_sum(K);
+        const int off = skew ? f.moff : 0, mst = f.mstep;
         const int nblk = (min(K, x0 + BX) - x0 + 15) / 16;
         const TM *Mp = (skew ? Ma : Ms) + (X ? x0 : (long long)x0 * P);
         const int last = FWD ? n - 1 : K - 1;
@@ -410,7 +412,8 @@ __device__ __forceinline__ void fold_tile(const TD *__restrict__ D, const TM *__
                 if constexpr (FWD) return Pair<TD>{base[row + gk], base[row + (n - 1 - gk)]};
                 else return base[row + off + mst * gk];
             };
-            auto lb = [&](int k0, int e) { return (Mp + (long long)k0 * P)[(unsigned)((tid + e * 256) / BN * P + (tid + e * 256) % BN)]; };
+            const int mode = BX > 64 ? min(tid % BN, outs - 1 - x0) : tid % BN;
+            auto lb = [&](int k0, int e) { return (Mp + (long long)k0 * P)[(unsigned)((tid + e * 256) / BN * P + mode)]; };
             run([&](auto nx) { fold_kloop<T, X, decltype(nx)::value, BM, BN, BK, NS, RW>(t, K, la, lb, fdat, fmat, sA, sB, tid); });
         } else {
             const int col = min(l0 + tid % BN, lines - 1);
@@ -418,7 +421,10 @@ __device__ __forceinline__ void fold_tile(const TD *__restrict__ D, const TM *__
             // positions as 32-bit offsets (an axis times its stride is at most the vector's 2^31 entries)
             const unsigned uld = (unsigned)ld, top = (unsigned)(n - 1) * uld, end = (unsigned)last * uld;
             const unsigned first = (unsigned)(tid / BN) * uld;
-            auto la = [&](int k0, int e) { return (Mp + k0)[(unsigned)((tid + e * 256) / BK * P + (tid + e * 256) % BK)]; };
+            auto la = [&](int k0, int e) {
+                const int idx = tid + e * 256, mode = BX > 64 ? min(idx / BK, outs - 1 - x0) : idx / BK;
+                return (Mp + k0)[(unsigned)(mode * P + idx % BK)];
+            };
             auto lb = [&](int k0, int e) {
                 const unsigned o = min(first + (unsigned)(k0 + e * (256 / BN)) * uld, end);
                 if constexpr (FWD) return Pair<TD>{base[o], base[top - o]};

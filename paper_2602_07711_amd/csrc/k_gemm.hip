@@ -141,12 +141,12 @@ hipError_t launch_fold_z32_in64(int mode, const FoldDesc &f, const double2 *D, c
     return fold_launch_cfg<FOLD_XF, double2, float2, float2, float>(f, D, Ms, Ma, C, s, cfg, real);
 }
 
-// A context's transform blocks from their compact FP64 form: 16 P^2 elements written for 4 nb^2 read, one launch instead
-// of the padded blocks in two precisions over the host link (6.3 MB at 64^3 and 256^3)
+// A context's transform blocks from their compact FP64 form: eight of nb^2 elements read, and written padded in two
+// precisions, one launch instead of the padded blocks over the host link (0.4 MB at 64^3, 3.1 MB at 256^3)
 __global__ __launch_bounds__(256) void k_fold_expand(FoldBlocks f) {
     const FoldBlock q = f.b[blockIdx.y];
-    for (int t = blockIdx.x * 256 + threadIdx.x; t < q.P * q.P; t += gridDim.x * 256) {
-        const int r = t / q.P, k = t - r * q.P;
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < q.rows * q.ld; t += gridDim.x * 256) {
+        const int r = t / q.ld, k = t - r * q.ld;
         const double2 v = r < q.nb && k < q.nb ? q.src[(long long)r * q.nb + k] : make_double2(0.0, 0.0);
         q.d64[t] = v;
         q.d32[t] = make_float2((float)v.x, (float)v.y);

@@ -210,6 +210,19 @@ void check_uploads() {
     helm_destroy(c);
 }
 
+// a small context is small: next to 100 bytes per unknown, its transform blocks and tables stay below half a megabyte, and
+// below one with the sine transforms'
+void check_memory() {
+    at = "memory of a small context";
+    helm_ctx *c = nullptr;
+    if (setup(&c) != HELM_OK) complain("set-up failed");
+    const size_t vectors = (size_t)100 * NX * NY * NZ;
+    if (live_bytes > vectors + (512u << 10)) complain("set-up takes more than half a megabyte");
+    if (helm_precond_apply(c, vec_y, vec_z, HELM_PREC_FFT2, 0) != HELM_OK) complain("failed");
+    if (live_bytes > vectors + (1u << 20)) complain("the sine transforms take more than half a megabyte");
+    helm_destroy(c);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -217,6 +230,7 @@ int main(int argc, char **argv) {
     if (what == "waits") check_setup_waits();
     else if (what == "faults") check_faults();
     else if (what == "uploads") check_uploads();
+    else if (what == "memory") check_memory();
     else return 2;
     if (!live.empty()) { at = "end"; complain("memory not given back"); }
     std::printf(bad ? "%d faults\n" : "ok\n", bad);

@@ -41,3 +41,7 @@ def test_a_failed_call_leaves_nothing_half_made(program):
 
 def test_matrices_are_uploaded_once(program):
     program("uploads")
+
+
+def test_a_small_context_is_small(program):
+    program("memory")
