@@ -42,8 +42,9 @@ struct StencilParams {
     // order 6 (uniform h)
     double c1;                   // 1/(30 h^2)
     double h2;                   // h^2
-    int zchunk;                  // z-planes per block
-    int tiles_x, tiles_y, zchunks;
+    int zchunk, zchunks;         // z-planes per block and blocks along z, of F - A x
+    int zchunk_plain, zchunks_plain;   // and of A x
+    int tiles_x, tiles_y;
     // complex k^2 (NULL for real k^2): imaginary parts of k^2 and of the order-6 field block
     const double *k2i;
     const double4 *fldi;

@@ -178,8 +178,9 @@ __global__ __launch_bounds__(NT) void k_matvec(const XT *__restrict__ x, const d
 }
 
 template <typename XT, bool KC>
-hipError_t launch_matvec_k(const StencilParams &p, const XT *x, const double *k2, const double4 *fld,
-                           const double2 *F, double2 *y, hipStream_t s) {
+hipError_t launch_matvec_k(StencilParams p, const XT *x, const double *k2, const double4 *fld, const double2 *F, double2 *y,
+                           hipStream_t s) {
+    if (!F) { p.zchunk = p.zchunk_plain; p.zchunks = p.zchunks_plain; }
     int T = p.tiles_x * p.tiles_y * p.zchunks;
     int grid = 8 * ((T + 7) / 8);
     dim3 blk(64, TY);
@@ -245,44 +246,62 @@ hipError_t launch_derived_fields_c(const double2 *k2_halo, int halo, double *k2,
     return hbad ? hipErrorInvalidValue : hipSuccess;
 }
 
-// Blocks of the step matvec that run at once (one per CU at order 6: 200 VGPRs, eight waves)
-template <int ORDER, bool KC> int matvec_resident() {
-    static const int cap = [] {
+// Blocks of a matvec that run at once (one per CU at order 6: 200 VGPRs, eight waves; two in the products y = A x of orders
+// 2 and 4) and CUs
+struct Resident { int blocks, cus; };
+template <int ORDER, bool KC, bool RESID> Resident matvec_resident() {
+    static const Resident r = [] {
         int dev = 0, cus = 0, nb = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_matvec<ORDER, true, double2, KC>, NT, 0) != hipSuccess)
-            return 256;
-        return nb * cus > 0 ? nb * cus : 256;
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_matvec<ORDER, RESID, double2, KC>, NT, 0) != hipSuccess || nb * cus <= 0)
+            return Resident{256, 256};
+        return Resident{nb * cus, cus};
     }();
-    return cap;
+    return r;
+}
+template <bool RESID> Resident matvec_resident(int order, bool kc) {
+    return order == 6 ? (kc ? matvec_resident<6, true, RESID>() : matvec_resident<6, false, RESID>())
+         : order == 4 ? (kc ? matvec_resident<4, true, RESID>() : matvec_resident<4, false, RESID>())
+                      : (kc ? matvec_resident<2, true, RESID>() : matvec_resident<2, false, RESID>());
 }
 
 // A block of zc planes streams zc + 2 of them and costs about two more to start, and blocks run in rounds of the
 // resident ones, so the length that makes rounds (zc + 4) least is taken, plus zc / 3 for the last round, which
 // finishes unevenly. Measured (order 6, one product): 32^3 11.7 -> 5.6 us (1 plane per block instead of 8), 64^3 12.3 ->
 // 6.9 (2), 128^3 33.0 -> 30.8 (16), 200^3 174 -> 152 (40 instead of 19), 250 x 190 x 217 194 -> 170 (28 instead of 20),
-// 256^3 unchanged (32; 64 planes: 270 against 253).
-void stencil_split(StencilParams *const *ps, int count) {
-    const StencilParams &p0 = *ps[0];
-    const bool kc = p0.k2i != nullptr;
-    const int cap = p0.order == 6 ? (kc ? matvec_resident<6, true>() : matvec_resident<6, false>())
-                  : p0.order == 4 ? (kc ? matvec_resident<4, true>() : matvec_resident<4, false>())
-                                  : (kc ? matvec_resident<2, true>() : matvec_resident<2, false>());
-    int nzmax = 1;
+// 256^3 unchanged (32; 64 planes: 270 against 253). Two blocks on a CU take half as long again as one and start more
+// slowly (seven planes): over twenty boxes that choice is the best length within 1 %, order 4, one product: 64^3 8.6 -> 5.5
+// us, 128^3 17.2 -> 17.0, 200^3 92.6 -> 77.2, 310 x 300 x 31 25.1 -> 23.2 (16 planes; counted as one block each, 7: 26.7).
+int matvec_chunk(StencilParams *const *ps, int count, const Resident &r) {
+    const bool shared = r.blocks > r.cus;
+    const double start = shared ? 7.0 : 4.0, slow = shared ? 1.5 : 1.0;
+    int nzmax = 1, best = 1;
     for (int i = 0; i < count; ++i) nzmax = ps[i]->nz > nzmax ? ps[i]->nz : nzmax;
-    int best = 1;
     double cost = 1e300;
     for (int zc = 1; zc <= nzmax; ++zc) {
         long long blocks = 0;
         for (int i = 0; i < count; ++i)
             blocks += (long long)ps[i]->tiles_x * ps[i]->tiles_y * ((ps[i]->nz + zc - 1) / zc);
-        const double c = (double)((blocks + cap - 1) / cap) * (zc + 4) + zc / 3.0;
+        const long long last = blocks % r.blocks;
+        const double rounds = (double)(blocks / r.blocks) * slow + (last > r.cus ? slow : last ? 1.0 : 0.0);
+        const double c = rounds * (zc + start) + zc / 3.0;
         if (c < cost) { cost = c; best = zc; }
     }
+    return best;
+}
+
+void stencil_split(StencilParams *const *ps, int count) {
+    const int order = ps[0]->order;
+    const bool kc = ps[0]->k2i != nullptr;
+    const int resid = matvec_chunk(ps, count, matvec_resident<true>(order, kc));
+    const int plain = matvec_chunk(ps, count, matvec_resident<false>(order, kc));
     for (int i = 0; i < count; ++i) {
-        ps[i]->zchunk = best < ps[i]->nz ? best : ps[i]->nz;
-        ps[i]->zchunks = (ps[i]->nz + ps[i]->zchunk - 1) / ps[i]->zchunk;
+        StencilParams &p = *ps[i];
+        p.zchunk = resid < p.nz ? resid : p.nz;
+        p.zchunks = (p.nz + p.zchunk - 1) / p.zchunk;
+        p.zchunk_plain = plain < p.nz ? plain : p.nz;
+        p.zchunks_plain = (p.nz + p.zchunk_plain - 1) / p.zchunk_plain;
     }
 }
 

@@ -142,7 +142,9 @@ __device__ __forceinline__ void matvec_tile(const XT *__restrict__ x, const doub
 
     // output coefficients of planes p-1, p, p+1 and the prefetched p+2, and F of p-1, p and the prefetched p+1, in rings
     // of four: moving them along would wait for the loads just issued (FP64 form: 256^3 253 -> 248 us, 200^3 152 -> 138
-    // us). With a complex k^2 the four-step loop spills, so there they are moved.
+    // us). With a complex k^2 the four-step loop spills, and at orders 2 and 4, which have F alone to carry, its registers
+    // leave one block on a CU instead of two (200^3, order 4: 101 us against 77), so there they are moved.
+    constexpr int STEPS = ORDER == 6 && !KC ? 4 : 2;
     FT fr[4];
     double2 Fr[4];
     fr[3] = FT{};
@@ -154,7 +156,7 @@ __device__ __forceinline__ void matvec_tile(const XT *__restrict__ x, const doub
     gload(std::integral_constant<int, 0>(), z0 - 1);
     gload(std::integral_constant<int, 1>(), z0);
     auto step = [&](auto stepc, int pz) {
-        constexpr int S = decltype(stepc)::value & 1, I = KC ? 0 : decltype(stepc)::value;
+        constexpr int S = decltype(stepc)::value & 1, I = STEPS == 2 ? 0 : decltype(stepc)::value;
         const std::integral_constant<int, S> setc;
         const int b = S;
         const FT &fm = fr[(I + 3) & 3], &f0 = fr[I], &fp = fr[(I + 1) & 3];
@@ -222,15 +224,15 @@ __device__ __forceinline__ void matvec_tile(const XT *__restrict__ x, const doub
             y[pidx] = RESID ? csub(Fm, am) : am;
         }
         am = a0; a0 = ap; ap = make_double2(0, 0);
-        if constexpr (KC) {
+        if constexpr (STEPS == 2) {
             fr[3] = fr[0]; fr[0] = fr[1]; fr[1] = fr[2];
             Fr[3] = Fr[0]; Fr[0] = Fr[1];
         }
     };
-    for (int pz = z0 - 1; pz <= z1; pz += KC ? 2 : 4) {
+    for (int pz = z0 - 1; pz <= z1; pz += STEPS) {
         step(std::integral_constant<int, 0>(), pz);
         if (pz + 1 <= z1) step(std::integral_constant<int, 1>(), pz + 1);
-        if constexpr (KC) continue;
+        if constexpr (STEPS == 2) continue;
         if (pz + 2 <= z1) step(std::integral_constant<int, 2>(), pz + 2);
         if (pz + 3 <= z1) step(std::integral_constant<int, 3>(), pz + 3);
     }
