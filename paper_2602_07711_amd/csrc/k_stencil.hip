@@ -95,7 +95,6 @@ __global__ void k_derived_c(const double2 *__restrict__ k2h, int halo, double *_
 // x and y neighbours of three, so a node costs 13 reads of f (5 at order 4), which the rows of a block share through
 // L1, instead of 25. Bound by HBM (f, k^2 and the field block read, F written: 72 B): 250 x 190 x 217, order 6,
 // 236 us (3.1 TB/s; one thread per node with 25 reads 329 us), 64^3 6.5 (8.5), 128^3 42 (60), 256^3 335 (518).
-constexpr int RHS_Y = 4;
 // order 2: the samples themselves, without the halo
 __global__ void k_rhs2(const double2 *__restrict__ f, double2 *__restrict__ F, int nx, int ny, long long n) {
     const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -104,17 +103,18 @@ __global__ void k_rhs2(const double2 *__restrict__ f, double2 *__restrict__ F, i
     const long long l = p / ((long long)nx * ny);
     F[p] = f[((l + 2) * (ny + 4) + (j + 2)) * (nx + 4) + (i + 2)];
 }
-template <int ORDER, bool KC, int ZC>
-__global__ __launch_bounds__(64 * RHS_Y) void k_rhs(const double2 *__restrict__ f, const double *__restrict__ k2,
+template <int ORDER, bool KC, int ZC, int RX>
+__global__ __launch_bounds__(256) void k_rhs(const double2 *__restrict__ f, const double *__restrict__ k2,
                                                     const double4 *__restrict__ fld, const double *__restrict__ k2i,
                                                     const double4 *__restrict__ fldi, double2 *__restrict__ F, int nx,
                                                     int ny, int nz, double h) {
-    const int tx = (nx + 63) / 64, ty = (ny + RHS_Y - 1) / RHS_Y;
+    constexpr int RY = 256 / RX;
+    const int tx = (nx + RX - 1) / RX, ty = (ny + RY - 1) / RY;
     const int T = tx * ty * ((nz + ZC - 1) / ZC);
     const int per = (T + 7) / 8;
     const int tile = (int)(blockIdx.x % 8) * per + blockIdx.x / 8;   // consecutive tiles on one XCD
     if (tile >= T) return;
-    const int io = tile % tx * 64 + threadIdx.x, jo = (tile / tx) % ty * RHS_Y + threadIdx.y;
+    const int io = tile % tx * RX + threadIdx.x, jo = (tile / tx) % ty * RY + threadIdx.y;
     const int z0 = tile / (tx * ty) * ZC, z1 = min(z0 + ZC, nz);
     const bool ok = io < nx && jo < ny;
     const int i = min(io, nx - 1), j = min(jo, ny - 1);
@@ -316,22 +316,33 @@ hipError_t launch_matvec(const StencilParams &p, const float2 *x, const double *
 }
 
 namespace {
-template <int ORDER, bool KC, int ZC>
+template <int ORDER, bool KC, int ZC, int RX>
 hipError_t rhs_launch(const StencilParams &p, const double2 *f, const double *k2, const double4 *fld, double h, double2 *F,
                       hipStream_t s) {
-    const long long T = (long long)((p.nx + 63) / 64) * ((p.ny + RHS_Y - 1) / RHS_Y) * ((p.nz + ZC - 1) / ZC);
-    hipLaunchKernelGGL((k_rhs<ORDER, KC, ZC>), dim3((unsigned)(8 * ((T + 7) / 8))), dim3(64, RHS_Y), 0, s, f, k2, fld, p.k2i,
+    constexpr int RY = 256 / RX;
+    const long long T = (long long)((p.nx + RX - 1) / RX) * ((p.ny + RY - 1) / RY) * ((p.nz + ZC - 1) / ZC);
+    hipLaunchKernelGGL((k_rhs<ORDER, KC, ZC, RX>), dim3((unsigned)(8 * ((T + 7) / 8))), dim3(RX, RY), 0, s, f, k2, fld, p.k2i,
                        p.fldi, F, p.nx, p.ny, p.nz, h);
     return hipGetLastError();
 }
-// the planes of a column follow one another at about 1 us each: long columns only where 1024 blocks remain
-template <int ORDER, bool KC>
+// Blocks of 32 x 8 nodes where a row's last 64 would be at most half used (24 nodes wide, 150 x 200, order 4: 10.5 -> 7.3 us,
+// one thread per node 9.9; 160^3, order 6: 126 -> 86). The planes of a column follow one another at about 1 us each: four
+// where 512 blocks remain (80^3, order 6: 17.3 -> 13.1 us; below, 64^3, one: 6.4 against 6.8), sixteen where 1024 do and at
+// order 6 4096, whose longer columns need the more to even out (200^3, complex k^2: 240 us with four, 287 with sixteen, one
+// thread per node 311; 256^3 464 and 451).
+template <int ORDER, bool KC, int RX>
 hipError_t rhs_columns(const StencilParams &p, const double2 *f, const double *k2, const double4 *fld, double h, double2 *F,
                        hipStream_t s) {
-    const long long planes = (long long)((p.nx + 63) / 64) * ((p.ny + RHS_Y - 1) / RHS_Y) * p.nz;
-    if (planes >= 16 * 1024) return rhs_launch<ORDER, KC, 16>(p, f, k2, fld, h, F, s);
-    if (planes >= 4 * 1024) return rhs_launch<ORDER, KC, 4>(p, f, k2, fld, h, F, s);
-    return rhs_launch<ORDER, KC, 1>(p, f, k2, fld, h, F, s);
+    constexpr int RY = 256 / RX;
+    const long long planes = (long long)((p.nx + RX - 1) / RX) * ((p.ny + RY - 1) / RY) * p.nz;
+    if (planes >= 16 * (ORDER == 6 ? 4096 : 1024)) return rhs_launch<ORDER, KC, 16, RX>(p, f, k2, fld, h, F, s);
+    if (planes >= 4 * 512) return rhs_launch<ORDER, KC, 4, RX>(p, f, k2, fld, h, F, s);
+    return rhs_launch<ORDER, KC, 1, RX>(p, f, k2, fld, h, F, s);
+}
+template <int ORDER, bool KC>
+hipError_t rhs_width(const StencilParams &p, const double2 *f, const double *k2, const double4 *fld, double h, double2 *F,
+                     hipStream_t s) {
+    return (p.nx - 1) % 64 < 32 ? rhs_columns<ORDER, KC, 32>(p, f, k2, fld, h, F, s) : rhs_columns<ORDER, KC, 64>(p, f, k2, fld, h, F, s);
 }
 }  // namespace
 
@@ -342,8 +353,8 @@ hipError_t launch_rhs(const StencilParams &p, const double2 *f, const double *k2
         hipLaunchKernelGGL(k_rhs2, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, f, F, p.nx, p.ny, n);
         return hipGetLastError();
     }
-    if (p.order == 4) return rhs_columns<4, false>(p, f, k2, fld, h, F, s);
-    return p.k2i ? rhs_columns<6, true>(p, f, k2, fld, h, F, s) : rhs_columns<6, false>(p, f, k2, fld, h, F, s);
+    if (p.order == 4) return rhs_width<4, false>(p, f, k2, fld, h, F, s);
+    return p.k2i ? rhs_width<6, true>(p, f, k2, fld, h, F, s) : rhs_width<6, false>(p, f, k2, fld, h, F, s);
 }
 
 }  // namespace helm
