@@ -894,7 +894,7 @@ helm_status setup_impl(helm_ctx **out, helm_grid g, const double h[3], const voi
     if (k2_complex && order == 6) work.take(&c.fldi, (size_t)c.n);
     work.take(&c.t1, (size_t)c.n);
     work.take(&c.t2, (size_t)c.n);
-    // the z-solve's chunk pivots of the EigT preconditioner (2 bytes per unknown), so that no later preconditioner
+    // the z-solve's chunk pivots of the EigT preconditioner (3 bytes per unknown: FP64 and FP32), so that no later preconditioner
     // call has to allocate them
     take_tpiv(c, work, &c.tpiv_eig);
     if ((st = work.commit(c)) != HELM_OK) return bail(st);

@@ -113,8 +113,8 @@ View view(helm_cnn &n, float *const *arr, int buf, int ch0) {
         }                                                                                               \
     } while (0)
 
-// 27-tap layers: direct-convolution format (forward, and the data gradient with mirrored taps); the 1-tap head:
-// implicit-GEMM format
+// 27-tap layers: direct-convolution format (forward, and the data gradient with mirrored taps); the 1-tap head: rows of
+// output channels, wt[COP][Kp]
 helm_status pack_all(helm_cnn &n) {
     CnnPackJobs p{};
     for (int l = 0; l < NL; ++l) {

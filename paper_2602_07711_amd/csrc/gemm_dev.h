@@ -267,7 +267,8 @@ __device__ __forceinline__ void gemm_tile(const TA *__restrict__ A, const TB *__
 // tile computes 64, 48 or 32 modes (BX = 64; 128, 96 or 64 for BX = 128), whichever its half still needs (with waves of
 // 32 x 32 a 200-long axis took 128 modes for its 100, now 112; columns took whole tiles per slice, 256 for its 200).
 // Bound by the matrix cores where they are many (FP64 MFMAs busy 70% of the time at 200^3), by latency where few.
-// One transform, before and after: FP64 200^3 x 168 -> 163 us, y 203 -> 163, y inverse 215 -> 161; 256^3 x 317 -> 304;
+// One transform, before and after: FP64 200^3 x 168 -> 163 us, y 203 -> 163, y inverse 215 -> 161 (four and a z-solve of 71
+// are an application of 711; under a profiler they take 175 to 182); 256^3 x 317 -> 304;
 // 32^3 5.2 -> 3.8, inverse 9.1 -> 6.3; FP32 256^3 x 159 -> 152, y inverse 136 -> 130, 64^3 inverse 10.3 -> 7.3.
 // The block matrices are zero-padded (fold_pad_sum, fold_pad_out), which makes their loads unconditional and lets the
 // data's run past the end of the half: they are clamped to the line's own values, which then meet zeros. A tile of 128

@@ -18,7 +18,8 @@
 // (checked on gfx950): A(row = lane%16, k = lane/16), B(k = lane/16, col = lane%16); accumulator register r
 // of a lane holds D(row = 4*r + lane/16, col = lane%16) for f64 and D(row = 4*(lane/16) + r, col = lane%16)
 // for f32.
-// A workgroup of 4 waves computes a BM x BN tile; each wave a (BM/2) x (BN/2) sub-tile of 16x16 blocks.
+// A workgroup of 4 waves computes a BM x BN tile of 16x16 blocks; each wave a (BM/2) x (BN/2) sub-tile of the face-ring
+// products, a quarter of the lines and all modes of a folded transform (gemm_dev.h).
 // Global->LDS staging is double buffered through registers (the next K-chunk is fetched while the current
 // one feeds the MFMAs). Tiles are mapped so that consecutive tiles run on the same XCD.
 #include "gemm_dev.h"

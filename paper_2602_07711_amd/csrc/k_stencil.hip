@@ -93,8 +93,9 @@ __global__ void k_derived_c(const double2 *__restrict__ k2h, int halo, double *_
 // h^4/90 P_h f - h^2/20 k^2 f + h^4/60 sum (k^2)_nu delta_nu f, the last with (k^2)_nu = 120 g_nu / h.
 // A thread owns a column of outputs over ZC planes and carries the centre values of five planes and the sums of the
 // x and y neighbours of three, so a node costs 13 reads of f (5 at order 4), which the rows of a block share through
-// L1, instead of 25. Bound by HBM (f, k^2 and the field block read, F written: 72 B): 250 x 190 x 217, order 6,
-// 236 us (3.1 TB/s; one thread per node with 25 reads 329 us), 64^3 6.5 (8.5), 128^3 42 (60), 256^3 335 (518).
+// L1, instead of 25. Bound by those reads through the caches (f, k^2 and the field block read, F written: 72 B):
+// 250 x 190 x 217, order 6, 227 us (3.3 TB/s; one thread per node with 25 reads 349 us), 64^3 6.2 (8.9), 128^3 34 (56),
+// 256^3 330 (526).
 // order 2: the samples themselves, without the halo
 __global__ void k_rhs2(const double2 *__restrict__ f, double2 *__restrict__ F, int nx, int ny, long long n) {
     const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
