@@ -1095,10 +1095,14 @@ helm_status helm_scale_guess(helm_ctx *ctx, const void *F_dev, void *x_dev, doub
     if (!F_dev || !x_dev) { c.err = "NULL pointer"; return HELM_EINVAL; }
     const int nb = dots_blocks(c.n);
     if (!c.sg_y) {
-        ST_TRY(dalloc(c, &c.sg_y, (size_t)c.n));
-        ST_TRY(dalloc(c, &c.sg_part, (size_t)nb * 2));
-        ST_TRY(dalloc(c, &c.sg_red, 2));
-        HIP_TRY(hipHostMalloc((void **)&c.sg_host, 2 * sizeof(double2), hipHostMallocDefault));
+        Slab slab;
+        slab.take(&c.sg_y, (size_t)c.n);
+        slab.take(&c.sg_part, (size_t)nb * 2);
+        slab.take(&c.sg_red, 2);
+        ST_TRY(slab.commit(c, [&]() -> helm_status {
+            HIP_TRY(hipHostMalloc((void **)&c.sg_host, 2 * sizeof(double2), hipHostMallocDefault));
+            return HELM_OK;
+        }));
     }
     double2 *x = (double2 *)x_dev;
     const double2 *F = (const double2 *)F_dev;

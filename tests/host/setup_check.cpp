@@ -77,7 +77,12 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
     for (size_t o = 0; o < n; o += 256) filled.insert((char *)d + o);
     return hipSuccess;
 }
-hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return fails() ? hipErrorUnknown : hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *, size_t n, hipMemcpyKind, hipStream_t) {
+    if (fails()) return hipErrorUnknown;
+    if (!inside(d)) { complain("copy to what was not allocated"); return hipErrorInvalidValue; }
+    std::memset(d, 0, n);
+    return hipSuccess;
+}
 hipError_t hipStreamSynchronize(hipStream_t) {
     if (fails()) return hipErrorUnknown;
     queued = 0;
@@ -106,7 +111,10 @@ hipError_t launch_derived_fields_c(const double2 *, int, double *k2, double *k2i
 hipError_t launch_rhs(const StencilParams &, const double2 *, const double *k2, const double4 *, double, double2 *, hipStream_t) { return launch({k2}); }
 hipError_t launch_matvec(const StencilParams &, const double2 *, const double *k2, const double4 *, const double2 *, double2 *, hipStream_t) { return launch({k2}); }
 hipError_t launch_matvec(const StencilParams &, const float2 *, const double *k2, const double4 *, const double2 *, double2 *, hipStream_t) { return launch({k2}); }
-hipError_t launch_dots(const double2 *, long long, int, const double2 *, long long, double2 *, int, double2 *, double2 *, hipStream_t) { return launch(); }
+hipError_t launch_dots(const double2 *, long long, int, const double2 *, long long, double2 *part, int, double2 *red, double2 *, hipStream_t) {
+    if (!part || !inside(part) || !red || !inside(red)) complain("a reduction without its arrays");
+    return launch();
+}
 hipError_t launch_lincomb(double2 *, const double2 *, double2, const double2 *, long long, int, const double2 *, long long, hipStream_t) { return launch(); }
 hipError_t launch_lincomb(double2 *, const double2 *, double2, const float2 *, long long, int, const double2 *, long long, hipStream_t) { return launch(); }
 hipError_t launch_lincomb_cgs(double2 *, const double2 *, long long, int, const double2 *, long long, double, hipStream_t) { return launch(); }
@@ -196,6 +204,18 @@ void check_faults() {
                     if (helm_precond_apply(c, vec_y, vec_z, kind, fp32) != HELM_OK) complain("next use failed");
                     helm_destroy(c);
                 }
+    // the work of helm_scale_guess: its vector, partials and reduced values on the device and the latter on the host
+    for (long k = 1; k <= 4; ++k) {
+        at = "scaled guess, call " + std::to_string(k);
+        fail_at = 0;
+        if (setup(&c) != HELM_OK) complain("set-up failed");
+        calls = 0, fail_at = k;
+        const helm_status st = helm_scale_guess(c, vec_y, vec_z, nullptr, nullptr);
+        if (st == HELM_OK) complain("not reported");
+        fail_at = 0;
+        (void)helm_scale_guess(c, vec_y, vec_z, nullptr, nullptr);
+        helm_destroy(c);
+    }
 }
 
 // the FP32 form of the face corrections is made from the FP64 one on the device: only the sine matrices go up again
